@@ -61,6 +61,18 @@ constexpr int kWindowHaloNull = 20;          // a single solve's with null colli
                                              // largest window's LDS for every workgroup)
 constexpr size_t kLdsWordsMax = 6144;        // 48 KB of 64-bit tallies per workgroup
 constexpr int kLdsWallsMax = 1024;
+// A tile's particles are split over several workgroups where the tiles alone
+// leave compute units idle (a 100-cell film has 15): up to kSplitTarget
+// workgroups per launch (four per compute unit), of at least kSplitMin
+// particles (one per lane) and of one particle per kSplitWords words of LDS
+// window, which every workgroup clears and flushes.  Measured: film of 100
+// cells, 1e5 particles, particle step 658 -> 30 us (512 / 2048 particles at
+// least: 27 / 38 us, but the two-time film's solve 1.85 ms against 2.2 / 3.0);
+// 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with null collisions,
+// 1e6 particles 1188 -> 729 us (one particle per 4 or 2 words: 806 / 1182).
+constexpr int kSplitTarget = 1024;
+constexpr int kSplitMin = 256;
+constexpr int kSplitWords = 8;
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -267,6 +279,27 @@ int scale_exponent(const iugkp_problem *p, double tau_min, const std::vector<dou
   return 62 - ((mant == 0.5) ? e - 1 : e);
 }
 
+// Split the tiles' particles over `target` workgroups or more where the tiles
+// alone are fewer.
+void split_tiles(InstHost &ih, int target)
+{
+  const Inst &d = ih.d;
+  const double all = static_cast<double>(d.m.n_emit) * d.N;
+  const double chunk = std::max({all / target, static_cast<double>(kSplitMin),
+                                 static_cast<double>(ih.lds_bytes / sizeof(long long)) / kSplitWords});
+  std::vector<TileDesc> out;
+  for (const TileDesc &t : ih.tiles) {
+    const double p = static_cast<double>(t.kind == 0 ? t.ex * t.ey : t.ex) * d.N;
+    const int parts = std::max(1, static_cast<int>(p / chunk + 0.5));
+    for (int k = 0; k < parts; ++k) {
+      out.push_back(t);
+      out.back().part = k;
+      out.back().parts = parts;
+    }
+  }
+  ih.tiles.swap(out);
+}
+
 // Tile table and LDS window: the whole domain when its tallies fit in LDS,
 // otherwise a window of the tile plus a margin, placed inside the domain.
 // Emitter tiles of edge x edge cells (and wall segments of edge faces), each
@@ -277,7 +310,7 @@ void plan_tiles(InstHost &ih, int edge = kTileX, int halo = kWindowHalo)
   Inst &d = ih.d;
   const Mesh &m = d.m;
   d.lds_walls = (m.n_b <= kLdsWallsMax) ? 1 : 0;
-  const size_t whole = iugkp::window_words(m.nx, m.ny, d.has_null, d.lds_walls, m.n_b);
+  const size_t whole = iugkp::window_words(m.dim, m.nx, m.ny, d.has_null, d.lds_walls, m.n_b);
   const bool whole_domain = whole <= kLdsWordsMax;
   if (whole_domain) {
     d.WX = m.nx;
@@ -296,6 +329,7 @@ void plan_tiles(InstHost &ih, int edge = kTileX, int halo = kWindowHalo)
   for (int ty = 0; ty < m.ny; ty += edge)
     for (int tx = 0; tx < m.nx; tx += edge) {
       TileDesc t{};
+      t.parts = 1;
       t.kind = 0;
       t.x0 = tx;
       t.y0 = ty;
@@ -309,6 +343,7 @@ void plan_tiles(InstHost &ih, int edge = kTileX, int halo = kWindowHalo)
   auto wall = [&](int b_first, int count, int along_x, int side_hi) {
     for (int s0 = 0; s0 < count; s0 += edge) {
       TileDesc t{};
+      t.parts = 1;
       t.kind = 1;
       t.x0 = b_first + s0;
       t.ex = std::min(edge, count - s0);
@@ -332,7 +367,8 @@ void plan_tiles(InstHost &ih, int edge = kTileX, int halo = kWindowHalo)
     wall(2 * m.ny, m.nx, 1, 0);
     wall(2 * m.ny + m.nx, m.nx, 1, 1);
   }
-  ih.lds_bytes = iugkp::window_words(d.WX, d.WY, d.has_null, d.lds_walls, m.n_b) * sizeof(long long);
+  ih.lds_bytes =
+      iugkp::window_words(m.dim, d.WX, d.WY, d.has_null, d.lds_walls, m.n_b) * sizeof(long long);
 }
 
 // Persistent population: N particles per cell in equilibrium (the cell's
@@ -785,6 +821,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   d.cg_max = o->cg_max_iters;
   d.F = scale_exponent(p, tmin, wall, T0, src);
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
+  if (multi_cg) split_tiles(ih, kSplitTarget);
 
 #define ALLOC(ptr, n) \
   if (ih.alloc(&(ptr), (n)) != hipSuccess) return fail(IUGKP_E_NOMEM, "hipMalloc failed");
@@ -1152,6 +1189,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.n_bands = K;
     d.Gs = nullptr;
     plan_tiles(ih);
+    split_tiles(ih, std::max(1, kSplitTarget / K));
     // row stripes for a band's face-tallied iterations when its free paths
     // reach half the domain's height (and 7 cells): a band with shorter ones
     // has long chains of null collisions wherever its relaxation time is

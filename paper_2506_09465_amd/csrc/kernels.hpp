@@ -246,7 +246,8 @@ __global__ void prepare_kernel(const Inst *__restrict__ insts, int faces_mode, i
 // The particle step.
 //
 // Work decomposition: workgroup = one emitter tile (a TX x TY block of cells, or
-// a segment of one wall) and all N particles of its emitters; particle p of the
+// a segment of one wall) and all N particles of its emitters, or a share of
+// them where a launch's tiles are fewer than the device needs; particle p of the
 // tile belongs to emitter p mod n_e (emitters run fastest, so the lanes of a
 // wavefront start in different cells) and has index k = p / n_e within it.
 // Each lane flies its particles one after the other, which evens out the
@@ -268,6 +269,7 @@ struct TileDesc {
   int x0, y0;      // cell tile: first cell; wall segment: first wall index in x0
   int ex, ey;      // cell tile: extent; wall segment: face count in ex
   int wx0, wy0;    // window origin (cells)
+  int part, parts; // this workgroup's share of the tile's particles: part of parts
 };
 
 __device__ __forceinline__ void atom_add(long long *a, long long v)
@@ -286,11 +288,13 @@ struct Window {
 };
 
 // LDS layout of one window: D [WY][WX], W [WY][WX] (null collisions only),
-// By [WY+1][WX], dB [WY+2][WX], B [n_b] (if kept in LDS).
-__host__ __device__ inline size_t window_words(int WX, int WY, int has_null, int lds_walls, int n_b)
+// in 2D By [WY+1][WX] and dB [WY+2][WX], B [n_b] (if kept in LDS).
+__host__ __device__ inline size_t window_words(int dim, int WX, int WY, int has_null,
+                                               int lds_walls, int n_b)
 {
-  return static_cast<size_t>(WX) * WY * (has_null ? 2 : 1) + static_cast<size_t>(WX) * (WY + 1) +
-         static_cast<size_t>(WX) * (WY + 2) + (lds_walls ? n_b : 0);
+  const size_t row = static_cast<size_t>(WX);
+  return row * WY * (has_null ? 2 : 1) + (dim == 2 ? row * (WY + 1) + row * (WY + 2) : 0) +
+         (lds_walls ? n_b : 0);
 }
 
 // The flight of particle k of emitter e carrying q: sampling (start point,
@@ -742,12 +746,13 @@ __global__ __launch_bounds__(BS) void march_kernel(const Inst *__restrict__ inst
     win.W = a.has_null ? p : nullptr;
     if (a.has_null) p += win.WX * win.WY;
     win.By = p;
-    p += win.WX * (win.WY + 1);
+    if (m.dim == 2) p += win.WX * (win.WY + 1);
     win.dB = p;
-    p += win.WX * (win.WY + 2);
+    if (m.dim == 2) p += win.WX * (win.WY + 2);
     win.B = in.lds_walls ? p : nullptr;
   }
-  const int nwords = static_cast<int>(window_words(win.WX, win.WY, a.has_null, in.lds_walls, m.n_b));
+  const int nwords = static_cast<int>(
+      window_words(m.dim, win.WX, win.WY, a.has_null, in.lds_walls, m.n_b));
   for (int i = threadIdx.x; i < nwords; i += BS) lds_words[i] = 0;
   if (threadIdx.x < 3) s_cnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_next = 0;
@@ -784,9 +789,17 @@ __global__ __launch_bounds__(BS) void march_kernel(const Inst *__restrict__ inst
       atom_add(&a.B[b], v);
   };
 
-  const FlyIn fa = {a.m, a.lam_min, a.slot, a.key0, a.key1, a.faces, a.has_null, a.ratio, in.e_off};
+  // (1D has no y faces and its x faces follow from the balance: nothing to
+  // tally on the way, so its flights take the closed form in every iteration)
+  const FlyIn fa = {a.m, a.lam_min, a.slot, a.key0, a.key1, m.dim == 2 ? a.faces : 0, a.has_null,
+                    a.ratio, in.e_off};
   const int n_e = (td.kind == 0) ? td.ex * td.ey : td.ex;
-  const uint32_t P = static_cast<uint32_t>(n_e) * a.N;
+  // this workgroup's particles [P0, P) of the tile's n_e N
+  const unsigned long long P_tile = static_cast<unsigned long long>(n_e) * a.N;
+  const uint32_t P0 = static_cast<uint32_t>(P_tile * static_cast<unsigned>(td.part) /
+                                            static_cast<unsigned>(td.parts));
+  const uint32_t P = static_cast<uint32_t>(P_tile * (static_cast<unsigned>(td.part) + 1u) /
+                                           static_cast<unsigned>(td.parts));
   unsigned long long n_fl = 0, n_seg = 0, n_cross = 0;
   int bad = 0;
   // particle p of the tile: emitter (tile order) fastest
@@ -802,7 +815,7 @@ __global__ __launch_bounds__(BS) void march_kernel(const Inst *__restrict__ inst
   };
   auto add_w = [&](int cx, int cy, long long v) { add_cell(win.W, a.W, cx, cy, v); };
   auto add_d = [&](int cx, int cy, long long v) { add_cell(win.D, a.D, cx, cy, v); };
-  if (!(EV && in.estimator) && a.has_null && P >= kRefillMinPer * BS) {
+  if (!(EV && in.estimator) && a.has_null && P - P0 >= kRefillMinPer * BS) {
     // Null collisions make a flight a chain of segments of geometric length:
     // each lane runs its flight a segment per trip, and the idle lanes of a
     // wavefront claim the tile's next particles (one LDS atomic per
@@ -824,7 +837,8 @@ __global__ __launch_bounds__(BS) void march_kernel(const Inst *__restrict__ inst
           uint32_t first = 0;
           if (lane == lead) first = atomicAdd(&s_next, static_cast<uint32_t>(__popcll(want)));
           first = static_cast<uint32_t>(__shfl(static_cast<int>(first), lead, 64));
-          const uint32_t p = first + static_cast<uint32_t>(__popcll(want & ((1ull << lane) - 1ull)));
+          const uint32_t p =
+              P0 + first + static_cast<uint32_t>(__popcll(want & ((1ull << lane) - 1ull)));
           if (p >= P) break;
           uint32_t e, k;
           emitter_of(p, e, k);
@@ -844,7 +858,7 @@ __global__ __launch_bounds__(BS) void march_kernel(const Inst *__restrict__ inst
       if (live) live = flight_segment(fa, f, add_diff, add_yface, add_wall, add_w, add_d, n_seg, n_cross);
     }
   } else
-  for (uint32_t p = threadIdx.x; p < P; p += BS) {
+  for (uint32_t p = P0 + threadIdx.x; p < P; p += BS) {
     uint32_t e, k;
     emitter_of(p, e, k);
     const long long q = a.base[e] + ((k < a.rem[e]) ? 1 : 0);
