@@ -44,8 +44,16 @@ int fail(int code, const std::string &msg)
       return fail(IUGKP_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(_e));   \
   } while (0)
 
+constexpr int kCgGroupMax = 256;             // workgroups of a group, at most one per CU
 constexpr int kCgGridMax = 64;               // workgroups of one CG group (barrier arrivals)
-constexpr int kCgWavesDefault = 8;           // tree blocks per CG workgroup of a single solve
+// tree blocks per CG workgroup of a single solve: a mesh of up to kCgAloneMax
+// blocks takes one workgroup (5 blocks 297 us per solve against 356 on two;
+// 12 blocks 6.9 ms against 6.6 on three), others kCgWavesMin, and up to
+// kCgWavesDefault where that keeps the group within one XCD's compute units
+// (28 blocks, four against eight each: 923 / 1013 us; 256 blocks, four each on
+// two workgroups per CU against eight: 4.0 / 3.4 ms)
+constexpr int kCgAloneMax = 8, kCgWavesMin = 4;
+constexpr int kCgWavesDefault = 8;
 constexpr int kBarStride = 64;               // batched CG barriers 256 bytes apart (no shared lines)
 constexpr double kStripeMinCells = 7.0;      // row stripes for face tallies when lambda_min >= 7 cells
 constexpr int kStripeBlock = 1024;           // threads of a stripe workgroup
@@ -76,10 +84,11 @@ constexpr int kSplitWords = 8;
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
-void *cg_kernel_for(int reg)
+void *cg_kernel_for(int reg, int G)
 {
-  return reg ? reinterpret_cast<void *>(iugkp::cg_kernel<true>)
-             : reinterpret_cast<void *>(iugkp::cg_kernel<false>);
+  return reg ? (G == 1 ? reinterpret_cast<void *>(iugkp::cg_one_kernel)
+                       : reinterpret_cast<void *>(iugkp::cg_kernel))
+             : reinterpret_cast<void *>(iugkp::cg_global_kernel);
 }
 
 // Launch shape of the single-solve CG on a mesh: a group of at most
@@ -87,8 +96,16 @@ void *cg_kernel_for(int reg)
 // cg_waves tree blocks each (0: the default); the register form when every
 // block has its own wave and the rows fit in LDS (cg_waves < 0 forces the
 // global-memory form).
+// Workgroups to launch for a group of G: kXcds times as many where one XCD
+// can hold the group, so that it may run there.
+int group_launch(int G, int per_cu, int nb)
+{
+  return (G > 1 && nb <= iugkp::kTree && G <= per_cu * iugkp::kCusPerXcd) ? iugkp::kXcds * G : G;
+}
+
 struct CgPlan {
   int grid = 1, tb = 1, reg = 1, threads = 64, per_cu = 1;
+  int launch = 1;              // workgroups launched (more than grid: elect_group)
   size_t lds = 0;
 };
 
@@ -99,10 +116,14 @@ int plan_cg(const iugkp::Mesh &m, int cg_waves, CgPlan &out)
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const int nbt = cdiv(m.n_cells, iugkp::kTree);
   const int hw = (m.dim == 2) ? m.nx : 1;
-  const int want = cg_waves != 0 ? std::abs(cg_waves) : kCgWavesDefault;
+  // (a mesh that one workgroup's waves hold takes one: nothing is exchanged)
+  const int want = cg_waves != 0 ? std::abs(cg_waves)
+                   : nbt <= kCgAloneMax ? kCgAloneMax
+                   : std::min(kCgWavesDefault, std::max(kCgWavesMin, cdiv(nbt, iugkp::kCusPerXcd)));
   int G = std::max(1, std::min(std::min(cdiv(nbt, want), kCgGridMax), n_cu));
   // more workgroups rather than the global form, while one per CU suffices
-  if (cdiv(nbt, G) > iugkp::kCgWavesMax && cdiv(nbt, iugkp::kCgWavesMax) <= n_cu)
+  if (cdiv(nbt, G) > iugkp::kCgWavesMax &&
+      cdiv(nbt, iugkp::kCgWavesMax) <= std::min(n_cu, kCgGroupMax))
     G = cdiv(nbt, iugkp::kCgWavesMax);
   const int TB = cdiv(nbt, G);
   G = cdiv(nbt, TB);
@@ -111,9 +132,10 @@ int plan_cg(const iugkp::Mesh &m, int cg_waves, CgPlan &out)
   int reg = (cg_waves >= 0 && TB <= iugkp::kCgWavesMax && lds <= kCgLdsMax) ? 1 : 0;
   if (!reg) lds = 2 * static_cast<size_t>(hw) * sizeof(double);
   if (lds > kCgLdsMax) return fail(IUGKP_E_INVALID_ARG, "mesh rows too long for the Newton CG");
+  lds += sizeof(double);       // (the register form's zero slot)
   const int threads = 64 * (reg ? TB : std::min(TB, iugkp::kCgWavesMax));
   int per_cu = 0;
-  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cg_kernel_for(reg), threads, lds));
+  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cg_kernel_for(reg, G), threads, lds));
   if (per_cu < 1 || G > per_cu * n_cu)
     return fail(IUGKP_E_DEVICE, "CG workgroups cannot all be resident");
   out.grid = G;
@@ -122,6 +144,7 @@ int plan_cg(const iugkp::Mesh &m, int cg_waves, CgPlan &out)
   out.threads = threads;
   out.lds = lds;
   out.per_cu = per_cu;
+  out.launch = reg ? group_launch(G, per_cu, nbt) : G;
   return IUGKP_OK;
 }
 
@@ -148,7 +171,7 @@ struct InstHost {
   // multi-workgroup CG (single solves)
   double *cg_pub = nullptr, *cg_mpart = nullptr;
   unsigned int *cg_barrier = nullptr;
-  int cg_grid = 1, cg_tb = 1, cg_reg = 1, cg_threads = 64;
+  int cg_grid = 1, cg_launch = 1, cg_tb = 1, cg_reg = 1, cg_threads = 64;
   size_t cg_lds = 0;
   // the CG group's footprint in compute units (workgroups / resident ones per
   // CU): grouped stepping keeps the CGs in flight within the device
@@ -868,7 +891,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
     ALLOC(d.cg_s, nc);
     ALLOC(ih.cg_pub, 6 * static_cast<size_t>(nc));
     ALLOC(ih.cg_mpart, 4 * static_cast<size_t>(nbt));
-    ALLOC(ih.cg_barrier, 2);
+    ALLOC(ih.cg_barrier, iugkp::kGroupWords + kCgGroupMax * iugkp::kCgFlagStep);
     d.cg_pub = ih.cg_pub;
     d.cg_mpart = ih.cg_mpart;
     d.cg_barrier = ih.cg_barrier;
@@ -949,6 +972,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
       CgPlan cp;
       if ((rc = plan_cg(m, o->cg_waves, cp))) return rc;
       ih.cg_grid = cp.grid;
+      ih.cg_launch = cp.launch;
       ih.cg_tb = cp.tb;
       ih.cg_reg = cp.reg;
       ih.cg_threads = cp.threads;
@@ -1522,7 +1546,9 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
   ca.max_iters = ih.d.cg_max;
   ca.barrier = ih.cg_barrier;
   ca.sc = sc;
-  iugkp::zero_u32_kernel<<<1, 64, 0, s>>>(ih.cg_barrier, 2);
+  ca.flags = ih.cg_barrier + iugkp::kGroupWords;
+  const int words = iugkp::kGroupWords + ih.cg_grid * iugkp::kCgFlagStep;
+  iugkp::zero_u32_kernel<<<cdiv(words, 256), 256, 0, s>>>(ih.cg_barrier, words);
   if (ev_a) HIP_TRY(hipEventRecord(ev_a, s));
   // Every workgroup must become resident for the group barrier.  Set-up
   // checked that the group fits the device; a plain launch (not a
@@ -1532,8 +1558,9 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
   // dispatched as other kernels' workgroups retire (none of them waits for the
   // CG), and a wait beyond the barrier's spin limit ends the solve with an
   // error instead of hanging.
-  void *args[] = {&ca};
-  HIP_TRY(hipLaunchKernel(cg_kernel_for(ih.cg_reg), dim3(ih.cg_grid),
+  int group = ih.cg_grid;
+  void *args[] = {&ca, &group};
+  HIP_TRY(hipLaunchKernel(cg_kernel_for(ih.cg_reg, ih.cg_grid), dim3(ih.cg_launch),
                                      dim3(ih.cg_threads), args, ih.cg_lds, s));
   if (ev_b) HIP_TRY(hipEventRecord(ev_b, s));
   return IUGKP_OK;
@@ -2281,7 +2308,8 @@ size_t diffusion_bytes(const Mesh &m)
   auto up = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t nc = m.n_cells, nbt = cdiv(m.n_cells, iugkp::kTree);
   return up(8 * static_cast<size_t>(m.n_fx)) + up(8 * std::max<size_t>(m.n_fy, 1)) +
-         5 * up(8 * nc) + up(8 * 6 * nc) + up(8 * 4 * nbt) + up(8) + up(sizeof(DevScalars));
+         5 * up(8 * nc) + up(8 * 6 * nc) + up(8 * 4 * nbt) +
+         up(4 * iugkp::kGroupWords) + up(sizeof(DevScalars));
 }
 
 DiffusionBufs carve_diffusion(const Mesh &m, unsigned char *base)
@@ -2304,7 +2332,7 @@ DiffusionBufs carve_diffusion(const Mesh &m, unsigned char *base)
   b.gs = reinterpret_cast<double *>(take(8 * nc));
   b.pub = reinterpret_cast<double *>(take(8 * 6 * nc));
   b.part = reinterpret_cast<double *>(take(8 * 4 * nbt));
-  b.barrier = reinterpret_cast<unsigned int *>(take(8));
+  b.barrier = reinterpret_cast<unsigned int *>(take(4 * iugkp::kGroupWords));
   b.sc = reinterpret_cast<DevScalars *>(take(sizeof(DevScalars)));
   return b;
 }
@@ -2363,9 +2391,16 @@ int diffusion_run(const Mesh &m, const CgPlan &cp, const DiffusionBufs &q, doubl
   ca.max_iters = max_iters;
   ca.barrier = q.barrier;
   ca.sc = q.sc;
-  iugkp::zero_u32_kernel<<<1, 64, 0, s>>>(q.barrier, 2);
-  void *args[] = {&ca};
-  HIP_TRY(hipLaunchKernel(cg_kernel_for(cp.reg), dim3(cp.grid), dim3(cp.threads), args, cp.lds, s));
+  // (the register form keeps its state in registers: the state arrays hold
+  // its barrier words; a group has at most one workgroup per 256 cells)
+  ca.flags = reinterpret_cast<unsigned int *>(q.gr);
+  iugkp::zero_u32_kernel<<<1, 64, 0, s>>>(q.barrier, iugkp::kGroupWords);
+  if (cp.reg && cp.grid > 1)
+    iugkp::zero_u32_kernel<<<cdiv(cp.grid * iugkp::kCgFlagStep, 256), 256, 0, s>>>(
+        ca.flags, cp.grid * iugkp::kCgFlagStep);
+  int group = cp.grid;
+  void *args[] = {&ca, &group};
+  HIP_TRY(hipLaunchKernel(cg_kernel_for(cp.reg, cp.grid), dim3(cp.launch), dim3(cp.threads), args, cp.lds, s));
   HIP_TRY(hipGetLastError());
   int head[2] = {0, 0};      // cg_iters, cg_status
   HIP_TRY(hipMemcpyAsync(head, &q.sc->cg_iters, sizeof(head), hipMemcpyDeviceToHost, s));
@@ -2984,6 +3019,7 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
         free_batch(b);
         return fail(IUGKP_E_INVALID_ARG, "mesh rows too long for the Newton CG");
       }
+      lds += sizeof(double);   // (the register form's zero slot)
       b->cg_G[i] = G;
       b->cg_tb[i] = TB | (reg ? iugkp::kCgJobReg : 0);
       b->pool.lds = std::max(b->pool.lds, lds);

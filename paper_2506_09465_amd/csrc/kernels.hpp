@@ -2260,9 +2260,21 @@ __global__ void newton_diag_kernel(Mesh m, const double *gx, const double *gy, d
 // the abort flag; every workgroup then leaves its next barrier at once and the
 // kernel reports the failure, so a broken barrier can never hang the device.
 // ---------------------------------------------------------------------------
+// Where a solve's workgroups run, which decides how far a store has to go to
+// be seen by the others: anywhere on the device (agent-scope stores, written
+// through to the device's coherence point), all on one XCD (stores that stop
+// in its L2, which agent-scope loads of the same XCD hit: 94 against 276 ns
+// until such a store has completed, about 0.23 against 0.5 us from a store to
+// a poll that sees it), or one workgroup (its CU's L1).
+enum : int { kSpanDevice = 0, kSpanXcd = 1, kSpanOne = 2 };
+
+template <int SPAN>
 __device__ __forceinline__ void xst(double *p, double v)
 {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (SPAN == kSpanDevice)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ double xld(const double *p)
@@ -2307,6 +2319,68 @@ __device__ __forceinline__ bool grid_barrier(unsigned int *counter, unsigned int
 }
 
 // ---------------------------------------------------------------------------
+// The workgroups of a solve's group, elected on the device.  A launch of
+// kXcds G workgroups (the dispatcher deals them out to the XCDs in turn) gives
+// every XCD a chance to hold a whole group: the first XCD on which G of them
+// have arrived takes the solve and the others leave.  Where none gets there
+// within kElectTicks (other kernels hold CUs), the first G to arrive anywhere
+// take it, with device-wide stores.  Members are resident when they are
+// chosen, so no group waits for a workgroup that has not been dispatched; an
+// election without G arrivals ends after the barrier's spin limit.
+// words (zero at the launch): [2] the choice, [3] arrivals, [4 + xcc] arrivals
+// on that XCD; [0] and [1] are the group barrier's.
+// ---------------------------------------------------------------------------
+constexpr int kXcds = 8;
+constexpr int kCusPerXcd = 32;
+constexpr int kGroupWords = 32;
+constexpr unsigned int kElectSpread = 0x100u, kElectFailed = 0x200u;
+constexpr unsigned long long kElectTicks = 2000;     // 20 us of the 100 MHz clock
+
+__device__ __forceinline__ bool elect_group(unsigned int *words, int G, int &rank, bool &one_xcd,
+                                            DevScalars *sc)
+{
+  __shared__ int s_rank, s_one;
+  if (threadIdx.x == 0) {
+    unsigned int xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    xcc &= 15u;
+    const int ta = static_cast<int>(__hip_atomic_fetch_add(words + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const int tx = static_cast<int>(__hip_atomic_fetch_add(words + 4 + xcc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    auto propose = [&](unsigned int v) {
+      unsigned int none = 0u;
+      return __hip_atomic_compare_exchange_strong(words + 2, &none, v, __ATOMIC_RELAXED,
+                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (tx == G - 1) propose(1u + xcc);
+    const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
+    unsigned int choice = 0u;
+    long spins = 0;
+    for (;;) {
+      choice = __hip_atomic_load(words + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (choice) break;
+      if (static_cast<unsigned long long>(wall_clock64()) - t0 > kElectTicks &&
+          __hip_atomic_load(words + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
+              static_cast<unsigned int>(G))
+        propose(kElectSpread);
+      if (++spins > kBarrierSpinLimit && propose(kElectFailed)) {
+        sc->cg_iters = 0;
+        sc->cg_status = -3;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    int r = -1;
+    if (choice == kElectSpread) r = ta < G ? ta : -1;
+    else if (choice == 1u + xcc) r = tx < G ? tx : -1;
+    s_rank = r;
+    s_one = choice != kElectSpread;
+  }
+  __syncthreads();
+  rank = s_rank;
+  one_xcd = s_one != 0;
+  return rank >= 0;
+}
+
+// ---------------------------------------------------------------------------
 // Conjugate gradients, single-reduction form (Chronopoulos & Gear 1989):
 //   x = 0, r = b, w = A r, gamma = (r, r), delta = (w, r), alpha = gamma / delta
 //   repeat: p = r + beta p, s = w + beta s (p = r, s = w the first time)
@@ -2332,6 +2406,8 @@ __device__ __forceinline__ bool grid_barrier(unsigned int *counter, unsigned int
 // ---------------------------------------------------------------------------
 constexpr int kCgWavesMax = 12;        // 768 threads: about 170 VGPRs per lane for the register form
 constexpr int kCgThreadsMax = 64 * kCgWavesMax;
+constexpr int kCgShareBlocks = 64;     // block sums of an XCD's group loaded by shares beyond this
+constexpr int kCgFlagStep = 32;        // words between two workgroups' device-wide barrier words
 
 struct CGArgs {
   Mesh m;
@@ -2343,7 +2419,8 @@ struct CGArgs {
   int TB;                    // tree blocks per workgroup
   double tol2;
   int max_iters;
-  unsigned int *barrier;     // [2], zero at the start of the solve
+  unsigned int *barrier;     // [kGroupWords], zero at the start of the solve
+  unsigned int *flags;       // [G] register form's barrier words, zero at the start
   DevScalars *sc;
 };
 
@@ -2380,19 +2457,7 @@ __device__ __forceinline__ double apply_cell(const Mesh &m, const CellCoef &k, i
   return acc;
 }
 
-// The same with the neighbour tests precomputed: bits 0..3 of nbm = left,
-// right, down, up neighbour present.
-template <class Get>
-__device__ __forceinline__ double apply_masked(const CellCoef &k, int c, int nx, unsigned nbm, Get v)
-{
-  double acc = k.d * v(c);
-  if (nbm & 1u) acc = acc - k.l * v(c - 1);
-  if (nbm & 2u) acc = acc - k.r * v(c + 1);
-  if (nbm & 4u) acc = acc - k.dn * v(c - nx);
-  if (nbm & 8u) acc = acc - k.up * v(c + nx);
-  return acc;
-}
-
+// bits 0..3: left, right, down, up neighbour present
 __device__ __forceinline__ unsigned neighbour_mask(const Mesh &m, int c)
 {
   const int iy = c / m.nx, ix = c - iy * m.nx;
@@ -2502,12 +2567,11 @@ __device__ __forceinline__ void group_tree_pairs(const double *part, int nb, dou
 }
 
 // The solve as seen by one workgroup of rank `rank` in a group of G resident
-// workgroups sharing the barrier counter a.barrier.  REG selects the register
-// form (requires a.TB <= blockDim.x / 64).
-template <bool REG>
-__device__ void cg_run(const CGArgs &a, int rank, int G)
+// workgroups sharing the barrier counter a.barrier: the global form (rows too
+// long for the register form's LDS staging, or on request).
+__device__ void cg_global_run(const CGArgs &a, int rank, int G)
 {
-  extern __shared__ double stage[];       // r on [h0, h1) (register form) or on the halo
+  extern __shared__ double stage[];       // r on the halo
   __shared__ double red[2 * kTree];        // chunk sums when nb > 256
   unsigned int epoch = 0;
   const Mesh &m = a.m;
@@ -2524,102 +2588,44 @@ __device__ void cg_run(const CGArgs &a, int rank, int G)
   const bool nb_lo = c0 > 0, nb_hi = c1 < n;       // a neighbour below / above exists
   double *const pub[2] = {a.pub, a.pub + 3 * static_cast<size_t>(n)};
   double *const part[2] = {a.part, a.part + 2 * static_cast<size_t>(nb)};
-  const int tbr = tb0 + wave;                       // the register form's block
-  const bool own = REG && wave < a.TB && tbr < tb1;
 
   auto halo_cell = [&](int i) { return i < nlo ? h0 + i : c1 + (i - nlo); };
   auto published = [&](int c) { return (nb_lo && c < c0 + hw) || (nb_hi && c >= c1 - hw); };
   auto rget = [&](int c) -> double {
-    if constexpr (REG) {
-      return stage[c - h0];
-    } else {
-      if (c < c0) return stage[c - h0];
-      if (c >= c1) return stage[nlo + (c - c1)];
-      return a.gr[c];
-    }
+    if (c < c0) return stage[c - h0];
+    if (c >= c1) return stage[nlo + (c - c1)];
+    return a.gr[c];
   };
-
-  double xr[4], rr[4], wr[4], pr[4], sr[4];
-  CellCoef kr[4];
-  // the first kHaloRegs halo slots of this thread: published (r, w, s), loaded
-  // right after the barrier together with the block sums
-  constexpr int kHaloRegs = 1;
-  double hr[kHaloRegs], hwv[kHaloRegs], hs[kHaloRegs];
-  auto preload_halo = [&](const double *pp) {
-#pragma unroll
-    for (int k = 0; k < kHaloRegs; ++k) {
-      const int i = threadIdx.x + k * blockDim.x;
-      hr[k] = 0.0;
-      hwv[k] = 0.0;
-      hs[k] = 0.0;
-      if (i < nhalo) {
-        const int c = halo_cell(i);
-        hr[k] = xld(&pp[c]);
-        hwv[k] = xld(&pp[n + c]);
-        hs[k] = xld(&pp[2 * static_cast<size_t>(n) + c]);
-      }
-    }
-  };
-  unsigned cm = 0u;        // register form: per cell q, bits 5q..5q+3 neighbours, 5q+4 published
 
   // w = A r on the own cells, block sums of (r, r) and (w, r) into pt, (r, w, s)
   // of the published cells into pn
   auto apply_pass = [&](double *pn, double *pt, bool start) {
-    if constexpr (REG) {
-      if (!own) return;
+    for (int tb = tb0 + wave; tb < tb1; tb += nw) {
       double g[4], d[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int c = tbr * kTree + lane + 64 * q;
+        const int c = tb * kTree + lane + 64 * q;
         g[q] = 0.0;
         d[q] = 0.0;
         if (c < n) {
-          const unsigned bits = cm >> (5 * q);
-          const double wv = apply_masked(kr[q], c, m.nx, bits, rget);
-          wr[q] = wv;
-          g[q] = rr[q] * rr[q];
-          d[q] = wv * rr[q];
-          if (bits & 16u) {
-            xst(&pn[c], rr[q]);
-            xst(&pn[n + c], wv);
-            xst(&pn[2 * static_cast<size_t>(n) + c], sr[q]);
+          const CellCoef k = load_coef(m, a.gx, a.gy, a.diag, c);
+          const double wv = apply_cell(m, k, c, rget);
+          a.gw[c] = wv;
+          const double rv = a.gr[c];
+          g[q] = rv * rv;
+          d[q] = wv * rv;
+          if (published(c)) {
+            xst<kSpanDevice>(&pn[c], rv);
+            xst<kSpanDevice>(&pn[n + c], wv);
+            xst<kSpanDevice>(&pn[2 * static_cast<size_t>(n) + c], start ? 0.0 : a.gs[c]);
           }
         }
       }
       const double sg = wave_tree256(g[0], g[1], g[2], g[3]);
       const double sd = wave_tree256(d[0], d[1], d[2], d[3]);
       if (lane == 0) {
-        xst(&pt[2 * tbr], sg);
-        xst(&pt[2 * tbr + 1], sd);
-      }
-    } else {
-      for (int tb = tb0 + wave; tb < tb1; tb += nw) {
-        double g[4], d[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int c = tb * kTree + lane + 64 * q;
-          g[q] = 0.0;
-          d[q] = 0.0;
-          if (c < n) {
-            const CellCoef k = load_coef(m, a.gx, a.gy, a.diag, c);
-            const double wv = apply_cell(m, k, c, rget);
-            a.gw[c] = wv;
-            const double rv = a.gr[c];
-            g[q] = rv * rv;
-            d[q] = wv * rv;
-            if (published(c)) {
-              xst(&pn[c], rv);
-              xst(&pn[n + c], wv);
-              xst(&pn[2 * static_cast<size_t>(n) + c], start ? 0.0 : a.gs[c]);
-            }
-          }
-        }
-        const double sg = wave_tree256(g[0], g[1], g[2], g[3]);
-        const double sd = wave_tree256(d[0], d[1], d[2], d[3]);
-        if (lane == 0) {
-          xst(&pt[2 * tb], sg);
-          xst(&pt[2 * tb + 1], sd);
-        }
+        xst<kSpanDevice>(&pt[2 * tb], sg);
+        xst<kSpanDevice>(&pt[2 * tb + 1], sd);
       }
     }
   };
@@ -2633,35 +2639,15 @@ __device__ void cg_run(const CGArgs &a, int rank, int G)
   };
 
   // ---- start: x = 0, r = b, w = A r
-  if constexpr (REG) {
-    for (int i = threadIdx.x; i < h1 - h0; i += blockDim.x) stage[i] = a.b[h0 + i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = tbr * kTree + lane + 64 * q;
-      xr[q] = 0.0;
-      pr[q] = 0.0;
-      sr[q] = 0.0;
-      wr[q] = 0.0;
-      rr[q] = 0.0;
-      kr[q] = CellCoef{0.0, 0.0, 0.0, 0.0, 0.0};
-      if (own && c < n) {
-        kr[q] = load_coef(m, a.gx, a.gy, a.diag, c);
-        rr[q] = a.b[c];
-        cm |= (neighbour_mask(m, c) | (published(c) ? 16u : 0u)) << (5 * q);
-      }
-    }
-  } else {
-    for (int i = threadIdx.x; i < nhalo; i += blockDim.x) stage[i] = a.b[halo_cell(i)];
-    for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
-      a.x[c] = 0.0;
-      a.gr[c] = a.b[c];
-    }
+  for (int i = threadIdx.x; i < nhalo; i += blockDim.x) stage[i] = a.b[halo_cell(i)];
+  for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
+    a.x[c] = 0.0;
+    a.gr[c] = a.b[c];
   }
   __syncthreads();
   apply_pass(pub[0], part[0], true);
   int status = -7;
   if (!group_barrier()) status = -3;
-  preload_halo(pub[0]);
   double gamma = 0.0, delta = 0.0;
   group_tree_pairs(part[0], nb, red, gamma, delta);
   const double thr = a.tol2 * gamma;
@@ -2678,50 +2664,21 @@ __device__ void cg_run(const CGArgs &a, int rank, int G)
   while (status == -7 && it < a.max_iters) {
     const bool first = (it == 0);
     const double *pp = pub[par];
-    // own cells: direction, x and r updates (register form: stage the new r)
-    if constexpr (REG) {
-      if (own) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int c = tbr * kTree + lane + 64 * q;
-          if (c < n) {
-            pr[q] = first ? rr[q] : rr[q] + beta * pr[q];
-            sr[q] = first ? wr[q] : wr[q] + beta * sr[q];
-            xr[q] = xr[q] + alpha * pr[q];
-            rr[q] = rr[q] - alpha * sr[q];
-            stage[c - h0] = rr[q];
-          }
-        }
-      }
-    } else {
-      for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
-        const double pv = first ? a.gr[c] : a.gr[c] + beta * a.gp[c];
-        const double sv = first ? a.gw[c] : a.gw[c] + beta * a.gs[c];
-        a.gp[c] = pv;
-        a.gs[c] = sv;
-        a.x[c] = a.x[c] + alpha * pv;
-        a.gr[c] = a.gr[c] - alpha * sv;
-      }
+    // own cells: direction, x and r updates
+    for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
+      const double pv = first ? a.gr[c] : a.gr[c] + beta * a.gp[c];
+      const double sv = first ? a.gw[c] : a.gw[c] + beta * a.gs[c];
+      a.gp[c] = pv;
+      a.gs[c] = sv;
+      a.x[c] = a.x[c] + alpha * pv;
+      a.gr[c] = a.gr[c] - alpha * sv;
     }
     // halo: the neighbours' new r from their published (r, w, s)
-#pragma unroll
-    for (int k = 0; k < kHaloRegs; ++k) {
-      const int i = threadIdx.x + k * blockDim.x;
-      if (i < nhalo) {
-        const int c = halo_cell(i);
-        const double sv = first ? hwv[k] : hwv[k] + beta * hs[k];
-        const double rv = hr[k] - alpha * sv;
-        if constexpr (REG) stage[c - h0] = rv;
-        else stage[i] = rv;
-      }
-    }
-    for (int i = threadIdx.x + kHaloRegs * blockDim.x; i < nhalo; i += blockDim.x) {
+    for (int i = threadIdx.x; i < nhalo; i += blockDim.x) {
       const int c = halo_cell(i);
       const double sw = xld(&pp[n + c]);
       const double sv = first ? sw : sw + beta * xld(&pp[2 * static_cast<size_t>(n) + c]);
-      const double rv = xld(&pp[c]) - alpha * sv;
-      if constexpr (REG) stage[c - h0] = rv;
-      else stage[i] = rv;
+      stage[i] = xld(&pp[c]) - alpha * sv;
     }
     __syncthreads();
     apply_pass(pub[par ^ 1], part[par ^ 1], false);
@@ -2731,7 +2688,6 @@ __device__ void cg_run(const CGArgs &a, int rank, int G)
     }
     par ^= 1;
     ++it;
-    preload_halo(pub[par]);
     double gamma_new = 0.0;
     group_tree_pairs(part[par], nb, red, gamma_new, delta);
     if (gamma_new <= thr) {
@@ -2749,25 +2705,292 @@ __device__ void cg_run(const CGArgs &a, int rank, int G)
     alpha = gamma_new / den;
     gamma = gamma_new;
   }
-  if constexpr (REG) {
-    if (own) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = tbr * kTree + lane + 64 * q;
-        if (c < n) a.x[c] = xr[q];
-      }
-    }
-  }
   if (rank == 0 && threadIdx.x == 0) {
     a.sc->cg_iters = it;
     a.sc->cg_status = status;
   }
 }
 
-template <bool REG>
-__global__ __launch_bounds__(kCgThreadsMax) void cg_kernel(CGArgs a)
+// The register form (a.TB <= blockDim.x / 64): wave w holds block g TB + w.
+// Latency bounds it, so the iteration is straight-line: cells past the end and
+// absent neighbours are zeros (coefficient 0, value read from a zero slot:
+// v - 0 * 0 is v for every v), the first iteration is a later one with beta = 0
+// and p = s = 0, and every wave reduces the block sums itself.  FLAGS: the group
+// barrier is a word per workgroup in a.flags instead of a counter (the
+// arrivals at one counter follow one another).
+template <int SPAN, bool FLAGS>
+__device__ __forceinline__ void cg_reg_run(const CGArgs &a, int rank, int G)
 {
-  cg_run<REG>(a, blockIdx.x, gridDim.x);
+  extern __shared__ double dyn[];          // a zero, then r on [h0, h1)
+  __shared__ double red[2 * kTree];        // chunk sums when nb > 256, or one workgroup's sums
+  __shared__ int s_abort;
+  double *const stage = dyn + 1;
+  unsigned int epoch = 0;
+  const int n = a.m.n_cells, nx = a.m.nx;
+  const int nb = (n + kTree - 1) / kTree;
+  const int tid = static_cast<int>(threadIdx.x), nt = static_cast<int>(blockDim.x);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int tb0 = rank * a.TB;
+  const int tb1 = min(tb0 + a.TB, nb);
+  const int c0 = min(tb0 * kTree, n), c1 = min(tb1 * kTree, n);
+  const int hw = (a.m.dim == 2) ? nx : 1;
+  const int h0 = max(0, c0 - hw), h1 = min(n, c1 + hw);
+  const int nlo = c0 - h0;                          // halo cells below the own range
+  const int nhalo = SPAN == kSpanOne ? 0 : (h1 - h0) - (c1 - c0);
+  const bool nb_lo = c0 > 0, nb_hi = c1 < n;       // a neighbour below / above exists
+  const int tbr = tb0 + wave;
+  const bool own = wave < a.TB && tbr < tb1;
+  const int cb = tbr * kTree + lane;                // this lane's first cell
+  auto halo_cell = [&](int i) { return i < nlo ? h0 + i : c1 + (i - nlo); };
+  const int hc = halo_cell(tid);                    // this thread's halo cell (tid < nhalo)
+
+  double xr[4], rr[4], wr[4], pr[4], sr[4], kd[4], kf[4][4];
+  int at[4][4];                                     // the neighbours' places in dyn
+  unsigned pubm = 0u;                               // bit q: cell q is published
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = cb + 64 * q;
+    xr[q] = pr[q] = sr[q] = wr[q] = rr[q] = kd[q] = 0.0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      kf[q][f] = 0.0;
+      at[q][f] = 0;
+    }
+    if (own && c < n) {
+      const CellCoef k = load_coef(a.m, a.gx, a.gy, a.diag, c);
+      const unsigned bits = neighbour_mask(a.m, c);
+      rr[q] = a.b[c];
+      kd[q] = k.d;
+      kf[q][0] = k.l;
+      kf[q][1] = k.r;
+      kf[q][2] = k.dn;
+      kf[q][3] = k.up;
+      at[q][0] = (bits & 1u) ? c - h0 : 0;          // (place of c is c - h0 + 1)
+      at[q][1] = (bits & 2u) ? c - h0 + 2 : 0;
+      at[q][2] = (bits & 4u) ? c - h0 + 1 - nx : 0;
+      at[q][3] = (bits & 8u) ? c - h0 + 1 + nx : 0;
+      if (SPAN != kSpanOne && ((nb_lo && c < c0 + hw) || (nb_hi && c >= c1 - hw))) pubm |= 1u << q;
+    }
+  }
+  const unsigned any_pub = __any(pubm != 0u);
+  if (tid == 0) {
+    dyn[0] = 0.0;
+    s_abort = 0;
+  }
+  for (int i = tid; i < h1 - h0; i += nt) stage[i] = a.b[h0 + i];
+  __syncthreads();
+
+  double hr = 0.0, hwv = 0.0, hs = 0.0;             // this thread's halo cell, as published
+  // w = A r on the own cells; its block sums of (r, r) and (w, r) and (r, w, s)
+  // of its published cells into buffer b
+  auto apply_pass = [&](int b) {
+    if (!own) return;
+    double v[4][4], g[4], d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int f = 0; f < 4; ++f) v[q][f] = dyn[at[q][f]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double t = kd[q] * rr[q];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) t = t - kf[q][f] * v[q][f];
+      wr[q] = t;
+      g[q] = rr[q] * rr[q];
+      d[q] = t * rr[q];
+    }
+    if (SPAN != kSpanOne && any_pub) {
+      double *const pn = a.pub + 3 * static_cast<size_t>(n) * b;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (pubm & (1u << q)) {
+          const int c = cb + 64 * q;
+          xst<SPAN>(&pn[c], rr[q]);
+          xst<SPAN>(&pn[n + c], wr[q]);
+          xst<SPAN>(&pn[2 * static_cast<size_t>(n) + c], sr[q]);
+        }
+    }
+    const double sg = wave_tree256(g[0], g[1], g[2], g[3]);
+    const double sd = wave_tree256(d[0], d[1], d[2], d[3]);
+    if (lane == 0) {
+      if (SPAN == kSpanOne && nb <= kTree) {
+        red[tbr] = sg;
+        red[kTree + tbr] = sd;
+      } else {
+        double *const pt = a.part + 2 * static_cast<size_t>(nb) * b;
+        xst<SPAN>(&pt[2 * tbr], sg);
+        xst<SPAN>(&pt[2 * tbr + 1], sd);
+      }
+    }
+  };
+  auto group_barrier = [&]() -> bool {
+    if (!FLAGS) return grid_barrier(a.barrier, epoch, G);
+    // (device-wide a line per word: stores to one line follow one another at
+    // the coherence point, 512 x 512 cells on 86 workgroups 6.9 -> 5.4 us per
+    // iteration; in one XCD's L2 the words share lines, one load polls them)
+    constexpr int kStep = SPAN == kSpanDevice ? kCgFlagStep : 1;
+    __builtin_amdgcn_s_waitcnt(0);                  // this wave's stores have completed
+    __syncthreads();
+    epoch += 1;
+    if (wave == 0) {
+      if (lane == 0) {
+        if (SPAN == kSpanDevice)
+          __hip_atomic_store(a.flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          __hip_atomic_store(a.flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      long spins = 0;
+      for (;;) {
+        bool ok = true;
+        for (int i = lane; i < G; i += 64)
+          ok = ok && __hip_atomic_load(a.flags + i * kStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
+        if (__all(ok)) break;
+        if (++spins > kBarrierSpinLimit ||
+            ((spins & 1023) == 0 &&
+             __hip_atomic_load(a.barrier + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          __hip_atomic_store(a.barrier + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          s_abort = 1;
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    return s_abort == 0;
+  };
+  // buffer b of every member: this thread's halo cell, and the sums; false on
+  // an abort
+  auto exchange = [&](int b, double &sg, double &sd) -> bool {
+    const bool share = SPAN == kSpanXcd && nb > kCgShareBlocks;
+    if (share) {
+      // one value per thread, met in LDS: every wave loading all of them keeps
+      // the CU's load path busy (256 blocks: 2.9 -> 2.6 us per iteration; 13
+      // blocks are loaded directly, 2.0 against 2.1 us)
+      if (!group_barrier()) return false;
+      const double *const pt = a.part + 2 * static_cast<size_t>(nb) * b;
+      if (tid < nhalo) {
+        const double *const pn = a.pub + 3 * static_cast<size_t>(n) * b;
+        hr = xld(&pn[hc]);
+        hwv = xld(&pn[n + hc]);
+        hs = xld(&pn[2 * static_cast<size_t>(n) + hc]);
+      }
+      for (int i = tid; i < 2 * nb; i += nt) red[(i & 1) * kTree + (i >> 1)] = xld(&pt[i]);
+    }
+    if (share || (SPAN == kSpanOne && nb <= kTree)) {
+      __syncthreads();
+      double g[4], d[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = lane + 64 * q;
+        g[q] = k < nb ? red[k] : 0.0;
+        d[q] = k < nb ? red[kTree + k] : 0.0;
+      }
+      sg = lane0(wave_tree256(g[0], g[1], g[2], g[3]));
+      sd = lane0(wave_tree256(d[0], d[1], d[2], d[3]));
+      return true;
+    }
+    if (SPAN == kSpanOne) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+    } else if (!group_barrier()) {
+      return false;
+    }
+    if (tid < nhalo) {
+      const double *const pn = a.pub + 3 * static_cast<size_t>(n) * b;
+      hr = xld(&pn[hc]);
+      hwv = xld(&pn[n + hc]);
+      hs = xld(&pn[2 * static_cast<size_t>(n) + hc]);
+    }
+    group_tree_pairs(a.part + 2 * static_cast<size_t>(nb) * b, nb, red, sg, sd);
+    return true;
+  };
+
+  apply_pass(0);
+  int status = -7, it = 0, par = 0;
+  double gamma = 0.0, delta = 0.0, alpha = 0.0, beta = 0.0;
+  if (!exchange(0, gamma, delta)) status = -3;
+  const double thr = a.tol2 * gamma;
+  if (status == -3) {
+  } else if (gamma == 0.0) {
+    status = 0;
+  } else if (!(delta > 0.0)) {
+    status = -6;
+  } else {
+    alpha = gamma / delta;
+  }
+  while (status == -7 && it < a.max_iters) {
+    if (own) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        pr[q] = rr[q] + beta * pr[q];
+        sr[q] = wr[q] + beta * sr[q];
+        xr[q] = xr[q] + alpha * pr[q];
+        rr[q] = rr[q] - alpha * sr[q];
+        stage[cb + 64 * q - h0] = rr[q];
+      }
+    }
+    // halo: the neighbours' new r from their published (r, w, s)
+    if (tid < nhalo) stage[hc - h0] = hr - alpha * (hwv + beta * hs);
+    for (int i = tid + nt; i < nhalo; i += nt) {
+      const int c = halo_cell(i);
+      const double *const pn = a.pub + 3 * static_cast<size_t>(n) * par;
+      const double sv = xld(&pn[n + c]) + beta * xld(&pn[2 * static_cast<size_t>(n) + c]);
+      stage[c - h0] = xld(&pn[c]) - alpha * sv;
+    }
+    __syncthreads();
+    par ^= 1;
+    apply_pass(par);
+    ++it;
+    double gamma_new = 0.0;
+    if (!exchange(par, gamma_new, delta)) {
+      status = -3;
+      break;
+    }
+    if (gamma_new <= thr) {
+      status = 0;
+      break;
+    }
+    beta = gamma_new / gamma;
+    double tq = beta * gamma_new;
+    tq = tq / alpha;
+    const double den = delta - tq;
+    if (!(den > 0.0)) {
+      status = -6;
+      break;
+    }
+    alpha = gamma_new / den;
+    gamma = gamma_new;
+  }
+  if (own) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (cb + 64 * q < n) a.x[cb + 64 * q] = xr[q];
+  }
+  if (rank == 0 && tid == 0) {
+    a.sc->cg_iters = it;
+    a.sc->cg_status = status;
+  }
+}
+
+// the single solve's CG.  G: the group's size; more workgroups than that are
+// launched where the group may find room on one XCD (elect_group).
+__global__ __launch_bounds__(kCgThreadsMax) void cg_kernel(CGArgs a, int G)
+{
+  int rank = blockIdx.x;
+  bool one_xcd = false;
+  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (one_xcd) cg_reg_run<kSpanXcd, true>(a, rank, G);
+  else cg_reg_run<kSpanDevice, true>(a, rank, G);
+}
+
+// the register form on one workgroup, and the global form
+__global__ __launch_bounds__(kCgThreadsMax) void cg_one_kernel(CGArgs a, int)
+{
+  cg_reg_run<kSpanOne, false>(a, 0, 1);
+}
+
+__global__ __launch_bounds__(kCgThreadsMax) void cg_global_kernel(CGArgs a, int G)
+{
+  cg_global_run(a, blockIdx.x, G);
 }
 
 // ---------------------------------------------------------------------------

@@ -848,8 +848,9 @@ __global__ __launch_bounds__(kCgThreadsMax) void cg_batch_kernel(const Inst *__r
     a.max_iters = in.cg_max;
     a.barrier = in.cg_barrier;
     a.sc = in.sc;
-    if (jb.tb & kCgJobReg) cg_run<true>(a, jb.rank, jb.G);
-    else cg_run<false>(a, jb.rank, jb.G);
+    if (!(jb.tb & kCgJobReg)) cg_global_run(a, jb.rank, jb.G);
+    else if (jb.G == 1) cg_reg_run<kSpanOne, false>(a, 0, 1);
+    else cg_reg_run<kSpanDevice, false>(a, jb.rank, jb.G);
     __syncthreads();
   }
 }
