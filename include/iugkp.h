@@ -124,18 +124,20 @@ typedef struct iugkp_options {
   int block_size;               /* transport kernel workgroup size: 0 (= 256), 64..1024 */
   int march;                    /* single solves on 2D meshes: 0 automatic (row stripes for
                                    face-tallied iterations with long free paths, tiles
-                                   otherwise; see iugkp_march_tuning), 1 emitter tiles, 2 row
+                                   otherwise; see iugkp_march_tuning; with null collisions or
+                                   expected-value rays, domain blocks), 1 emitter tiles, 2 row
                                    stripes (also for the expected-value estimator, with or
                                    without face tallies), 3 row stripes with the y faces cut
                                    into pieces (without null collisions; else as 2).
                                    Persistent scheme: the y faces of face-tallied moves by a
                                    row-stripe pass (2 or 3, or 0 with long free paths) or as
-                                   global atomics in the move (1).  Frequency bands: bands
+                                   global atomics in the move (1).  Frequency bands: domain
+                                   blocks where a band has null collisions, else bands
                                    whose free paths reach half the domain's height run their
-                                   face-tallied iterations by row stripes unless march is 1.
+                                   face-tallied iterations by row stripes; march 1: tiles.
                                    The result does not depend on it */
   int cg_waves;                 /* single solves: 256-cell tree blocks per CG workgroup, 0
-                                   (= 8) or 1..12 with the CG state in registers, -1..-12 with
+                                   (= 4 to 8) or 1..12 with the CG state in registers, -1..-12 with
                                    it in global memory (with IUGKP_PRECOND_MG: |cg_waves|
                                    wavefronts per workgroup); the result does not depend on
                                    it */
@@ -297,7 +299,7 @@ int iugkp_get_stats(iugkp_handle *h, iugkp_stats *stats);
 /* The particle step's form for the face-tallied iterations (the A4 march of
  * Sec. 3.1; how it is run is an implementation choice, not the paper's): 0 =
  * emitter tiles of 256 threads, 1 = emitter tiles of 512 threads, 2 = row
- * stripes, 3 = row stripes with the y faces in pieces (without null
+ * stripes (with null collisions: domain blocks), 3 = row stripes with the y faces in pieces (without null
  * collisions); -1 while the handle still measures them.  A 2D gray single solve
  * with the automatic march and the default block size times one face-tallied
  * iteration in each form (after an untimed first one) and keeps the fastest;

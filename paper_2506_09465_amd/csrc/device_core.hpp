@@ -14,17 +14,18 @@ namespace iugkp {
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of the 4x32
 // Philox S-box, multipliers 0xD2511F53 / 0xCD9E8D57, Weyl key increments
-// 0x9E3779B9 / 0xBB67AE85 between rounds.  32-bit multiplies map to
-// v_mul_lo_u32 / v_mul_hi_u32.
+// 0x9E3779B9 / 0xBB67AE85 between rounds.  Both halves of a product come from
+// one v_mad_u64_u32 (as v_mul_lo_u32 and v_mul_hi_u32, two quarter-rate
+// instructions, the 512 x 512 two-material step took 36.6 ms against 35.2).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1)
 {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c.x);
-    const uint32_t lo0 = 0xD2511F53u * c.x;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c.z);
-    const uint32_t lo1 = 0xCD9E8D57u * c.z;
+    const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c.x;
+    const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c.z;
+    const uint32_t hi0 = static_cast<uint32_t>(p0 >> 32), lo0 = static_cast<uint32_t>(p0);
+    const uint32_t hi1 = static_cast<uint32_t>(p1 >> 32), lo1 = static_cast<uint32_t>(p1);
     c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;

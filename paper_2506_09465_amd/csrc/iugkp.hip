@@ -26,6 +26,7 @@
 #include "host_math.hpp"
 #include "kernels.hpp"
 #include "mgcg.hpp"
+#include "blocks.hpp"
 
 namespace {
 
@@ -78,6 +79,24 @@ constexpr int kLdsWallsMax = 1024;
 // least: 27 / 38 us, but the two-time film's solve 1.85 ms against 2.2 / 3.0);
 // 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with null collisions,
 // 1e6 particles 1188 -> 729 us (one particle per 4 or 2 words: 806 / 1182).
+// The particle step by domain blocks (blocks.hpp) from this many flights per
+// iteration: measured to win from the smallest sizes on (40 x 30 cells,
+// expected value, 3e4 flights: 129 against 282 us by tiles; five bands on 64 x
+// 64, 2e5 flights: 463 against 867), but for one case: a gray analog iteration
+// without face tallies, whose tile march resolves long segments in closed form
+// and sends few tallies out of its windows.  There blocks take free paths
+// below kBlockQuietCells (256 x 256, 1e7 flights, 12.8 cells: 3.8 against 8.5
+// ms; 128 cells: 2.9 against 1.3) with kBlockQuietFlights flights or a mesh
+// beyond kBlockQuietMesh cells or of one block (128 x 128, 1e6 / 3e6 flights:
+// 1.07 / 1.48 against 0.71 / 1.43 ms; 256 x 256, 1e6: 1.50 against 2.16; 60 x 60,
+// 4e5: 0.41 against 0.53).
+constexpr double kBlockMinFlights = 30000.0;
+constexpr double kBlockQuietCells = 32.0, kBlockQuietFlights = 3e6;
+constexpr int kBlockQuietMesh = 32768;
+// units of work per round of the blocks' step: more balance better, fewer pay
+// for fewer LDS images (512 / 1024 / 2048 units: two-material square 30.5 /
+// 31.5 / 33.0 ms, expected-value cavity 8.6 / 8.1 / 9.3 ms)
+constexpr int kBlockTarget = 512, kBlockTargetEv = 1024;
 constexpr int kSplitTarget = 1024;
 constexpr int kSplitMin = 256;
 constexpr int kSplitWords = 8;
@@ -772,6 +791,16 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
   return IUGKP_OK;
 }
 
+// Whether a handle's particle step may run by domain blocks (blocks.hpp): 2D
+// flights that go far beyond an emitter tile's window with a tally at every
+// stop, that is with null collisions or expected-value rays.
+bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, bool has_null, double flights)
+{
+  return p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS && o->march == 0 && o->block_size == 0 &&
+         (has_null || o->estimator == IUGKP_EST_EXPECTED) && p->nx <= 0xffff && p->ny <= 0xffff &&
+         flights >= kBlockMinFlights;
+}
+
 int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, bool multi_cg,
                    InstHost &ih)
 {
@@ -992,6 +1021,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
   const bool lam_stripes = d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
   if (multi_cg && p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS &&
+      !blocks_wanted(p, o, d.has_null, static_cast<double>(ne) * d.N) &&
       ((ev && o->march >= 2) ||
        (!ev && o->tally_faces != IUGKP_FACES_OFF &&
         (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0)))))) {
@@ -1164,6 +1194,9 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   }
 
   rest.assign(K - 1, InstHost{});
+  bool any_null = false;
+  for (int k = 0; k < K; ++k) any_null = any_null || has_null[k];
+  const bool blocks = blocks_wanted(p, o, any_null, static_cast<double>(K) * ne * N);
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
   int ok = 1;
   unsigned long long acc = 0, wall_acc = 0;
@@ -1219,7 +1252,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     // has long chains of null collisions wherever its relaxation time is
     // above the minimum, which the tile march handles better (march 1 keeps
     // every band on tiles)
-    if (p->dim == 2 && o->tally_faces != IUGKP_FACES_OFF && o->march != 1 &&
+    if (!blocks && p->dim == 2 && o->tally_faces != IUGKP_FACES_OFF && o->march != 1 &&
         o->estimator == IUGKP_EST_ANALOG && lam[k] >= kStripeMinCells * std::min(p->dx, p->dy) &&
         lam[k] >= 0.5 * p->ny * p->dy) {
       const int rc = plan_stripes(ih, s, false, true);
@@ -1427,12 +1460,28 @@ int upload_inst(const InstHost &ih, int inst_index, Inst *d_inst, TileDesc *d_ti
 // ---------------------------------------------------------------------------
 // single solves
 // ---------------------------------------------------------------------------
+// The particle step by domain blocks (rounds 0: not used).
+struct BlockHost {
+  iugkp::BlockRun run{};
+  int rounds = 0, grid = 0;
+  bool quiet = false;              // also for gray analog iterations without face tallies
+  size_t lds = 0, plan_lds = 0;
+  std::vector<void *> allocs;
+  void release()
+  {
+    for (void *p : allocs) (void)hipFree(p);
+    allocs.clear();
+    rounds = 0;
+  }
+};
+
 struct iugkp_handle {
   hipStream_t stream = nullptr;
   bool own_stream = false;        // created (and destroyed) by the library
   InstHost ih;                    // the problem (gray), or band 0 (frequency bands)
   std::vector<InstHost> xb;       // bands 1 .. K-1
   BandsHost bh;
+  BlockHost blocks;
   Inst *d_inst = nullptr;         // [K]
   TileDesc *d_tiles = nullptr;    // the tiles of the bands without row stripes first
   int n_tiles = 0;
@@ -1463,6 +1512,7 @@ void free_handle(iugkp_handle *h)
   if (!h) return;
   if (h->own_stream && h->stream) (void)hipStreamSynchronize(h->stream);
   h->ih.release();
+  h->blocks.release();
   for (auto &b : h->xb) b.release();
   if (h->d_inst) (void)hipFree(h->d_inst);
   if (h->d_tiles) (void)hipFree(h->d_tiles);
@@ -1568,7 +1618,8 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
 
 // The particle step's form for the face-tallied iterations of a 2D gray
 // single solve with the automatic march and the default block size: emitter
-// tiles with 256 or 512 threads per workgroup, or row stripes.  Measured,
+// tiles with 256 or 512 threads per workgroup, or row stripes (flights with
+// null collisions: domain blocks in their place).  Measured,
 // not guessed: the first face-tallied iteration runs the planner's choice
 // (not timed: first launches), the next three one candidate each (timed by
 // the step's events), then the fastest, which every later handle of the
@@ -1662,6 +1713,24 @@ int launch_stripes(const InstHost &ih, const Inst *d_inst, bool pieces, hipStrea
   return IUGKP_OK;
 }
 
+// The particle step by domain blocks: every round, with the sort between them.
+int launch_blocks(const BlockHost &b, const Inst *d_inst, bool ev, int faces, hipStream_t s)
+{
+  iugkp::zero_u32_kernel<<<cdiv(b.rounds, 64), 64, 0, s>>>(b.run.next, b.rounds);
+  constexpr int sg = 2048;                   // (a few workgroups per CU, each a run of chunks)
+  if (ev) iugkp::block_sample_kernel<true><<<sg, iugkp::kSampleThreads, 0, s>>>(d_inst, b.run);
+  else iugkp::block_sample_kernel<false><<<sg, iugkp::kSampleThreads, 0, s>>>(d_inst, b.run);
+  for (int r = 0; r < b.rounds; ++r) {
+    if (r > 0) iugkp::block_plan_kernel<<<1, 1024, b.plan_lds, s>>>(b.run, r - 1);
+    if (ev)
+      iugkp::block_march_kernel<true><<<b.grid, iugkp::kBlockThreads, b.lds, s>>>(d_inst, b.run, r, faces);
+    else
+      iugkp::block_march_kernel<false><<<b.grid, iugkp::kBlockThreads, b.lds, s>>>(d_inst, b.run, r, faces);
+  }
+  HIP_TRY(hipGetLastError());
+  return IUGKP_OK;
+}
+
 // Enqueue one iteration on the handle's stream: its kernels and the copy of
 // the new scalars into h->hsc (complete_iteration waits for them).
 int enqueue_iteration(iugkp_handle *h, int faces)
@@ -1705,7 +1774,12 @@ int enqueue_iteration(iugkp_handle *h, int faces)
   iugkp::prepare_kernel<<<dim3(cdiv(nprep, 256), K), 256, 0, s>>>(h->d_inst, faces, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(h->ev[0], s));
-  if (ih.d.estimator && ih.stripe_R > 0) {
+  bool by_blocks = h->blocks.rounds > 0;
+  if (by_blocks && K == 1 && !ih.d.estimator)
+    by_blocks = faces ? (form = pick_form(h)) == kFormStripes : h->blocks.quiet;
+  if (by_blocks) {
+    if ((rc = launch_blocks(h->blocks, h->d_inst, ih.d.estimator != 0, faces, s))) return rc;
+  } else if (ih.d.estimator && ih.stripe_R > 0) {
     iugkp::march_stripes_ev_kernel<kStripeBlock>
         <<<dim3(ih.stripe_C, ih.stripe_S), kStripeBlock, ih.stripe_lds, s>>>(h->d_inst, ih.stripe_R,
                                                                               ih.stripe_C, faces);
@@ -1836,6 +1910,145 @@ int write_band_outputs(iugkp_handle *h, double *T_out, double *qx_out, double *q
 
 const InstHost &band_of(const iugkp_handle *h, int k) { return k == 0 ? h->ih : h->xb[k - 1]; }
 
+// Cut every band's mesh into blocks whose tallies fit a workgroup's LDS (the
+// fewest rounds, then the fewest blocks), round 0's units, and the record
+// chunks of two rounds.  IUGKP_E_NOMEM without the memory (the caller falls
+// back to tiles).
+int plan_blocks(iugkp_handle *h)
+{
+  BlockHost &b = h->blocks;
+  const Mesh &m = h->ih.d.m;
+  const int K = h->bh.K;
+  int dev = 0, n_cu = 0, lds_max = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  int has_null = 0;
+  for (int k = 0; k < K; ++k) has_null |= band_of(h, k).d.has_null;
+  const int faces = h->ih.opt.tally_faces != IUGKP_FACES_OFF;
+  const int ratios = has_null && !h->ih.d.estimator;
+  const int words = (lds_max - 6144) / 8;           // (less the kernel's static LDS)
+  int nbx = 0, nby = 0;
+  for (int sum = 2; nbx == 0 && sum <= m.nx + m.ny; ++sum)
+    for (int x = 1; x < sum; ++x) {
+      const int y = sum - x;
+      if (x > m.nx || y > m.ny) continue;
+      if (iugkp::block_words(cdiv(m.nx, x), cdiv(m.ny, y), has_null, faces, ratios) > words) continue;
+      if (nbx == 0 || x * y < nbx * nby) {
+        nbx = x;
+        nby = y;
+      }
+    }
+  const int T1 = nbx * nby;
+  if (nbx == 0 || T1 > iugkp::kBlocksMax / K) return IUGKP_E_NOMEM;
+  std::vector<iugkp::BlockDesc> blk(static_cast<size_t>(K) * T1 + 1);
+  std::vector<iugkp::BlockUnit> units;
+  double flights = 0.0;
+  for (int k = 0; k < K; ++k) flights += static_cast<double>(m.n_emit) * band_of(h, k).d.N;
+  // chunks of a unit of round 0
+  const int target = h->ih.d.estimator ? kBlockTargetEv : kBlockTarget;
+  const double share = std::min(static_cast<double>(iugkp::kUnitChunksMax),
+                                std::max(static_cast<double>(iugkp::kUnitChunksMin),
+                                         std::ceil(flights / iugkp::kChunk / target)));
+  unsigned long long slab = 0, base = 0;
+  int ex_max = 1, ey_max = 1;
+  for (int k = 0; k < K; ++k)
+    for (int by = 0; by < nby; ++by)
+      for (int bx = 0; bx < nbx; ++bx) {
+        const int t = k * T1 + by * nbx + bx;
+        iugkp::BlockDesc &d = blk[t];
+        d.inst = k;
+        d.x0 = static_cast<int>(static_cast<long long>(m.nx) * bx / nbx);
+        d.y0 = static_cast<int>(static_cast<long long>(m.ny) * by / nby);
+        d.ex = static_cast<int>(static_cast<long long>(m.nx) * (bx + 1) / nbx) - d.x0;
+        d.ey = static_cast<int>(static_cast<long long>(m.ny) * (by + 1) / nby) - d.y0;
+        ex_max = std::max(ex_max, d.ex);
+        ey_max = std::max(ey_max, d.ey);
+        d.n_e = d.ex * d.ey + (bx == 0 ? d.ey : 0) + (bx == nbx - 1 ? d.ey : 0) +
+                (by == 0 ? d.ex : 0) + (by == nby - 1 ? d.ex : 0);
+        d.nb[0] = bx > 0 ? t - 1 : t;               // (the mesh's edge: never entered)
+        d.nb[1] = bx < nbx - 1 ? t + 1 : t;
+        d.nb[2] = by > 0 ? t - nbx : t;
+        d.nb[3] = by < nby - 1 ? t + nbx : t;
+        const unsigned long long P = static_cast<unsigned long long>(d.n_e) * band_of(h, k).d.N;
+        const unsigned long long nc = (P + iugkp::kChunk - 1) / iugkp::kChunk;
+        d.base = static_cast<uint32_t>(base);
+        base += nc;
+        if (base >= (1ull << 25)) return IUGKP_E_NOMEM;    // (25 bits of a list entry)
+        const unsigned long long parts =
+            static_cast<unsigned long long>(std::ceil(static_cast<double>(nc) / share));
+        for (unsigned long long i = 0; i < parts; ++i) {
+          iugkp::BlockUnit u;
+          u.t = t;
+          u.first = static_cast<uint32_t>(nc * i / parts);
+          u.count = static_cast<uint32_t>(nc * (i + 1) / parts) - u.first;
+          u.cap = u.count + iugkp::kOpenChunks;
+          u.slab = static_cast<uint32_t>(slab);
+          slab += u.cap;
+          units.push_back(u);
+        }
+      }
+  blk.back().base = static_cast<uint32_t>(base);
+  const int T = K * T1;
+  // most units of a round, and most chunks: at most one chunk per 64 flights
+  // and kOpenChunks partly filled ones per unit of the round that wrote them,
+  // again kOpenChunks per unit of the round that reads them
+  const double full = static_cast<double>(base) + 1.0;
+  const double u_max = std::max({static_cast<double>(units.size()), static_cast<double>(target + T),
+                                 (full / iugkp::kUnitChunksMax + T + 1.0) /
+                                     (1.0 - static_cast<double>(iugkp::kOpenChunks) / iugkp::kUnitChunksMax)});
+  const double chunks = std::max(static_cast<double>(slab), full + 2.0 * iugkp::kOpenChunks * (u_max + 1.0));
+  if (chunks >= static_cast<double>(1u << 25)) return IUGKP_E_NOMEM;
+  const size_t n_u = static_cast<size_t>(u_max) + 1, n_c = static_cast<size_t>(chunks) + 1;
+  b.rounds = nbx + nby - 1;
+  bool ok = true;
+  auto get = [&](auto **p, size_t n) {
+    void *q = nullptr;
+    ok = ok && hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(**p)) == hipSuccess;
+    if (q) b.allocs.push_back(q);
+    *p = static_cast<std::remove_reference_t<decltype(**p)> *>(q);
+  };
+  iugkp::BlockRun &r = b.run;
+  iugkp::BlockDesc *d_blk = nullptr;
+  iugkp::BlockUnit *d_units0 = nullptr;
+  get(&d_blk, blk.size());
+  get(&d_units0, units.size());
+  get(&r.next, b.rounds);
+  get(&r.rec[1], n_c * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
+  if (b.rounds > 1) {
+    for (int i = 0; i < 2; ++i) {
+      get(&r.units[i], n_u);
+      get(&r.list[i], 4 * n_c);
+    }
+    get(&r.rec[0], n_c * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
+    get(&r.n_units, 2);
+    get(&r.seg_off, T + 1);
+    get(&r.seg_pos, 4 * n_u);
+    get(&r.seg_pre, 4 * n_u);
+  }
+  get(&r.out_n, 4 * n_u);
+  if (!ok) {
+    (void)hipGetLastError();
+    b.release();
+    return IUGKP_E_NOMEM;
+  }
+  r.blk = d_blk;
+  r.T = T;
+  r.target = static_cast<uint32_t>(target);
+  r.units0 = d_units0;
+  r.n_units0 = static_cast<uint32_t>(units.size());
+  b.grid = n_cu;
+  b.quiet = h->ih.d.lam_min < kBlockQuietCells * std::min(m.dx, m.dy) &&
+            (T == 1 || flights >= kBlockQuietFlights || m.n_cells > kBlockQuietMesh);
+  b.lds = static_cast<size_t>(iugkp::block_words(ex_max, ey_max, has_null, faces, ratios)) * sizeof(long long);
+  b.plan_lds = static_cast<size_t>(T) * sizeof(unsigned long long);
+  HIP_TRY(hipMemcpyAsync(d_blk, blk.data(), blk.size() * sizeof(blk[0]), hipMemcpyHostToDevice, h->stream));
+  HIP_TRY(hipMemcpyAsync(d_units0, units.data(), units.size() * sizeof(units[0]), hipMemcpyHostToDevice,
+                         h->stream));
+  HIP_TRY(hipStreamSynchronize(h->stream));
+  return IUGKP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1866,8 +2079,25 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
   }
   const int K = h->bh.K;
   h->block = options->block_size ? options->block_size : 256;
-  if (!bands && h->ih.stripe_R > 0 && !h->ih.d.estimator) {
-    h->form_default = !h->ih.stripe_pref ? kFormTiles256
+  // by domain blocks where wanted; without the memory as without them
+  const bool wanted =
+      [&] {
+        bool null = false;
+        double n = 0.0;
+        for (int k = 0; k < K; ++k) {
+          null = null || band_of(h, k).d.has_null;
+          n += static_cast<double>(h->ih.d.m.n_emit) * band_of(h, k).d.N;
+        }
+        return blocks_wanted(problem, options, null, n);
+      }();
+  if (wanted && (rc = plan_blocks(h)) && rc != IUGKP_E_NOMEM) {
+    free_handle(h);
+    return rc;
+  }
+  const bool blocks = h->blocks.rounds > 0;
+  if (!bands && (h->ih.stripe_R > 0 || blocks) && !h->ih.d.estimator) {
+    h->form_default = blocks ? kFormStripes
+                      : !h->ih.stripe_pref ? kFormTiles256
                       : (options->march == 3 && !h->ih.d.has_null) ? kFormPieces : kFormStripes;
     h->form_search = (options->march == 0 && options->block_size == 0);
     if (h->form_search) {

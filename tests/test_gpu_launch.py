@@ -117,3 +117,68 @@ def test_cg_groups_of_many_streams(gpu):
     torch.cuda.synchronize()
     for a, g in zip(alone, got):
         assert torch.equal(a, g)
+
+
+# The particle step by domain blocks: one block, two and several (odd cuts,
+# one-cell-wide remainders impossible to avoid), flights that cross many of
+# them and end on every wall, with and without face tallies, null collisions,
+# expected-value rays; more flights than one unit of work takes.
+BLOCKS = {
+    "null_one_block": (lambda: two_material_2d(n=61, kn_right=0.05, ratio=30.0, particles=300_000), {}),
+    "null_wide": (lambda: _two_tau(301, 71, 0.02, 0.5, 400_000), {}),
+    "null_tall": (lambda: _two_tau(67, 290, 0.02, 1.0, 400_000), {}),
+    "null_many": (lambda: _two_tau(211, 197, 0.004, 0.4, 300_000), {}),
+    "ev_one_block": (lambda: cavity_2d(n=90, ny=77, kn=0.3, particles=220_000, newton=False), {"estimator": 1}),
+    "ev_many": (lambda: cavity_2d(n=230, ny=170, kn=0.2, particles=220_000, newton=False), {"estimator": 1}),
+    "null_few_flights": (lambda: _two_tau(70, 61, 0.05, 0.5, 33_000), {}),
+    "null_no_weight": (lambda: _two_tau(101, 90, 0.05, 0.5, 60_000), {"T_init": "ref"}),
+    "ev_null": (lambda: _two_tau(150, 141, 0.05, 0.5, 220_000), {"estimator": 1}),
+}
+
+
+def _two_tau(nx, ny, kn_a, kn_b, particles):
+    """A cavity with two relaxation times in an irregular pattern."""
+    w = cavity_2d(n=nx, ny=ny, kn=kn_a, particles=particles, newton=False)
+    w.tau = np.where(np.random.default_rng(5).random(w.n_cells) < 0.5, kn_a, kn_b)
+    return w
+
+
+@pytest.mark.parametrize("name", list(BLOCKS))
+@pytest.mark.parametrize("faces", [True, False])
+def test_domain_blocks_bitwise(oracle_mod, gpu, name, faces):
+    make, kw = BLOCKS[name]
+    w = make()
+    mode = oracle_mod.FACES_EVERY if faces else oracle_mod.FACES_OFF
+    kw = dict({"T_init": seeded_temperature(w.n_cells)}, **kw)
+    if isinstance(kw["T_init"], str):       # (only the walls emit at first)
+        kw["T_init"] = np.full(w.n_cells, w.t_ref)
+    o, s = _pair(oracle_mod, gpu, w, tally_faces=mode, **kw)
+    for i in range(2):
+        assert o.step(1) == 0 and s.step(1) == 0
+        if faces:
+            _same_iteration(o, s, f"{name} it{i}")
+        else:
+            _same_cells(o, s, f"{name} it{i}")
+
+
+@pytest.mark.parametrize("faces", [True, False])
+def test_domain_blocks_bands_bitwise(oracle_mod, gpu, faces):
+    """Three bands in one launch, one of them without null collisions, several
+    blocks each: domain blocks (march 0) against every band on tiles."""
+    from synth import nongray_two_material_2d
+    w = nongray_two_material_2d(n=120, K=3, ratio=20.0, particles=400_000)
+    w.tau = w.tau.copy()
+    w.tau[120 * 120: 2 * 120 * 120] = w.tau[-1]
+    mode = gpu.FACES_EVERY if faces else gpu.FACES_OFF
+    T0 = seeded_temperature(w.n_cells)
+    a = gpu.Solver(w, tally_faces=mode, T_init=T0)
+    b = gpu.Solver(w, tally_faces=mode, T_init=T0, march=1)
+    for it in range(2):
+        assert a.step(1) == 0 and b.step(1) == 0
+        ta, tb = a.tallies(), b.tallies()
+        for k in ta if faces else ("D", "W", "B"):
+            assert torch.equal(ta[k], tb[k]), (it, k)
+        assert torch.equal(a.state()[2], b.state()[2]) and torch.equal(a.state()[3], b.state()[3])
+    sa, sb = a.stats(), b.stats()
+    for k in ("flights", "segments", "crossings"):
+        assert sa[k] == sb[k]
