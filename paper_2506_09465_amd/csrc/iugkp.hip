@@ -79,18 +79,21 @@ constexpr int kLdsWallsMax = 1024;
 // least: 27 / 38 us, but the two-time film's solve 1.85 ms against 2.2 / 3.0);
 // 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with null collisions,
 // 1e6 particles 1188 -> 729 us (one particle per 4 or 2 words: 806 / 1182).
-// The particle step by domain blocks (blocks.hpp) from this many flights per
-// iteration: measured to win from the smallest sizes on (40 x 30 cells,
-// expected value, 3e4 flights: 129 against 282 us by tiles; five bands on 64 x
-// 64, 2e5 flights: 463 against 867), but for one case: a gray analog iteration
-// without face tallies, whose tile march resolves long segments in closed form
-// and sends few tallies out of its windows.  There blocks take free paths
-// below kBlockQuietCells (256 x 256, 1e7 flights, 12.8 cells: 3.8 against 8.5
-// ms; 128 cells: 2.9 against 1.3) with kBlockQuietFlights flights or a mesh
-// beyond kBlockQuietMesh cells or of one block (128 x 128, 1e6 / 3e6 flights:
-// 1.07 / 1.48 against 0.71 / 1.43 ms; 256 x 256, 1e6: 1.50 against 2.16; 60 x 60,
-// 4e5: 0.41 against 0.53).
-constexpr double kBlockMinFlights = 30000.0;
+// The particle step by domain blocks (blocks.hpp) against emitter tiles.  An
+// expected-value step takes blocks from kBlockMinFlightsEv rays per iteration
+// (40 x 30 cells, 3e4 rays: 129 against 282 us by tiles).  An analog one with
+// null collisions takes them where flights go far: from kBlockMinFlights
+// flights whose mean free path, over the cells, exceeds the tiles' window
+// margin of kWindowHalo cells (three bands on 64 x 64, 4e4 flights, all far: 98
+// against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
+// One case is measured apart, a gray iteration without face tallies, whose tile
+// march resolves long segments in closed form and sends few tallies out of its
+// windows.  There blocks take free paths below kBlockQuietCells (256 x 256, 1e7
+// flights, 12.8 cells: 3.8 against 8.5 ms; 128 cells: 2.9 against 1.3) with
+// kBlockQuietFlights flights or a mesh beyond kBlockQuietMesh cells or of one
+// block (128 x 128, 1e6 / 3e6 flights: 1.07 / 1.48 against 0.71 / 1.43 ms; 256 x
+// 256, 1e6: 1.50 against 2.16; 60 x 60, 4e5: 0.41 against 0.53).
+constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
 constexpr double kBlockQuietCells = 32.0, kBlockQuietFlights = 3e6;
 constexpr int kBlockQuietMesh = 32768;
 // units of work per round of the blocks' step: more balance better, fewer pay
@@ -205,6 +208,7 @@ struct InstHost {
   // row-stripe particle step for face-tallied iterations (single solves)
   int stripe_R = 0, stripe_S = 0, stripe_C = 0;
   size_t stripe_lds = 0;
+  bool blocks = false;               // domain blocks wanted (the handle's step, all bands)
   int stripe_pref = 0;               // the planner's choice (stripes set up for a search too)
   // the persistent scheme's row-stripe face pass (rows per stripe, stripes,
   // chunks, LDS bytes; 0 rows: y faces as global atomics in the move)
@@ -791,14 +795,23 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
   return IUGKP_OK;
 }
 
-// Whether a handle's particle step may run by domain blocks (blocks.hpp): 2D
-// flights that go far beyond an emitter tile's window with a tally at every
-// stop, that is with null collisions or expected-value rays.
-bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, bool has_null, double flights)
+// Whether a handle's particle step may run by domain blocks: 2D, enough
+// expected-value rays or far flights with null collisions (kBlockMinFlights).
+bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, double flights, double far)
 {
-  return p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS && o->march == 0 && o->block_size == 0 &&
-         (has_null || o->estimator == IUGKP_EST_EXPECTED) && p->nx <= 0xffff && p->ny <= 0xffff &&
-         flights >= kBlockMinFlights;
+  if (p->dim != 2 || o->scheme != IUGKP_SCHEME_EMITTERS || o->march != 0 || o->block_size != 0 ||
+      p->nx > 0xffff || p->ny > 0xffff)
+    return false;
+  return o->estimator == IUGKP_EST_EXPECTED ? flights >= kBlockMinFlightsEv : far >= kBlockMinFlights;
+}
+
+// Whether flights with null collisions go far: free path lam on the smallest
+// relaxation time tmin, relaxation times tau[0, n).
+bool flights_go_far(const iugkp_problem *p, const double *tau, int n, double tmin, double lam)
+{
+  double sum = 0.0;
+  for (int c = 0; c < n; ++c) sum += tau[c] / tmin;
+  return sum > n && lam * (sum / n) > kWindowHalo * std::min(p->dx, p->dy);
 }
 
 int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, bool multi_cg,
@@ -872,6 +885,10 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   d.tol2 = o->cg_tol * o->cg_tol;
   d.cg_max = o->cg_max_iters;
   d.F = scale_exponent(p, tmin, wall, T0, src);
+  {
+    const double n = static_cast<double>(ne) * d.N;
+    ih.blocks = multi_cg && blocks_wanted(p, o, n, flights_go_far(p, tau.data(), nc, tmin, d.lam_min) ? n : 0.0);
+  }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
   if (multi_cg) split_tiles(ih, kSplitTarget);
 
@@ -1021,7 +1038,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
   const bool lam_stripes = d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
   if (multi_cg && p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS &&
-      !blocks_wanted(p, o, d.has_null, static_cast<double>(ne) * d.N) &&
+      !ih.blocks &&
       ((ev && o->march >= 2) ||
        (!ev && o->tally_faces != IUGKP_FACES_OFF &&
         (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0)))))) {
@@ -1194,9 +1211,12 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   }
 
   rest.assign(K - 1, InstHost{});
-  bool any_null = false;
-  for (int k = 0; k < K; ++k) any_null = any_null || has_null[k];
-  const bool blocks = blocks_wanted(p, o, any_null, static_cast<double>(K) * ne * N);
+  double far = 0.0;
+  for (int k = 0; k < K; ++k)
+    if (flights_go_far(p, tau.data() + static_cast<size_t>(k) * nc, nc, ts[k], lam[k]))
+      far += static_cast<double>(ne) * N;
+  const bool blocks = blocks_wanted(p, o, static_cast<double>(K) * ne * N, far);
+  ih0.blocks = blocks;
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
   int ok = 1;
   unsigned long long acc = 0, wall_acc = 0;
@@ -1945,11 +1965,11 @@ int plan_blocks(iugkp_handle *h)
   std::vector<iugkp::BlockUnit> units;
   double flights = 0.0;
   for (int k = 0; k < K; ++k) flights += static_cast<double>(m.n_emit) * band_of(h, k).d.N;
-  // chunks of a unit of round 0
   const int target = h->ih.d.estimator ? kBlockTargetEv : kBlockTarget;
-  const double share = std::min(static_cast<double>(iugkp::kUnitChunksMax),
-                                std::max(static_cast<double>(iugkp::kUnitChunksMin),
-                                         std::ceil(flights / iugkp::kChunk / target)));
+  // chunks of a unit of round 0
+  const double share = static_cast<double>(iugkp::unit_chunks(
+      static_cast<uint32_t>(std::min(flights / iugkp::kChunk + K * T1, 4e9)),
+      static_cast<uint32_t>(target), static_cast<uint32_t>(n_cu)));
   unsigned long long slab = 0, base = 0;
   int ex_max = 1, ey_max = 1;
   for (int k = 0; k < K; ++k)
@@ -2035,6 +2055,7 @@ int plan_blocks(iugkp_handle *h)
   r.blk = d_blk;
   r.T = T;
   r.target = static_cast<uint32_t>(target);
+  r.cus = static_cast<uint32_t>(n_cu);
   r.units0 = d_units0;
   r.n_units0 = static_cast<uint32_t>(units.size());
   b.grid = n_cu;
@@ -2080,17 +2101,7 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
   const int K = h->bh.K;
   h->block = options->block_size ? options->block_size : 256;
   // by domain blocks where wanted; without the memory as without them
-  const bool wanted =
-      [&] {
-        bool null = false;
-        double n = 0.0;
-        for (int k = 0; k < K; ++k) {
-          null = null || band_of(h, k).d.has_null;
-          n += static_cast<double>(h->ih.d.m.n_emit) * band_of(h, k).d.N;
-        }
-        return blocks_wanted(problem, options, null, n);
-      }();
-  if (wanted && (rc = plan_blocks(h)) && rc != IUGKP_E_NOMEM) {
+  if (h->ih.blocks && (rc = plan_blocks(h)) && rc != IUGKP_E_NOMEM) {
     free_handle(h);
     return rc;
   }

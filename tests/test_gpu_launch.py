@@ -130,8 +130,8 @@ BLOCKS = {
     "null_many": (lambda: _two_tau(211, 197, 0.004, 0.4, 300_000), {}),
     "ev_one_block": (lambda: cavity_2d(n=90, ny=77, kn=0.3, particles=220_000, newton=False), {"estimator": 1}),
     "ev_many": (lambda: cavity_2d(n=230, ny=170, kn=0.2, particles=220_000, newton=False), {"estimator": 1}),
-    "null_few_flights": (lambda: _two_tau(70, 61, 0.05, 0.5, 33_000), {}),
-    "null_no_weight": (lambda: _two_tau(101, 90, 0.05, 0.5, 60_000), {"T_init": "ref"}),
+    "null_few_flights": (lambda: _two_tau(70, 61, 0.2, 0.9, 37_000), {}),
+    "null_no_weight": (lambda: _two_tau(101, 90, 0.1, 0.5, 60_000), {"T_init": "ref"}),
     "ev_null": (lambda: _two_tau(150, 141, 0.05, 0.5, 220_000), {"estimator": 1}),
 }
 
