@@ -47,6 +47,15 @@ int fail(int code, const std::string &msg)
 
 constexpr int kCgGroupMax = 256;             // workgroups of a group, at most one per CU
 constexpr int kCgGridMax = 64;               // workgroups of one CG group (barrier arrivals)
+// The banded multigrid CG of a single solve runs on a workgroup per two rows of
+// its level 1 (its phases wait for the loads of a few cells per thread one after
+// another): as many as one XCD holds while the solve's vectors stay in its L2
+// (up to kMgXcdBlocks blocks of 256 cells), beyond that kMgGroupMax anywhere.
+// us per solve on 32 in one XCD / up to 128 anywhere: 160 x 160 cells 577 / 667,
+// 224 x 224 776 / 789, 256 x 256 904 / 795, 512 x 512 1861 / 1478; 128 x 128 on 8 /
+// 32: 559 / 432.
+constexpr int kMgXcdBlocks = 200;
+constexpr int kMgGroupMax = 128;
 // tree blocks per CG workgroup of a single solve: a mesh of up to kCgAloneMax
 // blocks takes one workgroup (5 blocks 297 us per solve against 356 on two;
 // 12 blocks 6.9 ms against 6.6 on three), others kCgWavesMin, and up to
@@ -199,11 +208,12 @@ struct InstHost {
   // CU): grouped stepping keeps the CGs in flight within the device
   double cg_cus = 0.0;
   // multigrid-preconditioned CG (cg_precond == IUGKP_PRECOND_MG): level table
-  int mg_L = 0, mg_Lg = 0, mg_grid = 1, mg_threads = 64;
+  int mg_L = 0, mg_Lg = 0, mg_grid = 1, mg_launch = 1, mg_threads = 64;
   size_t mg_lds = 0;
   iugkp::MGLevel *mg_lv = nullptr;
   // its banded form: the second buffers of r and s, the LDS layout
-  int mg_band = 0, mg_stage0 = 0, mg_stage_n = 0;
+  int mg_band = 0, mg_stage0 = 0, mg_stage_n = 0, mg_zero0 = 0, mg_zero_n = 0,
+      mg_slots = 0;
   double *mg_r2 = nullptr, *mg_s2 = nullptr;
   // row-stripe particle step for face-tallied iterations (single solves)
   int stripe_R = 0, stripe_S = 0, stripe_C = 0;
@@ -566,11 +576,33 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-  const size_t lds_budget = static_cast<size_t>(lds_max) - 12 * 1024;  // static: reductions, level table
+  const size_t lds_budget = static_cast<size_t>(lds_max) - 13 * 1024;  // static: reductions, level table
+  // (MgLds: three vectors, and the rows as three arrays, four in 2D)
+  auto level_words = [&](int from, int k, long long &rows) {
+    const bool y = lv[from].ny > 1;
+    rows += (y ? 4ll : 3ll) * iugkp::mg_row_words(lv[k].nx, lv[k].ny, y);
+    return 3ll * iugkp::mg_vec_words(lv[k].nx, lv[k].ny, y);
+  };
+  // (records for the levels after the first, where they fit the threads)
+  const int wg_threads = single ? 64 * (o->cg_waves != 0 ? std::abs(o->cg_waves) : kCgWavesDefault)
+                                : 64 * iugkp::kMgPoolWaves;
+  auto slots_for = [&](int from) {
+    const int n = L - 1 - from;
+    return n >= 1 && n <= iugkp::kMgSlots && lv[from].ny > 1 && lv[from + 1].n <= wg_threads ? n : 0;
+  };
+  auto local_words = [&](int from, long long &rows) {
+    long long vecs = 0;
+    rows = 0;
+    const int slots = slots_for(from);
+    for (int k = from; k < L; ++k)
+      if (slots && k > from) rows += iugkp::mg_rec_words(lv[k].nx, lv[k].ny);
+      else vecs += level_words(from, k, rows);
+    return vecs;
+  };
   auto local_bytes = [&](int from) {
-    size_t w = 0;
-    for (int k = from; k < L; ++k) w += 6 * static_cast<size_t>(lv[k].n);
-    return w * sizeof(double);
+    long long rows = 0;
+    const long long vecs = local_words(from, rows);
+    return static_cast<size_t>(vecs + rows + (from > 0 ? lv[from].n : 0)) * sizeof(double);
   };
   int Lg = 0;
   while (Lg < L && lv[Lg].n > iugkp::kMgLocalMax) ++Lg;
@@ -578,37 +610,50 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
   if (local_bytes(Lg) > lds_budget) return fail(IUGKP_E_DEVICE, "no LDS for the multigrid");
   const int waves = o->cg_waves != 0 ? std::abs(o->cg_waves) : kCgWavesDefault;
   const int nb0 = cdiv(lv[0].n, iugkp::kTree);
-  const int G = std::max(1, std::min(std::min(cdiv(nb0, waves), kCgGridMax), n_cu));
+  const int G0 = std::max(1, std::min(std::min(cdiv(nb0, waves), kCgGridMax), n_cu));
+  int G = G0;
+  if (single && Lg > 0 && has_y)
+    G = std::max(G0, std::min({nb0 <= kMgXcdBlocks ? iugkp::kCusPerXcd : kMgGroupMax, lv[1].ny / 2, n_cu}));
   // The banded form (2D meshes, or no grid level): LDS for the level Lg
   // result kept through a band phase, then the LDS levels or the staging of
   // a band window, whichever is larger.  Its windows for a group of Gp
   // members (one window per phase when the budget allows; a batch instance's
   // group changes from replay to replay, so it takes the largest stage), and
   // the smallest stage with one row (one block) per window.
-  // (the LDS levels' rows, 3 doubles per cell, stay for the whole solve; their
-  // vectors, 3 per cell, share the stage with the band windows)
-  const long long levels_words = static_cast<long long>(local_bytes(Lg) / sizeof(double)) / 2;
-  const long long rows_words = levels_words;
+  // (the LDS levels' rows stay for the whole solve; their vectors share the
+  // stage with the band windows)
   auto band_need = [&](int Gp) {
-    long long w = levels_words;
+    long long rows = 0, w = local_words(Lg, rows);
     for (int k = 0; k < Lg; ++k) {
-      const long long nxk = lv[k].nx;
-      w = std::max(w, (6ll * cdiv(lv[k + 1].ny, Gp) + 10) * nxk);
-      if (k >= 1) w = std::max(w, (3ll * cdiv(lv[k].ny, Gp) + 8) * nxk);
+      const long long S = lv[k].nx + 1;
+      w = std::max(w, (6ll * cdiv(lv[k + 1].ny, Gp) + 10) * S + iugkp::kMgWindow);
+      if (k >= 1) w = std::max(w, (3ll * cdiv(lv[k].ny, Gp) + 8) * S + iugkp::kMgWindow);
     }
     if (Lg >= 1) {
       const long long nx0 = lv[0].nx;
       const long long rmax = 2 + (static_cast<long long>(iugkp::kTree) * cdiv(nb0, Gp) - 1 + nx0 - 1) / nx0;
-      w = std::max(w, (3 * rmax + 14) * nx0);
+      w = std::max(w, (3 * rmax + 14) * (nx0 + 1) + iugkp::kMgWindow);
     }
     return w;
   };
-  const long long e_words = (Lg >= 1) ? lv[Lg].n : 0;
-  const long long band_budget =
-      static_cast<long long>(lds_budget / sizeof(double)) - e_words - rows_words;
-  const bool band = (Lg == 0 || has_y) && 64 * waves <= iugkp::kMgBandThreads &&
-                    band_need(1 << 20) <= band_budget;
-  const int stage0 = band ? static_cast<int>(e_words + rows_words) : 0;
+  long long rows_words = 0, e_words = 0, band_budget = 0;
+  auto band_fits = [&] {
+    local_words(Lg, rows_words);
+    e_words = (Lg >= 1) ? lv[Lg].n : 0;
+    band_budget = static_cast<long long>(lds_budget / sizeof(double)) - e_words - rows_words;
+    return band_need(1 << 20) <= band_budget;
+  };
+  // (rows too long for a window beside the LDS levels: fewer of those)
+  const bool may_band = (Lg == 0 || has_y) && 64 * waves <= iugkp::kMgBandThreads;
+  const int Lg0 = Lg;
+  while (may_band && !band_fits() && Lg > 0 && Lg < L - 1) ++Lg;
+  const bool band = may_band && band_fits();
+  if (!band) {
+    Lg = Lg0;
+    G = G0;
+    band_fits();
+  }
+  const int stage0 = static_cast<int>(e_words + rows_words);
   const long long stage_n =
       band ? std::min(band_budget, band_need(single ? G : 1)) : 0;
 #define ALLOC(ptr, cnt) \
@@ -639,22 +684,35 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
     ALLOC(lv[k].e, lv[k].n);
   }
   if (Lg > 0) ALLOC(lv[Lg].b, lv[Lg].n);
-  // LDS offsets: banded, [E][rows of every LDS level][vectors | staging];
-  // otherwise each level's vectors and rows together
+  // LDS offsets: [E][rows of every LDS level][b vectors][x and t vectors], the
+  // banded form's windows over the vectors
+  const bool ly = lv[Lg].ny > 1;
+  const int slots = slots_for(Lg), Lv = slots ? Lg + 1 : L;
   int off = stage0, roff = static_cast<int>(e_words);
-  for (int k = Lg; k < L; ++k) {
+  for (int k = 0; k < L; ++k) lv[k].rnx = 1.0f / static_cast<float>(lv[k].nx);
+  for (int k = Lg; k < Lv; ++k) {
+    const int rw = iugkp::mg_row_words(lv[k].nx, lv[k].ny, ly);
+    lv[k].dg = roff;
+    lv[k].rdl = roff + rw;
+    lv[k].lgx = roff + 2 * rw;
+    lv[k].lgy = roff + 3 * rw;
+    roff += (ly ? 4 : 3) * rw;
     lv[k].lb = off;
-    lv[k].lx = off + lv[k].n;
-    lv[k].lt = off + 2 * lv[k].n;
-    off += 3 * lv[k].n;
-    if (band) {
-      lv[k].lc = roff;
-      roff += 3 * lv[k].n;
-    } else {
-      lv[k].lc = off;
-      off += 3 * lv[k].n;
-    }
+    off += iugkp::mg_vec_words(lv[k].nx, lv[k].ny, ly);
   }
+  for (int k = Lv; k < L; ++k) {
+    lv[k].rec = roff;
+    roff += iugkp::mg_rec_words(lv[k].nx, lv[k].ny);
+  }
+  ih.mg_zero0 = off;
+  for (int k = Lg; k < Lv; ++k) {
+    lv[k].lx = off;
+    off += iugkp::mg_vec_words(lv[k].nx, lv[k].ny, ly);
+    lv[k].lt = off;
+    off += iugkp::mg_vec_words(lv[k].nx, lv[k].ny, ly);
+  }
+  ih.mg_slots = slots;
+  ih.mg_zero_n = off - ih.mg_zero0;
   for (int k = 0; k + 1 < L; ++k) {
     const int nf = std::max(lv[k + 1].ny * (lv[k + 1].nx + 1), (lv[k + 1].ny + 1) * lv[k + 1].nx);
     iugkp::mg_coarsen_faces_kernel<<<cdiv(nf, 256), 256, 0, s>>>(
@@ -663,6 +721,18 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
     iugkp::mg_coarsen_diag_kernel<<<cdiv(lv[k + 1].n, 256), 256, 0, s>>>(
         lv[k + 1], has_y, const_cast<double *>(lv[k + 1].diag));
   }
+  if (band)
+    for (int k = 0; k < Lg; ++k) {
+      const size_t nfx = static_cast<size_t>(lv[k].ny) * (lv[k].nx + 1);
+      const size_t nfy = static_cast<size_t>(lv[k].ny + 1) * lv[k].nx;
+      double *z = nullptr;
+      ALLOC(z, nfx + nfy + lv[k].n + 16);
+      lv[k].gxz = z;
+      lv[k].gyz = z + nfx + 8;
+      lv[k].rd = z + nfx + nfy + 16;
+      iugkp::mg_rows_kernel<<<cdiv(std::max(nfx, nfy), 256), 256, 0, s>>>(lv[k], z, z + nfx + 8,
+                                                                          z + nfx + nfy + 16);
+    }
   HIP_TRY(hipGetLastError());
   ALLOC(ih.mg_lv, L);
 #undef ALLOC
@@ -685,6 +755,7 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
   ih.mg_stage_n = static_cast<int>(stage_n);
   ih.cg_cus = static_cast<double>(G) / per_cu;
   ih.mg_grid = G;
+  ih.mg_launch = group_launch(G, per_cu, nb0);
   ih.mg_threads = 64 * waves;
   ih.mg_lds = lds;
   return IUGKP_OK;
@@ -1589,12 +1660,18 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
     ma.band = ih.mg_band;
     ma.stage0 = ih.mg_stage0;
     ma.stage_n = ih.mg_stage_n;
-    iugkp::zero_u32_kernel<<<1, 64, 0, s>>>(ih.cg_barrier, 2);
+    ma.zero0 = ih.mg_zero0;
+    ma.zero_n = ih.mg_zero_n;
+    ma.slots = ih.mg_slots;
+    ma.flags = ih.cg_barrier + iugkp::kGroupWords;
+    const int words = iugkp::kGroupWords + ih.mg_grid * iugkp::kCgFlagStep;
+    iugkp::zero_u32_kernel<<<cdiv(words, 256), 256, 0, s>>>(ih.cg_barrier, words);
     if (ev_a) HIP_TRY(hipEventRecord(ev_a, s));
-    void *args[] = {&ma};
+    int group = ih.mg_grid;
+    void *args[] = {&ma, &group};
     HIP_TRY(hipLaunchKernel(ih.mg_band ? reinterpret_cast<const void *>(iugkp::mgcg_band_kernel)
                                        : reinterpret_cast<const void *>(iugkp::mgcg_kernel),
-                            dim3(ih.mg_grid), dim3(ih.mg_threads), args, ih.mg_lds, s));
+                            dim3(ih.mg_launch), dim3(ih.mg_threads), args, ih.mg_lds, s));
     if (ev_b) HIP_TRY(hipEventRecord(ev_b, s));
     return IUGKP_OK;
   }
@@ -3345,6 +3422,9 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
       ma.band = ih.mg_band;
       ma.stage0 = ih.mg_stage0;
       ma.stage_n = ih.mg_stage_n;
+      ma.zero0 = ih.mg_zero0;
+      ma.zero_n = ih.mg_zero_n;
+      ma.slots = ih.mg_slots;
     }
     if (any_mg) {
       if (hipMalloc(reinterpret_cast<void **>(&b->d_mg_args), n * sizeof(iugkp::MGArgs)) !=

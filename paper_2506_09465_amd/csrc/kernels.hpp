@@ -2318,6 +2318,52 @@ __device__ __forceinline__ bool grid_barrier(unsigned int *counter, unsigned int
   return s_abort == 0;
 }
 
+// The same barrier with a word per workgroup, its last epoch, in place of the
+// counter, whose arrivals follow one another: a store per workgroup, then one
+// wavefront polls the group's words.  Device-wide a line per word (stores to
+// one line follow one another at the coherence point: 512 x 512 cells on 86
+// workgroups, plain CG, 6.9 -> 5.4 us per iteration); in one XCD's L2 the words
+// share lines and one load polls them.  words[1] = abort flag as above.
+constexpr int kCgFlagStep = 32;        // words between two workgroups' device-wide barrier words
+
+template <int SPAN>
+__device__ __forceinline__ bool flag_barrier(unsigned int *words, unsigned int *flags, int rank,
+                                             int G, unsigned int &epoch)
+{
+  constexpr int kStep = SPAN == kSpanDevice ? kCgFlagStep : 1;
+  __shared__ int s_abort;
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  __builtin_amdgcn_s_waitcnt(0);                  // this wave's stores have completed
+  __syncthreads();
+  epoch += 1;
+  if (threadIdx.x < 64) {
+    if (lane == 0) {
+      if (SPAN == kSpanDevice)
+        __hip_atomic_store(flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        __hip_atomic_store(flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    long spins = 0;
+    int abort = 0;
+    for (;;) {
+      bool ok = true;
+      for (int i = lane; i < G; i += 64)
+        ok = ok && __hip_atomic_load(flags + i * kStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
+      if (__all(ok)) break;
+      if (++spins > kBarrierSpinLimit ||
+          ((spins & 1023) == 0 &&
+           __hip_atomic_load(words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+        __hip_atomic_store(words + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        abort = 1;
+        break;
+      }
+    }
+    if (lane == 0) s_abort = abort;
+  }
+  __syncthreads();
+  return s_abort == 0;
+}
+
 // ---------------------------------------------------------------------------
 // The workgroups of a solve's group, elected on the device.  A launch of
 // kXcds G workgroups (the dispatcher deals them out to the XCDs in turn) gives
@@ -2407,7 +2453,6 @@ __device__ __forceinline__ bool elect_group(unsigned int *words, int G, int &ran
 constexpr int kCgWavesMax = 12;        // 768 threads: about 170 VGPRs per lane for the register form
 constexpr int kCgThreadsMax = 64 * kCgWavesMax;
 constexpr int kCgShareBlocks = 64;     // block sums of an XCD's group loaded by shares beyond this
-constexpr int kCgFlagStep = 32;        // words between two workgroups' device-wide barrier words
 
 struct CGArgs {
   Mesh m;
@@ -2723,7 +2768,6 @@ __device__ __forceinline__ void cg_reg_run(const CGArgs &a, int rank, int G)
 {
   extern __shared__ double dyn[];          // a zero, then r on [h0, h1)
   __shared__ double red[2 * kTree];        // chunk sums when nb > 256, or one workgroup's sums
-  __shared__ int s_abort;
   double *const stage = dyn + 1;
   unsigned int epoch = 0;
   const int n = a.m.n_cells, nx = a.m.nx;
@@ -2775,7 +2819,6 @@ __device__ __forceinline__ void cg_reg_run(const CGArgs &a, int rank, int G)
   const unsigned any_pub = __any(pubm != 0u);
   if (tid == 0) {
     dyn[0] = 0.0;
-    s_abort = 0;
   }
   for (int i = tid; i < h1 - h0; i += nt) stage[i] = a.b[h0 + i];
   __syncthreads();
@@ -2825,37 +2868,7 @@ __device__ __forceinline__ void cg_reg_run(const CGArgs &a, int rank, int G)
   };
   auto group_barrier = [&]() -> bool {
     if (!FLAGS) return grid_barrier(a.barrier, epoch, G);
-    // (device-wide a line per word: stores to one line follow one another at
-    // the coherence point, 512 x 512 cells on 86 workgroups 6.9 -> 5.4 us per
-    // iteration; in one XCD's L2 the words share lines, one load polls them)
-    constexpr int kStep = SPAN == kSpanDevice ? kCgFlagStep : 1;
-    __builtin_amdgcn_s_waitcnt(0);                  // this wave's stores have completed
-    __syncthreads();
-    epoch += 1;
-    if (wave == 0) {
-      if (lane == 0) {
-        if (SPAN == kSpanDevice)
-          __hip_atomic_store(a.flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-          __hip_atomic_store(a.flags + rank * kStep, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-      long spins = 0;
-      for (;;) {
-        bool ok = true;
-        for (int i = lane; i < G; i += 64)
-          ok = ok && __hip_atomic_load(a.flags + i * kStep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
-        if (__all(ok)) break;
-        if (++spins > kBarrierSpinLimit ||
-            ((spins & 1023) == 0 &&
-             __hip_atomic_load(a.barrier + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-          __hip_atomic_store(a.barrier + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          s_abort = 1;
-          break;
-        }
-      }
-    }
-    __syncthreads();
-    return s_abort == 0;
+    return flag_barrier<SPAN>(a.barrier, a.flags, rank, G, epoch);
   };
   // buffer b of every member: this thread's halo cell, and the sums; false on
   // an abort

@@ -44,10 +44,58 @@ constexpr int kMgLocalMax = 1024;       // levels up to this size live in LDS
 struct MGLevel {
   int nx, ny, n, has_y;
   const double *gx, *gy, *diag;         // operator of the level
+  // banded grid levels: its faces with those at the mesh's edge zeroed, and
+  // the diagonal's reciprocals (mg_recip); padded for reads past a row's end
+  const double *gxz, *gyz, *rd;
   double *b, *xa, *xb, *xd, *e;         // grid levels (level 0: b = r, e = u)
-  int lb, lx, lt, lc;                   // LDS levels: offsets (doubles) of b, x, t and
-                                        // of the rows (3 doubles per cell)
+  int lb, lx, lt;                       // LDS levels: offsets (doubles) of the vectors,
+  int dg, rdl, lgx, lgy;                // and of the rows (MgLds)
+  float rnx;                            // 1 / nx
+  int rec;                              // small levels: offset of the records (MgSlot)
+  // the banded form, filled by each workgroup of the group: its coarse rows and
+  // its rows (level 0: its 256-cell blocks), and the windows each takes
+  int c0, c1, r0, r1, wdown, wup;
 };
+
+// An LDS level.  Its arrays have rows of S = nx + 1 values, the last one a pad:
+// vectors a row of pads before and after too (2D; in 1D one pad before), so
+// that cell (ix, iy), at j = ix + iy S + (2D: S, 1D: 1), has its neighbours at
+// j +- 1 and j +- S, an absent one a pad.  Pads of x and t hold zeros, and the
+// faces at the mesh's edge are stored as zeros: an absent neighbour's term is
+// v - 0 * 0, which is v for every v, so no pass tests for the edges.  Rows: the
+// diagonal, its reciprocal, the left and the lower face of cell (ix, iy) at ix +
+// iy S (its right and upper ones are its neighbours'; the lower faces have a
+// row more).
+struct MgLds {
+  int nx, ny, n, S, lb, lx, lt, dg, rd, gx, gy;
+  float rnx;
+};
+// The levels below the first LDS level, where each has at most a cell per
+// thread and there are at most kMgSlots (a solve's iteration runs mostly in
+// their passes' latency, so indices stay in registers and every access is at a
+// constant from one of them): a record per cell, rows padded as above (a row
+// more at the end), pads all zeros: an absent child's residual is 0 as well.
+constexpr int kMgSlots = 6;
+constexpr int kMgRec = 7;               // dg, rd, left face, lower face, b, x, t
+enum : int { kMgDg = 0, kMgRd = 1, kMgGl = 2, kMgGd = 3, kMgB = 4, kMgX = 5, kMgT = 6 };
+__host__ __device__ inline int mg_rec_words(int nx, int ny)
+{
+  return kMgRec * ((ny + 3) * (nx + 1) + 2);
+}
+struct MgSlot {
+  int n, row, crow;                     // cells; words of a row, and of the next level's
+  int own;                              // this thread's cell
+  int child;                            // the first child of this thread's cell
+  int par, parl, pard;                  // its parent, the left one's and the lower one's
+};
+__host__ __device__ inline int mg_vec_words(int nx, int ny, bool y)
+{
+  return y ? (ny + 2) * (nx + 1) + 2 : nx + 4;
+}
+__host__ __device__ inline int mg_row_words(int nx, int ny, bool y)   // per array
+{
+  return y ? (ny + 1) * (nx + 1) + 2 : nx + 3;
+}
 
 struct MGArgs {
   const MGLevel *lv;                    // [L] level table
@@ -57,13 +105,16 @@ struct MGArgs {
   double *part;                         // [nb][3] block sums of (r, u), (w, u), (r, r)
   double tol2;
   int max_iters;
-  unsigned int *barrier;                // [2], zero at the start of the solve
+  unsigned int *barrier;                // zero at the start of the solve, as are
+  unsigned int *flags;                  // the group's barrier words (single solves)
   DevScalars *sc;
   // the banded form (mgband.hpp): second buffers of r and s, and the dynamic
   // LDS layout, [stage0) the coarse result kept across a band phase, then
   // stage_n doubles holding the LDS levels or a band window's staging
   double *r2, *s2;
   int band, stage0, stage_n;
+  int zero0, zero_n;                    // the x and t vectors of the LDS levels
+  int slots;                            // levels with records, 0: none
 };
 
 // Row c of A_k: the diagonal, the four face conductances and the neighbour
@@ -110,28 +161,60 @@ __device__ __forceinline__ MGRow mg_row(const MGLevel &l, int c)
   return mg_row_at(l, c - iy * l.nx, iy);
 }
 
-// the same row of an LDS level, whose coefficients sit in LDS as three per
-// cell: the diagonal and the right and upper faces (a cell's left face is
-// its left neighbour's right face, its lower face the one below's upper face;
-// an absent neighbour's face is read at the cell itself and never used)
-__device__ __forceinline__ MGRow mg_row_lds_at(const MGLevel &l, const double *lds, int ix, int iy)
+// The reciprocal with which mg_div divides by d: not a number where d or a
+// quotient may leave the range in which its steps are exact.
+__host__ __device__ inline double mg_recip(double d)
 {
-  MGRow r;
-  mg_row_index(r, l.nx, l.ny, ix, iy);
-  const double *k = lds + l.lc;
-  const int c = iy * l.nx + ix;
-  r.dg = k[3 * c];
-  r.gr = k[3 * c + 1];
-  r.gu = k[3 * c + 2];
-  r.gl = k[3 * r.jl + 1];
-  r.gd = k[3 * r.jd + 2];
-  return r;
+  return (d >= 0x1p-300 && d <= 0x1p300) ? 1.0 / d : __builtin_nan("");
 }
 
-__device__ __forceinline__ MGRow mg_row_lds(const MGLevel &l, const double *lds, int c)
+// a / d, correctly rounded, from y = mg_recip(d): two Newton corrections of a
+// y; the last, from a quotient within one unit of the exact one with the
+// remainder exact and y correctly rounded, rounds correctly (Markstein 1990).
+// Quotients that are zero, out of range or not finite are divided.  5
+// dependent operations instead of a division's 11.
+__device__ __forceinline__ double mg_div(double a, double d, double y)
 {
-  const int iy = c / l.nx;
-  return mg_row_lds_at(l, lds, c - iy * l.nx, iy);
+  double q = a * y;
+  q = __builtin_fma(__builtin_fma(-q, d, a), y, q);
+  q = __builtin_fma(__builtin_fma(-q, d, a), y, q);
+  const unsigned e = (static_cast<unsigned>(__double2hiint(q)) >> 20) & 0x7ffu;
+  if (__builtin_expect(e - 723u > 600u, 0)) q = a / d;
+  return q;
+}
+
+// A row of the operator with zero faces at the mesh's edge, and the damped
+// Jacobi sweep of its cell: v = {v_c, v_l, v_r, v_dn, v_up}, an absent
+// neighbour's value 0.
+struct MGRowZ {
+  double dg, rd, gl, gr, gd, gu;
+};
+__device__ __forceinline__ double mg_apply_z(const MGRowZ &r, double vc, double vl, double vr,
+                                             double vd, double vu)
+{
+  double acc = r.dg * vc;
+  acc = acc - r.gl * vl;
+  acc = acc - r.gr * vr;
+  acc = acc - r.gd * vd;
+  return acc - r.gu * vu;
+}
+__device__ __forceinline__ double mg_sweep_z(const MGRowZ &r, double b, double vc, double vl,
+                                             double vr, double vd, double vu)
+{
+  const double t = b - mg_apply_z(r, vc, vl, vr, vd, vu);
+  return vc + mg_div(kMgOmega * t, r.dg, r.rd);
+}
+// the sweep from zero
+__device__ __forceinline__ double mg_sweep_first_z(double bv, double dg, double rd)
+{
+  return 0.0 + mg_div(kMgOmega * bv, dg, rd);
+}
+
+// i / nx for i < 2^20 (rnx = 1 / nx: the quotient's error stays below half
+// the distance of (i + 0.5) / nx from a whole number)
+__device__ __forceinline__ int mg_row_of(int i, float rnx)
+{
+  return static_cast<int>((static_cast<float>(i) + 0.5f) * rnx);
 }
 
 // aggregates (on a level of nxc columns) of the cell of row r and of its
@@ -186,24 +269,25 @@ __device__ __forceinline__ double mg_apply(const MGLevel &l, int c, Get v)
   return mg_apply_row(mg_row(l, c), c, v);
 }
 
-// Loads and stores of values other workgroups (SC = agent scope) or only the
-// waves of this workgroup (SC = workgroup scope, a solve run by a single
-// workgroup) write between barriers.
-template <int SC>
+// Loads and stores of values that other workgroups (kSpanOne: only other waves
+// of this one) write between barriers.
+template <int SPAN>
 __device__ __forceinline__ double mld(const double *p)
 {
-  return __hip_atomic_load(const_cast<double *>(p), __ATOMIC_RELAXED, SC);
+  return __hip_atomic_load(const_cast<double *>(p), __ATOMIC_RELAXED,
+                           SPAN == kSpanOne ? __HIP_MEMORY_SCOPE_WORKGROUP
+                                            : __HIP_MEMORY_SCOPE_AGENT);
 }
-template <int SC>
+template <int SPAN>
 __device__ __forceinline__ void mst(double *p, double v)
 {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, SC);
+  xst<SPAN>(p, v);
 }
 
 // Sums of the nb published NV-tuples (layout [nb][NV]) in the fixed order of
 // the host-side definition: the 256-element tree over each chunk, then over
 // the chunk sums (nb <= 65536).  Every thread gets every result.
-template <int NV, int SC>
+template <int NV, int SPAN>
 __device__ __forceinline__ void group_tree_n(const double *part, int nb, double *red,
                                              double (&out)[NV])
 {
@@ -216,7 +300,7 @@ __device__ __forceinline__ void group_tree_n(const double *part, int nb, double 
     for (int q = 0; q < 4; ++q) {
       const int i = k * kTree + lane + 64 * q;
 #pragma unroll
-      for (int j = 0; j < NV; ++j) v[j][q] = i < nb ? mld<SC>(&part[NV * i + j]) : 0.0;
+      for (int j = 0; j < NV; ++j) v[j][q] = i < nb ? mld<SPAN>(&part[NV * i + j]) : 0.0;
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) r[j] = wave_tree256(v[j][0], v[j][1], v[j][2], v[j][3]);
@@ -296,164 +380,467 @@ __device__ __forceinline__ void mg_cells(int N, Ld load, Fin finish)
   }
 }
 
-// the five row coefficients of every cell of the LDS levels (no barrier)
-__device__ __forceinline__ void mg_lds_rows(const MGLevel *lv, int Lg, int L, double *lds)
+// A pointer to global memory, read as a scalar: a pointer loaded from memory is
+// otherwise taken for one to any memory, with slower accesses that also wait
+// for the LDS.
+template <class T>
+__device__ __forceinline__ T *mg_global(T *p)
 {
-  for (int k = Lg; k < L; ++k) {
-    const MGLevel F = lv[k];
-    mg_cells<4>(
-        F.n, [&](int i) { return mg_row(F, i); },
-        [&](int i, const MGRow &r) {
-          double *dst = lds + F.lc + 3 * i;
-          dst[0] = r.dg;
-          dst[1] = r.gr;
-          dst[2] = r.gu;
+  typedef __attribute__((address_space(1))) T GT;
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
+  const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
+  return (T *)(GT *)((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+__device__ __forceinline__ int mg_scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// a grid level's descriptor as scalars
+__device__ __forceinline__ MGLevel mg_level(const MGLevel &l)
+{
+  MGLevel f = l;
+  f.nx = mg_scalar(l.nx);
+  f.ny = mg_scalar(l.ny);
+  f.n = mg_scalar(l.n);
+  f.has_y = mg_scalar(l.has_y);
+  f.gx = mg_global(l.gx);
+  f.gy = mg_global(l.gy);
+  f.diag = mg_global(l.diag);
+  f.gxz = mg_global(l.gxz);
+  f.gyz = mg_global(l.gyz);
+  f.rd = mg_global(l.rd);
+  f.b = mg_global(l.b);
+  f.xa = mg_global(l.xa);
+  f.xb = mg_global(l.xb);
+  f.xd = mg_global(l.xd);
+  f.e = mg_global(l.e);
+  f.rnx = __int_as_float(mg_scalar(__float_as_int(l.rnx)));
+  f.rec = mg_scalar(l.rec);
+  f.c0 = mg_scalar(l.c0);
+  f.c1 = mg_scalar(l.c1);
+  f.r0 = mg_scalar(l.r0);
+  f.r1 = mg_scalar(l.r1);
+  f.wdown = mg_scalar(l.wdown);
+  f.wup = mg_scalar(l.wup);
+  return f;
+}
+
+// an LDS level's descriptor as scalars
+__device__ __forceinline__ MgLds mg_lds_level(const MGLevel &l)
+{
+  MgLds f;
+  f.nx = mg_scalar(l.nx);
+  f.ny = mg_scalar(l.ny);
+  f.n = mg_scalar(l.n);
+  f.S = f.nx + 1;
+  f.lb = mg_scalar(l.lb);
+  f.lx = mg_scalar(l.lx);
+  f.lt = mg_scalar(l.lt);
+  f.dg = mg_scalar(l.dg);
+  f.rd = mg_scalar(l.rdl);
+  f.gx = mg_scalar(l.lgx);
+  f.gy = mg_scalar(l.lgy);
+  f.rnx = __int_as_float(mg_scalar(__float_as_int(l.rnx)));
+  return f;
+}
+
+// a solve's arguments, those of a batch being read from memory
+__device__ __forceinline__ MGArgs mg_args(const MGArgs &in)
+{
+  MGArgs a = in;
+  a.lv = mg_global(in.lv);
+  a.b = mg_global(in.b);
+  a.x = mg_global(in.x);
+  a.p = mg_global(in.p);
+  a.s = mg_global(in.s);
+  a.w = mg_global(in.w);
+  a.part = mg_global(in.part);
+  a.barrier = mg_global(in.barrier);
+  a.sc = mg_global(in.sc);
+  a.r2 = mg_global(in.r2);
+  a.s2 = mg_global(in.s2);
+  return a;
+}
+
+// the rows of the LDS levels, and zeros in the pads of their vectors (no barrier)
+__device__ __forceinline__ void mg_lds_rows(const MGLevel *lv, int Lg, int L, double *lds,
+                                            int zero0, int zero_n, int slots)
+{
+  const bool Y = lv[Lg].ny > 1;
+  for (int k = Lg + 1; slots && k < L; ++k) {
+    const MGLevel F = mg_level(lv[k]);
+    const int S = F.nx + 1;
+    for (int i = threadIdx.x; i < mg_rec_words(F.nx, F.ny) / kMgRec; i += blockDim.x) {
+      const int r = i / S - 1, col = i - (r + 1) * S;
+      const bool cell = r >= 0 && r < F.ny && col < F.nx;
+      const int c = cell ? r * F.nx + col : 0;
+      double *const R = lds + F.rec + kMgRec * i;
+      const double dg = F.diag[c], gl = F.gx[cell ? r * S + col : 0], gd = Y ? F.gy[c] : 0.0;
+      R[kMgDg] = cell ? dg : 0.0;
+      R[kMgRd] = cell ? mg_recip(dg) : 0.0;
+      R[kMgGl] = cell && col > 0 ? gl : 0.0;
+      R[kMgGd] = cell && r > 0 ? gd : 0.0;
+      R[kMgB] = 0.0;
+      R[kMgX] = 0.0;
+      R[kMgT] = 0.0;
+    }
+  }
+  for (int k = Lg; k < (slots ? Lg + 1 : L); ++k) {
+    const MGLevel F = mg_level(lv[k]);
+    const int S = F.nx + 1;
+    mg_cells<1>(
+        Y ? (F.ny + 1) * S : S,
+        [&](int i) {
+          const int r = i / S, col = i - r * S;
+          const bool cell = col < F.nx && r < F.ny;
+          const int c = cell ? r * F.nx + col : 0;
+          MGRowZ v;
+          v.dg = F.diag[c];
+          v.gl = F.gx[cell ? r * S + col : 0];
+          v.gd = Y ? F.gy[cell ? r * F.nx + col : 0] : 0.0;
+          if (!cell || col == 0) v.gl = 0.0;
+          if (!cell || r == 0) v.gd = 0.0;
+          return v;
+        },
+        [&](int i, const MGRowZ &v) {
+          lds[F.dg + i] = v.dg;
+          lds[F.rdl + i] = mg_recip(v.dg);
+          lds[F.lgx + i] = v.gl;
+          if (Y) lds[F.lgy + i] = v.gd;
         });
+  }
+  for (int i = threadIdx.x; i < zero_n; i += blockDim.x) lds[zero0 + i] = 0.0;
+}
+
+// this thread's places in the records of levels Lg + 1 .. Lg + slots
+__device__ __forceinline__ void mg_slots(const MGLevel *lv, int Lg, int slots,
+                                         MgSlot (&sl)[kMgSlots])
+{
+  const int tid = static_cast<int>(threadIdx.x);
+#pragma unroll
+  for (int s = 0; s < kMgSlots; ++s) {
+    MgSlot v{0, 0, 0, 0, 0, 0, 0, 0};
+    if (s < slots) {
+      const MGLevel &F = lv[Lg + 1 + s], &U = lv[Lg + s], &C = lv[Lg + 1 + (s + 1 < slots ? s + 1 : s)];
+      const int S = F.nx + 1, Sc = C.nx + 1, Su = U.nx + 1;
+      const int i = tid < F.n ? tid : 0, r = i / F.nx, col = i - r * F.nx;
+      v.n = mg_scalar(F.n);
+      v.row = mg_scalar(kMgRec * S);
+      v.crow = mg_scalar(kMgRec * Sc);
+      v.own = F.rec + kMgRec * ((r + 1) * S + col);
+      v.child = U.rec + kMgRec * ((2 * r + 1) * Su + 2 * col);
+      v.par = C.rec + kMgRec * (((r >> 1) + 1) * Sc + (col >> 1));
+      v.parl = v.par - ((col & 1) ? 0 : kMgRec);
+      v.pard = v.par - ((r & 1) ? 0 : kMgRec * Sc);
+    }
+    sl[s] = v;
+  }
+}
+
+// The part of the V-cycle on the records: from level Lg + 1's b and x to its t.
+// Levels of at most 64 cells are run by wavefront 0 alone: its LDS operations
+// execute in order, so their passes need no workgroup barrier.
+__device__ __forceinline__ void mg_slot_cycle(double *lds, const MgSlot (&sl)[kMgSlots], int slots)
+{
+  const int tid = static_cast<int>(threadIdx.x);
+  auto meet = [](bool alone) {
+    if (alone) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  auto row = [](const double *V, int S) {
+    return MGRowZ{V[kMgDg], V[kMgRd], V[kMgGl], V[kMgGl + kMgRec], V[kMgGd], V[kMgGd + S]};
+  };
+  // from field `in` to the other of x and t
+  auto sweep = [&](const MgSlot &f, int in, int out) {
+    if (tid < f.n) {
+      double *const V = lds + f.own;
+      const double *const X = V + in;
+      V[out] = mg_sweep_z(row(V, f.row), V[kMgB], X[0], X[-kMgRec], X[kMgRec], X[-f.row], X[f.row]);
+    }
+    meet(f.n <= 64);
+  };
+#pragma unroll
+  for (int s = 0; s + 1 < kMgSlots; ++s) {
+    if (s + 1 >= slots) break;
+    if (sl[s].n <= 64 && tid >= 64) break;
+    sweep(sl[s], kMgX, kMgT);
+    const MgSlot &c = sl[s + 1];
+    if (tid < c.n) {
+      const int S = sl[s].row;
+      const double *const F = lds + c.child, *const F2 = F + S, *const F3 = F2 + S;
+      const double *const T = F + kMgT, *const T2 = F2 + kMgT;
+      constexpr int R = kMgRec;
+      const double v00 = T[0], v01 = T[R], v10 = T2[0], v11 = T2[R];
+      const double m0 = F2[kMgGd], m1 = F2[kMgGd + R];
+      const MGRowZ r0{F[kMgDg], 0.0, F[kMgGl], F[kMgGl + R], F[kMgGd], m0};
+      const MGRowZ r1{F[kMgDg + R], 0.0, r0.gr, F[kMgGl + 2 * R], F[kMgGd + R], m1};
+      const MGRowZ r2{F2[kMgDg], 0.0, F2[kMgGl], F2[kMgGl + R], m0, F3[kMgGd]};
+      const MGRowZ r3{F2[kMgDg + R], 0.0, r2.gr, F2[kMgGl + 2 * R], m1, F3[kMgGd + R]};
+      const double q0 = F[kMgB] - mg_apply_z(r0, v00, T[-R], v01, T[-S], v10);
+      const double q1 = F[kMgB + R] - mg_apply_z(r1, v01, v00, T[2 * R], T[R - S], v11);
+      const double q2 = F2[kMgB] - mg_apply_z(r2, v10, T2[-R], v11, v00, T2[S]);
+      const double q3 = F2[kMgB + R] - mg_apply_z(r3, v11, v10, T2[2 * R], v01, T2[R + S]);
+      const double v = (q0 + q1) + (q2 + q3);
+      const bool last = s + 2 == slots;
+      double *const C = lds + c.own;
+      const double q = mg_div(last ? v : kMgOmega * v, C[kMgDg], C[kMgRd]);
+      C[kMgB] = v;
+      C[last ? kMgT : kMgX] = last ? q : 0.0 + q;
+    }
+    meet(c.n <= 64);
+  }
+#pragma unroll
+  for (int s = kMgSlots - 2; s >= 0; --s) {
+    if (s + 1 >= slots) continue;
+    const MgSlot &f = sl[s];
+    if (f.n <= 64 && tid >= 64) continue;
+    if (f.n > 64 && sl[s + 1].n <= 64) __syncthreads();
+    if (tid < f.n) {
+      double *const V = lds + f.own;
+      const double *const T = V + kMgT, *const P = lds + kMgT;
+      const double vc = T[0] + kMgScale * P[f.par];
+      const double vl = T[-kMgRec] + kMgScale * P[f.parl];
+      const double vr = T[kMgRec] + kMgScale * P[f.parl + kMgRec];
+      const double vd = T[-f.row] + kMgScale * P[f.pard];
+      const double vu = T[f.row] + kMgScale * P[f.pard + f.crow];
+      V[kMgX] = mg_sweep_z(row(V, f.row), V[kMgB], vc, vl, vr, vd, vu);
+    }
+    meet(f.n <= 64);
+    sweep(f, kMgX, kMgT);
   }
 }
 
 // The V-cycle of the LDS levels Lg..L-1, run by every workgroup on its own
-// copy: b of level Lg from global memory (b_global) or already in LDS; its
-// result ends in level Lg's t vector.  Descent: b loaded with the first
-// sweep; per level the second sweep, then the restriction with the next
-// level's first sweep (the one-cell level: its exact solve).  Ascent: the
-// correction fused into the first post-sweep (the neighbours' corrected
-// values recomputed), the second post-sweep.  Each level's result ends in its
-// t vector.
-template <int SC>
-__device__ __forceinline__ void mg_lds_cycle(const MGLevel *lv, int Lg, int L, double *lds,
-                                             bool b_global)
+// copy: b of level Lg from global memory (b_global; the pads' zeros written
+// here, the LDS being used for other things between two cycles) or already in
+// LDS; its result ends in E (cell by cell), or in level Lg's t vector (E null).
+// Descent: b loaded with the first sweep; per level the second sweep, then the
+// restriction with the next level's first sweep (the one-cell level: its exact
+// solve).  Ascent: the correction fused into the first post-sweep (the
+// neighbours' corrected values recomputed), the second post-sweep.
+template <int SPAN, bool Y>
+__device__ __forceinline__ void mg_lds_cycle_y(const MGLevel *lv, int Lg, int L, double *lds,
+                                               double *E, bool b_global, int zero0, int zero_n,
+                                               const MgSlot (&sl)[kMgSlots], int slots)
 {
-  // an LDS level, two cells per thread at a time (computed, then stored),
-  // then a workgroup barrier
-  auto for_local = [&](int nl, auto compute, auto store) {
-    const int bd = blockDim.x;
-    for (int i0 = threadIdx.x; i0 < nl; i0 += 2 * bd) {
-      const int i1 = i0 + bd;
-      const auto v0 = compute(i0);
-      const auto v1 = compute(i1 < nl ? i1 : i0);
-      store(i0, v0);
-      if (i1 < nl) store(i1, v1);
+  // A pass over an LDS level, then a workgroup barrier; a level of at most one
+  // cell per lane is run by wavefront 0 alone (the others wait at the end of
+  // the small levels): its LDS operations execute in order, so a pass needs no
+  // workgroup barrier.  Each pass is in the code once, for both: the
+  // instruction cache holds an iteration.
+  bool alone = false;
+  auto run = [&](int nl, auto cell) {
+    const int bd = alone ? 64 : static_cast<int>(blockDim.x);
+#pragma unroll 1
+    for (int i = threadIdx.x; i < nl; i += bd) cell(i);
+    if (alone) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  // two cells per thread at a time where the level has more cells than threads
+  auto run2 = [&](int nl, auto compute, auto store) {
+    const int bd = static_cast<int>(blockDim.x);
+#pragma unroll 1
+    for (int i = threadIdx.x; i < nl; i += 2 * bd) {
+      const int i1 = i + bd < nl ? i + bd : i;
+      const auto v0 = compute(i), v1 = compute(i1);
+      store(i, v0);
+      store(i1, v1);
     }
     __syncthreads();
   };
-  // a level of at most one cell per lane, run by wavefront 0 alone: its LDS
-  // operations execute in order, so a pass needs no workgroup barrier
-  auto for_wave = [&](int nl, auto compute, auto store) {
-    const int i = static_cast<int>(threadIdx.x);
-    const auto v = compute(i < nl ? i : 0);
-    if (i < nl) store(i, v);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  auto front = [](const MgLds &F) { return Y ? F.S : 1; };
+  auto row = [&](const MgLds &F, int jc) {
+    const double *C = lds + jc;
+    MGRowZ r;
+    r.dg = C[F.dg];
+    r.rd = C[F.rd];
+    r.gl = C[F.gx];
+    r.gr = C[F.gx + 1];
+    r.gd = Y ? C[F.gy] : 0.0;
+    r.gu = Y ? C[F.gy + F.S] : 0.0;
+    return r;
   };
-  const MGLevel T = lv[Lg];
-  for_local(
-      T.n,
-      [&](int i) {
-        const double bv = b_global ? mld<SC>(&T.b[i]) : lds[T.lb + i];
-        return MgV2{bv, mg_sweep_first(bv, lds[T.lc + 3 * i])};
-      },
-      [&](int i, MgV2 v) {
-        lds[T.lb + i] = v.a;
-        if (L - 1 > Lg) lds[T.lx + i] = v.b;
-        else lds[T.lt + i] = v.a / lds[T.lc + 3 * i];
-      });
+  auto sweep = [&](const MgLds &F, const double *X, int i) {
+    const int jc = i + mg_row_of(i, F.rnx), j = jc + front(F);
+    const double *V = X + j;
+    return mg_sweep_z(row(F, jc), lds[F.lb + j], V[0], V[-1], V[1], Y ? V[-F.S] : 0.0,
+                      Y ? V[F.S] : 0.0);
+  };
+  auto at = [&](const MgLds &F, int i) { return i + mg_row_of(i, F.rnx) + front(F); };
+  {
+    const MgLds T = mg_lds_level(lv[Lg]);
+    const bool one = L - 1 == Lg;
+    if (b_global) {
+      for (int i = threadIdx.x; i < zero_n; i += blockDim.x) lds[zero0 + i] = 0.0;
+      const double *src = mg_global(lv[Lg].b);
+      mg_cells<2>(
+          T.n, [&](int i) { return mld<SPAN>(&src[i]); },
+          [&](int i, double v) { lds[T.lb + at(T, i)] = v; });
+      __syncthreads();
+    }
+    run(T.n, [&](int i) {
+      const int jc = i + mg_row_of(i, T.rnx), j = jc + front(T);
+      const double bv = lds[T.lb + j], dg = lds[T.dg + jc], rd = lds[T.rd + jc];
+      const double q = mg_div(one ? bv : kMgOmega * bv, dg, rd);
+      if (!one) lds[T.lx + j] = 0.0 + q;
+      else if (E) E[i] = q;
+      else lds[T.lt + j] = q;
+    });
+    if (one) return;
+  }
   // descent step at level k (second sweep, restriction with the next
   // level's first sweep) and ascent step (corrected first post-sweep,
-  // second post-sweep), with `run` one of the two pass forms
-  auto down = [&](int k, auto run) {
-    const MGLevel F = lv[k], Cl = lv[k + 1];
-    const double *B = lds + F.lb, *X = lds + F.lx;
+  // second post-sweep)
+  // (Rec: the coarser level has records)
+  auto down = [&](auto Rec, int k) {
+    const MgLds F = mg_lds_level(lv[k]), Cl = mg_lds_level(lv[k + 1]);
+    const double *X = lds + F.lx;
     double *Tm = lds + F.lt;
-    run(
-        F.n,
-        [&](int i) {
-          const MGRow r = mg_row_lds(F, lds, i);
-          const double t = B[i] - mg_apply_row(r, i, [&](int j) { return X[j]; });
-          return X[i] + (kMgOmega * t) / r.dg;
-        },
-        [&](int i, double v) { Tm[i] = v; });
+    if constexpr (decltype(Rec)::value)
+      run2(F.n, [&](int i) { return sweep(F, X, i); }, [&](int i, double v) { Tm[at(F, i)] = v; });
+    else
+      run(F.n, [&](int i) { Tm[at(F, i)] = sweep(F, X, i); });
     const bool last = (k + 1 == L - 1);
     run(
         Cl.n,
         [&](int C) {
-          const int J = C / Cl.nx, I = C - J * Cl.nx;
-          double q[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int ix = 2 * I + (k & 1), iy = 2 * J + (k >> 1);
-            const bool in = (ix < F.nx && iy < F.ny);
-            const int cx = in ? ix : 2 * I, cy = in ? iy : 2 * J;
-            const int f = cy * F.nx + cx;
-            const MGRow r = mg_row_lds_at(F, lds, cx, cy);
-            const double res = B[f] - mg_apply_row(r, f, [&](int j) { return Tm[j]; });
-            q[k] = in ? res : 0.0;
+          // the four children's residuals: their twelve values and rows loaded
+          // once each; an absent child's row is read at its neighbour, and its
+          // residual not used
+          const int J = mg_row_of(C, Cl.rnx), I = C - J * Cl.nx;
+          const int S = F.S, jc = 2 * J * S + 2 * I;
+          const bool right = 2 * I + 1 < F.nx, up = Y && 2 * J + 1 < F.ny;
+          const int sy = up ? S : 0;
+          const double *V = Tm + jc + front(F), *Bv = lds + F.lb + jc + front(F), *R = lds + jc;
+          const double v00 = V[0], v01 = V[1], vl0 = V[-1], vr0 = V[2];
+          const double v10 = Y ? V[S] : 0.0, v11 = Y ? V[S + 1] : 0.0;
+          const double gx0 = R[F.gx], gx1 = R[F.gx + 1], gx2 = R[F.gx + 2];
+          const double gm0 = Y ? R[F.gy + S] : 0.0, gm1 = Y ? R[F.gy + S + 1] : 0.0;
+          MGRowZ r0{R[F.dg], 0.0, gx0, gx1, Y ? R[F.gy] : 0.0, gm0};
+          MGRowZ r1{R[F.dg + 1], 0.0, gx1, gx2, Y ? R[F.gy + 1] : 0.0, gm1};
+          const double q0 = Bv[0] - mg_apply_z(r0, v00, vl0, v01, Y ? V[-S] : 0.0, v10);
+          const double q1 = Bv[1] - mg_apply_z(r1, v01, v00, vr0, Y ? V[1 - S] : 0.0, v11);
+          double q2 = 0.0, q3 = 0.0;
+          if (Y) {
+            const double *V2 = V + sy, *R2 = R + sy;
+            const double hx0 = R2[F.gx], hx1 = R2[F.gx + 1], hx2 = R2[F.gx + 2];
+            MGRowZ r2{R2[F.dg], 0.0, hx0, hx1, gm0, R2[F.gy + S]};
+            MGRowZ r3{R2[F.dg + 1], 0.0, hx1, hx2, gm1, R2[F.gy + S + 1]};
+            q2 = Bv[sy] - mg_apply_z(r2, v10, V2[-1], v11, v00, V2[S]);
+            q3 = Bv[sy + 1] - mg_apply_z(r3, v11, v10, V2[2], v01, V2[S + 1]);
           }
-          return (q[0] + q[1]) + (q[2] + q[3]);
-        },
-        [&](int C, double v) {
-          lds[Cl.lb + C] = v;
-          const double dg = lds[Cl.lc + 3 * C];
-          if (last) lds[Cl.lt + C] = v / dg;
-          else lds[Cl.lx + C] = mg_sweep_first(v, dg);
+          const double v = (q0 + (right ? q1 : 0.0)) + ((up ? q2 : 0.0) + (right && up ? q3 : 0.0));
+          if constexpr (decltype(Rec)::value) {
+            double *const R = lds + mg_scalar(lv[k + 1].rec) + kMgRec * (C + J + Cl.S);
+            const double q = mg_div(last ? v : kMgOmega * v, R[kMgDg], R[kMgRd]);
+            R[kMgB] = v;
+            R[last ? kMgT : kMgX] = last ? q : 0.0 + q;
+          } else {
+            const int jC = C + J;
+            const double q = mg_div(last ? v : kMgOmega * v, lds[Cl.dg + jC], lds[Cl.rd + jC]);
+            lds[Cl.lb + jC + front(Cl)] = v;
+            lds[(last ? Cl.lt : Cl.lx) + jC + front(Cl)] = last ? q : 0.0 + q;
+          }
         });
   };
-  auto up = [&](int k, auto run) {
-    const MGLevel F = lv[k], Cl = lv[k + 1];
-    const double *B = lds + F.lb, *E = lds + Cl.lt;
+  auto up = [&](auto Rec, int k) {
+    const MgLds F = mg_lds_level(lv[k]), Cl = mg_lds_level(lv[k + 1]);
+    constexpr int W = decltype(Rec)::value ? kMgRec : 1;
+    const double *Ec = decltype(Rec)::value ? lds + mg_scalar(lv[k + 1].rec) + kMgT + kMgRec * Cl.S
+                                            : lds + Cl.lt + front(Cl);
     double *X = lds + F.lx, *Tm = lds + F.lt;
-    run(
-        F.n,
-        [&](int i) {
-          const MGRow r = mg_row_lds(F, lds, i);
-          int pc[5];
-          mg_parents(r, Cl.nx, pc);
-          const int js[5] = {i, r.jl, r.jr, r.jd, r.ju};
-          double xc5[5];
-#pragma unroll
-          for (int q = 0; q < 5; ++q) xc5[q] = Tm[js[q]] + kMgScale * E[pc[q]];
-          const double t = B[i] - mg_apply_vals(r, xc5);
-          return xc5[0] + (kMgOmega * t) / r.dg;
-        },
-        [&](int i, double v) { X[i] = v; });
-    run(
-        F.n,
-        [&](int i) {
-          const MGRow r = mg_row_lds(F, lds, i);
-          const double t = B[i] - mg_apply_row(r, i, [&](int j) { return X[j]; });
-          return X[i] + (kMgOmega * t) / r.dg;
-        },
-        [&](int i, double v) { Tm[i] = v; });
+    auto first = [&](int i) {
+      const int iy = mg_row_of(i, F.rnx), ix = i - iy * F.nx;
+      const int S = F.S, jc = i + iy, Sc = Cl.S;
+      const double *V = Tm + jc + front(F);
+      const double *P = Ec + W * ((iy >> 1) * Sc + (ix >> 1));
+      // (a left or lower absent neighbour's parent is a pad as well)
+      const int pl = (ix & 1) - 1, pr = ix & 1;
+      const double e0 = P[0], el = P[W * pl], er = P[W * pr];
+      const double vc = V[0] + kMgScale * e0, vl = V[-1] + kMgScale * el;
+      double vr = V[1] + kMgScale * er, vd = 0.0, vu = 0.0;
+      vr = ix < F.nx - 1 ? vr : 0.0;
+      if (Y) {
+        vd = V[-S] + kMgScale * P[(iy & 1) ? 0 : -W * Sc];
+        vu = V[S] + kMgScale * P[(iy & 1) ? W * Sc : 0];
+        vu = iy < F.ny - 1 ? vu : 0.0;
+      }
+      return mg_sweep_z(row(F, jc), lds[F.lb + jc + front(F)], vc, vl, vr, vd, vu);
+    };
+    auto second = [&](int i, double v) {
+      if (k == Lg && E) E[i] = v;
+      else Tm[at(F, i)] = v;
+    };
+    if constexpr (decltype(Rec)::value) {
+      run2(F.n, first, [&](int i, double v) { X[at(F, i)] = v; });
+      run2(F.n, [&](int i) { return sweep(F, X, i); }, second);
+    } else {
+      run(F.n, [&](int i) { X[at(F, i)] = first(i); });
+      run(F.n, [&](int i) { second(i, sweep(F, X, i)); });
+    }
   };
+  if constexpr (Y) {
+    if (slots) {
+      down(std::true_type{}, Lg);
+      mg_slot_cycle(lds, sl, slots);
+      if (sl[0].n <= 64) __syncthreads();
+      up(std::true_type{}, Lg);
+      return;
+    }
+  }
   // the levels of at most 64 cells (from ks on) by wavefront 0 alone
   int ks = Lg;
-  while (ks < L - 1 && lv[ks].n > 64) ++ks;
-  for (int k = Lg; k < ks; ++k) down(k, for_local);
-  if (ks < L - 1) {
-    if (threadIdx.x < 64) {
-      for (int k = ks; k < L - 1; ++k) down(k, for_wave);
-      for (int k = L - 2; k >= ks; --k) up(k, for_wave);
-    }
-    __syncthreads();
+  while (ks < L - 1 && mg_scalar(lv[ks].n) > 64) ++ks;
+  const bool first_wave = threadIdx.x < 64;
+#pragma unroll 1
+  for (int k = Lg; k < L - 1; ++k) {
+    alone = k >= ks;
+    if (alone && !first_wave) break;
+    down(std::false_type{}, k);
   }
-  for (int k = ks - 1; k >= Lg; --k) up(k, for_local);
+#pragma unroll 1
+  for (int k = L - 2; k >= Lg; --k) {
+    alone = k >= ks;
+    if (!alone || first_wave) up(std::false_type{}, k);
+    if (k == ks) __syncthreads();
+  }
+}
+
+template <int SPAN>
+__device__ __forceinline__ void mg_lds_cycle(const MGLevel *lv, int Lg, int L, double *lds,
+                                             double *E, bool b_global, int zero0, int zero_n,
+                                               const MgSlot (&sl)[kMgSlots], int slots)
+{
+  if (__builtin_amdgcn_readfirstlane(lv[Lg].ny) > 1)
+    mg_lds_cycle_y<SPAN, true>(lv, Lg, L, lds, E, b_global, zero0, zero_n, sl, slots);
+  else
+    mg_lds_cycle_y<SPAN, false>(lv, Lg, L, lds, E, b_global, zero0, zero_n, sl, slots);
 }
 
 // The preconditioned CG of one system, run by the G workgroups of a group of
 // which this one is number bid (G = 1: one workgroup alone, its exchanges
 // through workgroup-scope memory operations and workgroup barriers).
-template <int SC>
-__device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, double *lds,
+template <int SPAN, bool FLAGS>
+__device__ __forceinline__ void mgcg_solve(const MGArgs &in, int G, int bid, double *lds,
                                            double *red, MGLevel *s_lv)
 {
+  const MGArgs a = mg_args(in);
   const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int gwv = bid * nw + wave, gstride = G * nw;
   if (bid == 0 && threadIdx.x == 0) a.sc->cg_t0 = static_cast<unsigned long long>(wall_clock64());
   const int L = a.L, Lg = a.Lg;
   mg_stage_levels(a.lv, L, s_lv);
   const MGLevel *lv = s_lv;
-  const MGLevel L0 = lv[0];
+  const MGLevel L0 = mg_level(lv[0]);
   const int n = L0.n, nb = (n + kTree - 1) / kTree;
   unsigned int epoch = 0;
 
@@ -463,6 +850,7 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
       __syncthreads();
       return true;
     }
+    if (FLAGS) return flag_barrier<SPAN>(a.barrier, a.flags, bid, G, epoch);
     return grid_barrier(a.barrier, epoch, G);
   };
   // The cells of a grid level this thread owns, Q of a block at a time: the Q
@@ -522,25 +910,27 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
   using V2 = MgV2;
 
   // rows of the LDS levels, once per solve
-  mg_lds_rows(lv, Lg, L, lds);
+  mg_lds_rows(lv, Lg, L, lds, a.zero0, a.zero_n, a.slots);
+  MgSlot sl[kMgSlots];
+  mg_slots(lv, Lg, a.slots, sl);
   __syncthreads();
 
   // the V-cycle on r (published as lv[0].b, and lv[0].xa = the first sweep
   // when level 0 is a grid level); u ends in lv[0].e, or in LDS when Lg = 0
   auto vcycle = [&]() -> bool {
     for (int k = 0; k < Lg; ++k) {
-      const MGLevel F = lv[k];
+      const MGLevel F = mg_level(lv[k]);
       for_flat(
           Q2{}, F.n,
           [&](int c) {
-            auto xa = [&](int j) { return mld<SC>(&F.xa[j]); };
+            auto xa = [&](int j) { return mld<SPAN>(&F.xa[j]); };
             const MGRow r = mg_row(F, c);
-            const double t = mld<SC>(&F.b[c]) - mg_apply_row(r, c, xa);
+            const double t = mld<SPAN>(&F.b[c]) - mg_apply_row(r, c, xa);
             return xa(c) + (kMgOmega * t) / r.dg;
           },
-          [&](int c, double v) { mst<SC>(&F.xb[c], v); });
+          [&](int c, double v) { mst<SPAN>(&F.xb[c], v); });
       if (!bar()) return false;
-      const MGLevel Cl = lv[k + 1];
+      const MGLevel Cl = mg_level(lv[k + 1]);
       const bool grid_next = (k + 1 < Lg);
       for_flat(
           Q1{}, Cl.n,
@@ -558,12 +948,12 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
               const int cx = in[k] ? ix : 2 * I, cy = in[k] ? iy : 2 * J;
               const int f = cy * F.nx + cx;
               rw[k] = mg_row_at(F, cx, cy);
-              bv[k] = mld<SC>(&F.b[f]);
-              xv[k][0] = mld<SC>(&F.xb[f]);
-              xv[k][1] = mld<SC>(&F.xb[rw[k].jl]);
-              xv[k][2] = mld<SC>(&F.xb[rw[k].jr]);
-              xv[k][3] = mld<SC>(&F.xb[rw[k].jd]);
-              xv[k][4] = mld<SC>(&F.xb[rw[k].ju]);
+              bv[k] = mld<SPAN>(&F.b[f]);
+              xv[k][0] = mld<SPAN>(&F.xb[f]);
+              xv[k][1] = mld<SPAN>(&F.xb[rw[k].jl]);
+              xv[k][2] = mld<SPAN>(&F.xb[rw[k].jr]);
+              xv[k][3] = mld<SPAN>(&F.xb[rw[k].jd]);
+              xv[k][4] = mld<SPAN>(&F.xb[rw[k].ju]);
             }
             double q[4];
 #pragma unroll
@@ -575,13 +965,14 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
             return V2{B, sweep_first(B, Cl.diag[C])};
           },
           [&](int C, V2 v) {
-            mst<SC>(&Cl.b[C], v.a);
-            if (grid_next) mst<SC>(&Cl.xa[C], v.b);
+            mst<SPAN>(&Cl.b[C], v.a);
+            if (grid_next) mst<SPAN>(&Cl.xa[C], v.b);
           });
       if (!bar()) return false;
     }
     // the LDS levels, in every workgroup
-    mg_lds_cycle<SC>(lv, Lg, L, lds, true);
+    mg_lds_cycle<SPAN>(lv, Lg, L, lds, Lg > 0 ? lds : nullptr, true, a.zero0, a.zero_n,
+                       sl, a.slots);
     // Ascent.  The last sweep of a grid level whose finer level has at most
     // one cell per thread is not stored: that finer level's first post-sweep
     // recomputes it at the (at most three) aggregates its cell and neighbours
@@ -589,19 +980,19 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
     // its own.
     auto fused = [&](int k) { return k >= 1 && lv[k - 1].n <= nthr; };
     for (int k = Lg - 1; k >= 0; --k) {
-      const MGLevel F = lv[k], Cl = lv[k + 1];
+      const MGLevel F = mg_level(lv[k]), Cl = mg_level(lv[k + 1]);
       const bool recompute = (k + 1 < Lg) && fused(k + 1);
       // the coarse level's final value at aggregate P: from LDS, or the
       // second post-sweep of a grid level evaluated here
       auto e_grid = [&](int P) {
         const MGRow rc = mg_row(Cl, P);
-        const double b = mld<SC>(&Cl.b[P]);
+        const double b = mld<SPAN>(&Cl.b[P]);
         double v5[5];
-        v5[0] = mld<SC>(&Cl.xd[P]);
-        v5[1] = mld<SC>(&Cl.xd[rc.jl]);
-        v5[2] = mld<SC>(&Cl.xd[rc.jr]);
-        v5[3] = mld<SC>(&Cl.xd[rc.jd]);
-        v5[4] = mld<SC>(&Cl.xd[rc.ju]);
+        v5[0] = mld<SPAN>(&Cl.xd[P]);
+        v5[1] = mld<SPAN>(&Cl.xd[rc.jl]);
+        v5[2] = mld<SPAN>(&Cl.xd[rc.jr]);
+        v5[3] = mld<SPAN>(&Cl.xd[rc.jd]);
+        v5[4] = mld<SPAN>(&Cl.xd[rc.ju]);
         const double t = b - mg_apply_vals(rc, v5);
         return v5[0] + (kMgOmega * t) / rc.dg;
       };
@@ -620,13 +1011,13 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
               mg_parents(r, Cl.nx, pc);
               double xb5[5], e5[5];
 #pragma unroll
-              for (int q = 0; q < 5; ++q) xb5[q] = mld<SC>(&F.xb[js[q]]);
+              for (int q = 0; q < 5; ++q) xb5[q] = mld<SPAN>(&F.xb[js[q]]);
               if constexpr (decltype(FromLds)::value == 1) {
 #pragma unroll
-                for (int q = 0; q < 5; ++q) e5[q] = lds[Cl.lt + pc[q]];
+                for (int q = 0; q < 5; ++q) e5[q] = lds[pc[q]];
               } else if constexpr (decltype(FromLds)::value == 0) {
 #pragma unroll
-                for (int q = 0; q < 5; ++q) e5[q] = mld<SC>(&Cl.e[pc[q]]);
+                for (int q = 0; q < 5; ++q) e5[q] = mld<SPAN>(&Cl.e[pc[q]]);
               } else {
                 // distinct aggregates: the cell's own, the one across an x
                 // face (left or right) and the one across a y face
@@ -639,14 +1030,14 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
                 e5[3] = (pc[3] == pc[0]) ? e0 : ey;
                 e5[4] = (pc[4] == pc[0]) ? e0 : ey;
               }
-              const double bc = mld<SC>(&F.b[c]);
+              const double bc = mld<SPAN>(&F.b[c]);
               double xc5[5];
 #pragma unroll
               for (int q = 0; q < 5; ++q) xc5[q] = xb5[q] + kMgScale * e5[q];
               const double t = bc - mg_apply_vals(r, xc5);
               return xc5[0] + (kMgOmega * t) / r.dg;
             },
-            [&](int c, double v) { mst<SC>(&F.xd[c], v); });
+            [&](int c, double v) { mst<SPAN>(&F.xd[c], v); });
       };
       // e of the coarse level: 1 from LDS, 0 stored by its last sweep, 2 recomputed
       if (k + 1 == Lg) post1(std::integral_constant<int, 1>{});
@@ -657,17 +1048,20 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
       for_flat(
           Q2{}, F.n,
           [&](int c) {
-            auto xd = [&](int j) { return mld<SC>(&F.xd[j]); };
+            auto xd = [&](int j) { return mld<SPAN>(&F.xd[j]); };
             const MGRow r = mg_row(F, c);
-            const double t = mld<SC>(&F.b[c]) - mg_apply_row(r, c, xd);
+            const double t = mld<SPAN>(&F.b[c]) - mg_apply_row(r, c, xd);
             return xd(c) + (kMgOmega * t) / r.dg;
           },
-          [&](int c, double v) { mst<SC>(&F.e[c], v); });
+          [&](int c, double v) { mst<SPAN>(&F.e[c], v); });
       if (!bar()) return false;
     }
     return true;
   };
-  auto uget = [&](int j) { return Lg == 0 ? lds[L0.lt + j] : mld<SC>(&L0.e[j]); };
+  auto uget = [&](int j) {
+    if (Lg > 0) return mld<SPAN>(&L0.e[j]);
+    return lds[L0.lt + j + mg_row_of(j, L0.rnx) + (L0.ny > 1 ? L0.nx + 1 : 1)];
+  };
   // w = A u on the own cells and the block sums of (r, u), (w, u), (r, r)
   auto matvec = [&]() -> bool {
     for (int blk = gwv; blk < nb; blk += gstride) {
@@ -678,7 +1072,7 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
         const int c = c0 < n ? c0 : blk * kTree;
         const double uc = uget(c);
         const double wv = mg_apply(L0, c, uget);
-        const double rv = mld<SC>(&L0.b[c]);
+        const double rv = mld<SPAN>(&L0.b[c]);
         const bool in = c0 < n;
         wq[q] = wv;
         g[q] = in ? rv * uc : 0.0;
@@ -694,9 +1088,9 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
       const double sd = wave_tree256(d[0], d[1], d[2], d[3]);
       const double sr = wave_tree256(rr[0], rr[1], rr[2], rr[3]);
       if (lane == 0) {
-        mst<SC>(&a.part[3 * blk], sg);
-        mst<SC>(&a.part[3 * blk + 1], sd);
-        mst<SC>(&a.part[3 * blk + 2], sr);
+        mst<SPAN>(&a.part[3 * blk], sg);
+        mst<SPAN>(&a.part[3 * blk + 1], sd);
+        mst<SPAN>(&a.part[3 * blk + 2], sr);
       }
     }
     return bar();
@@ -709,14 +1103,14 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
       Q4{}, n, [&](int c) { return V2{a.b[c], sweep_first(a.b[c], L0.diag[c])}; },
       [&](int c, V2 v) {
         a.x[c] = 0.0;
-        mst<SC>(&L0.b[c], v.a);
-        if (Lg > 0) mst<SC>(&L0.xa[c], v.b);
+        mst<SPAN>(&L0.b[c], v.a);
+        if (Lg > 0) mst<SPAN>(&L0.xa[c], v.b);
       });
   if (!bar() || !vcycle() || !matvec()) {
     status = -3;
   } else {
     double s3[3];
-    group_tree_n<3, SC>(a.part, nb, red, s3);
+    group_tree_n<3, SPAN>(a.part, nb, red, s3);
     gamma = s3[0];
     delta = s3[1];
     thr = a.tol2 * s3[2];
@@ -737,15 +1131,15 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
           const double pv = first ? uc : uc + beta * a.p[c];
           const double sv = first ? wv : wv + beta * a.s[c];
           const double xv = a.x[c] + alpha * pv;
-          const double rv = mld<SC>(&L0.b[c]) - alpha * sv;
+          const double rv = mld<SPAN>(&L0.b[c]) - alpha * sv;
           return U5{pv, sv, xv, rv, sweep_first(rv, L0.diag[c])};
         },
         [&](int c, U5 v) {
           a.p[c] = v.p;
           a.s[c] = v.s;
           a.x[c] = v.x;
-          mst<SC>(&L0.b[c], v.r);
-          if (Lg > 0) mst<SC>(&L0.xa[c], v.xa);
+          mst<SPAN>(&L0.b[c], v.r);
+          if (Lg > 0) mst<SPAN>(&L0.xa[c], v.xa);
         });
     if (!bar() || !vcycle() || !matvec()) {
       status = -3;
@@ -753,7 +1147,7 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
     }
     ++it;
     double s3[3];
-    group_tree_n<3, SC>(a.part, nb, red, s3);
+    group_tree_n<3, SPAN>(a.part, nb, red, s3);
     const double gamma_new = s3[0];
     delta = s3[1];
     if (s3[2] <= thr) {
@@ -784,26 +1178,44 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &a, int G, int bid, doub
 
 namespace iugkp {
 
-__global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a)
+// The single solve's group of G workgroups; more are launched where the group
+// may find room on one XCD (elect_group).
+__global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
 {
   extern __shared__ double lds[];
   __shared__ double red[3 * kTree];
   __shared__ MGLevel s_lv[kMgLevelsMax];
-  mgcg_solve<__HIP_MEMORY_SCOPE_AGENT>(a, static_cast<int>(gridDim.x),
-                                       static_cast<int>(blockIdx.x), lds, red, s_lv);
+  int rank = blockIdx.x;
+  bool one_xcd = false;
+  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (one_xcd) mgcg_solve<kSpanXcd, true>(a, G, rank, lds, red, s_lv);
+  else mgcg_solve<kSpanDevice, true>(a, G, rank, lds, red, s_lv);
 }
 
 // the banded form (mgband.hpp), for the meshes whose rows fit its windows;
 // workgroups of at most kMgBandThreads threads, whose lanes then have the
 // registers its batched loads take
 constexpr int kMgBandThreads = 512;
-__global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a)
+// A chain of short dependent phases bounds it: the latency of a few loads per
+// thread, of LDS passes and of 2 Lg barriers per iteration, and the fetch of the
+// code, which an iteration runs through once.  So each phase is in the code
+// once, unrolled little (two cells in the phases that load most; four and eight
+// made 76000 instructions of it, and 70 us per iteration), levels' addresses are
+// scalars to global memory, the rows each workgroup takes are worked out once
+// per solve, and the small levels run from registers' addresses on records.
+// us per iteration, before and after: 512 x 512 cells 123 and 82, 256 x 256 68
+// and 44, 128 x 128 50 and 24, 64 x 64 38 and 17, 30 x 20 20 and 13; the 256 x
+// 256 cavity to steady state 24.4 to 17.8 ms.
+__global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int G)
 {
   extern __shared__ double lds[];
   __shared__ double red[3 * kTree];
   __shared__ MGLevel s_lv[kMgLevelsMax];
-  mgcg_band_solve<__HIP_MEMORY_SCOPE_AGENT>(a, static_cast<int>(gridDim.x),
-                                            static_cast<int>(blockIdx.x), lds, red, s_lv);
+  int rank = blockIdx.x;
+  bool one_xcd = false;
+  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (one_xcd) mgcg_band_solve<kSpanXcd, true>(a, G, rank, lds, red, s_lv);
+  else mgcg_band_solve<kSpanDevice, true>(a, G, rank, lds, red, s_lv);
 }
 
 // ---------------------------------------------------------------------------
@@ -871,8 +1283,8 @@ __global__ __launch_bounds__(64 * kMgPoolWaves) void mgcg_batch_kernel(const int
   for (int e = e0; e < e1; ++e) {
     const CgJob jb = jobs[e];
     const MGArgs &a = mg[jb.inst];
-    if (a.band) mgcg_band_solve<__HIP_MEMORY_SCOPE_AGENT>(a, jb.G, jb.rank, lds, red, s_lv);
-    else mgcg_solve<__HIP_MEMORY_SCOPE_AGENT>(a, jb.G, jb.rank, lds, red, s_lv);
+    if (a.band) mgcg_band_solve<kSpanDevice, false>(a, jb.G, jb.rank, lds, red, s_lv);
+    else mgcg_solve<kSpanDevice, false>(a, jb.G, jb.rank, lds, red, s_lv);
     __syncthreads();
   }
 }
@@ -912,6 +1324,19 @@ __global__ void mg_coarsen_diag_kernel(MGLevel c, int has_y, double *diag)
     d = d + c.gy[(J + 1) * c.nx + I];
   }
   diag[i] = d;
+}
+
+// the banded form's copies of a level's operator (MGLevel)
+__global__ void mg_rows_kernel(MGLevel l, double *gxz, double *gyz, double *rd)
+{
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const int S = l.nx + 1;
+  if (i < l.ny * S) {
+    const int ix = i % S;
+    gxz[i] = (ix > 0 && ix < l.nx) ? l.gx[i] : 0.0;
+  }
+  if (i < (l.ny + 1) * l.nx) gyz[i] = (i >= l.nx && i < l.ny * l.nx) ? l.gy[i] : 0.0;
+  if (i < l.n) rd[i] = mg_recip(l.diag[i]);
 }
 
 }  // namespace iugkp

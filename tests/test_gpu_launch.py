@@ -182,3 +182,37 @@ def test_domain_blocks_bands_bitwise(oracle_mod, gpu, faces):
     sa, sb = a.stats(), b.stats()
     for k in ("flights", "segments", "crossings"):
         assert sa[k] == sb[k]
+
+
+# The multigrid-preconditioned CG: levels in LDS with records (at most one cell
+# per thread and six levels below the first) and without, a first LDS level of
+# one, two and many cells per thread, groups on one XCD and device-wide, more
+# members than rows, windows of one row, rows too long for the windows beside
+# the LDS levels or for any; odd sizes at each level; and operators so large
+# that no reciprocal is used in place of a division.
+MG = {
+    "lds_32x32": (32, 32, 0, 1.0), "lds_33x31": (33, 31, 0, 1.0), "lds_33x31_w1": (33, 31, 1, 1.0),
+    "lds_2x500": (2, 500, 0, 1.0), "lds_500x2": (500, 2, 0, 1.0), "lds_5x1": (5, 1, 0, 1.0),
+    "xcd_33x32": (33, 32, 0, 1.0), "xcd_65x63_w2": (65, 63, 2, 1.0), "xcd_129x127": (129, 127, 0, 1.0),
+    "device_257x255": (257, 255, 0, 1.0), "tall_9x1200": (9, 1200, 0, 1.0),
+    "wide_700x9": (700, 9, 0, 1.0), "wide_790x30": (790, 30, 0, 1.0), "wide_1500x5": (1500, 5, 0, 1.0),
+    "huge_40x36": (40, 36, 0, 1e95), "huge_30x20": (30, 20, 0, 1e95),
+}
+
+
+@pytest.mark.parametrize("name", list(MG))
+def test_mg_launch_forms_bitwise(oracle_mod, gpu, name):
+    nx, ny, waves, scale = MG[name]
+    w = cavity_2d(n=nx, ny=ny, kn=0.02, particles=20 * nx * ny)
+    rng = np.random.default_rng(nx * ny)
+    D = rng.uniform(0.5, 2.0, size=(2, w.n_cells)) * w.vg * 1e-2 * scale
+    kw = dict(newton=True, diff_x=D[0], diff_y=D[1], tally_faces=oracle_mod.FACES_OFF,
+              cg_precond=oracle_mod.PRECOND_MG, T_init=seeded_temperature(w.n_cells))
+    o = oracle_mod.Oracle(w, **kw)
+    s = gpu.Solver(w, cg_waves=waves, **kw)
+    for i in range(2):
+        assert o.step(1) == 0 and s.step(1) == 0
+        _, _, E, G = s.state()
+        assert np.array_equal(o.E(), E.cpu().numpy()), f"{name} iteration {i}: E differs"
+        assert np.array_equal(o.G(), G.cpu().numpy()), f"{name} iteration {i}: G differs"
+        assert o.info().cg_iters_last == s.stats()["cg_iters_last"], name
