@@ -64,7 +64,11 @@ constexpr int kMgGroupMax = 128;
 // two workgroups per CU against eight: 4.0 / 3.4 ms)
 constexpr int kCgAloneMax = 8, kCgWavesMin = 4;
 constexpr int kCgWavesDefault = 8;
-constexpr int kBarStride = 64;               // batched CG barriers 256 bytes apart (no shared lines)
+// workgroups of a batched multigrid solve (64 cavities of 256 x 256 cells, one
+// solve of all: 32 / 64 / 128 of them 297 / 285 / 286 ms)
+constexpr int kMgPoolGroupMax = 64;
+constexpr int kBarStride =                   // words of a batched CG's barrier
+    iugkp::kGroupWords + kMgPoolGroupMax * iugkp::kCgFlagStep;
 constexpr double kStripeMinCells = 7.0;      // row stripes for face tallies when lambda_min >= 7 cells
 constexpr int kStripeBlock = 1024;           // threads of a stripe workgroup
 constexpr int kStripeMinRows = 4;
@@ -2948,7 +2952,7 @@ struct iugkp_batch {
   std::vector<unsigned long long> h_clk;
   iugkp::MGArgs *d_mg_args = nullptr;   // the multigrid jobs' arguments, per instance
   DevScalars *d_scs = nullptr;       // every instance's scalars, contiguous
-  unsigned int *d_bars = nullptr;    // every instance's CG barrier [2], kBarStride apart
+  unsigned int *d_bars = nullptr;    // every instance's CG barrier words, kBarStride apart
   DevScalars *hsc = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -3298,8 +3302,8 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
     // one wave per tree block and at most kCgWavesMax blocks per workgroup
     // (register form), or, for rows too long for the LDS staging or groups
     // beyond one workgroup per CU, the global form on kCgGridMax workgroups;
-    // with the multigrid preconditioner at most kCgGridMax workgroups of one
-    // wave per 256-cell block of the finest level.
+    // with the multigrid preconditioner at most kMgPoolGroupMax workgroups, of
+    // one wave per 256-cell block of the finest level or of two rows of level 1.
     int dev = 0, n_cu = 0, khz = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -3311,8 +3315,9 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
       const Mesh &m = ih.d.m;
       const int nbt = cdiv(m.n_cells, iugkp::kTree);
       if (ih.mg_L > 0) {
-        const int G = std::max(1, std::min(std::min(cdiv(nbt, iugkp::kMgPoolWaves), kCgGridMax),
-                                           n_cu));
+        const int G = std::max(1, std::min({std::max(cdiv(nbt, iugkp::kMgPoolWaves),
+                                                     ih.mg_Lg > 0 && ih.mg_band ? (m.ny + 1) / 4 : 0),
+                                            kMgPoolGroupMax, n_cu}));
         b->cg_G[i] = G;
         b->mg_gmax[i] = G;
         b->cg_tb[i] = 0;
@@ -3416,6 +3421,7 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
       ma.tol2 = ih.d.tol2;
       ma.max_iters = ih.d.cg_max;
       ma.barrier = ih.d.cg_barrier;
+      ma.flags = ih.d.cg_barrier + iugkp::kGroupWords;
       ma.sc = ih.d.sc;
       ma.r2 = ih.mg_r2;
       ma.s2 = ih.mg_s2;

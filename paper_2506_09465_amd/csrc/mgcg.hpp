@@ -455,6 +455,7 @@ __device__ __forceinline__ MGArgs mg_args(const MGArgs &in)
   a.w = mg_global(in.w);
   a.part = mg_global(in.part);
   a.barrier = mg_global(in.barrier);
+  a.flags = mg_global(in.flags);
   a.sc = mg_global(in.sc);
   a.r2 = mg_global(in.r2);
   a.s2 = mg_global(in.s2);
@@ -1283,8 +1284,8 @@ __global__ __launch_bounds__(64 * kMgPoolWaves) void mgcg_batch_kernel(const int
   for (int e = e0; e < e1; ++e) {
     const CgJob jb = jobs[e];
     const MGArgs &a = mg[jb.inst];
-    if (a.band) mgcg_band_solve<kSpanDevice, false>(a, jb.G, jb.rank, lds, red, s_lv);
-    else mgcg_solve<kSpanDevice, false>(a, jb.G, jb.rank, lds, red, s_lv);
+    if (a.band) mgcg_band_solve<kSpanDevice, true>(a, jb.G, jb.rank, lds, red, s_lv);
+    else mgcg_solve<kSpanDevice, true>(a, jb.G, jb.rank, lds, red, s_lv);
     __syncthreads();
   }
 }
