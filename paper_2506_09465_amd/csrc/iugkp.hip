@@ -192,6 +192,57 @@ using iugkp::TileDesc;
 
 namespace {
 
+// The device memory of a handle or of a whole batch: arrays are cut, 256 bytes
+// apart, from chunks as large as all before together, up to kMax; an array of
+// more than half a chunk has an allocation of its own, as has any where no
+// chunk is to be had.  (Each allocation and release is a call into the driver:
+// 64 cavities of 256 x 256 cells take about 60 arrays each, 45 of the 285 ms of
+// creating, solving and closing their batch.)
+struct Arena {
+  static constexpr size_t kMin = size_t{1} << 20, kMax = size_t{256} << 20;
+  std::vector<void *> allocs;
+  unsigned char *next = nullptr;
+  size_t left = 0, taken = 0;
+
+  template <class T>
+  hipError_t alloc(T **p, size_t n)
+  {
+    const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
+    const size_t chunk = std::min(kMax, std::max(kMin, taken));
+    *p = nullptr;
+    if (bytes > left && bytes <= chunk / 2) {
+      void *q = nullptr;
+      if (hipMalloc(&q, chunk) == hipSuccess) {
+        allocs.push_back(q);
+        next = static_cast<unsigned char *>(q);
+        left = chunk;
+        taken += chunk;
+      } else {
+        (void)hipGetLastError();
+      }
+    }
+    if (bytes <= left) {
+      *p = reinterpret_cast<T *>(next);
+      next += bytes;
+      left -= bytes;
+      return hipSuccess;
+    }
+    const hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+    if (e == hipSuccess) {
+      allocs.push_back(*p);
+      taken += bytes;
+    }
+    return e;
+  }
+  void release()
+  {
+    for (void *q : allocs) (void)hipFree(q);
+    allocs.clear();
+    next = nullptr;
+    left = taken = 0;
+  }
+};
+
 // Host-side record of one problem instance and the device memory it owns.
 struct InstHost {
   Inst d{};                          // descriptor (device pointers) as uploaded
@@ -199,7 +250,7 @@ struct InstHost {
   int mem_kind = IUGKP_MEM_HOST;
   std::vector<TileDesc> tiles;       // inst field filled by the owner
   size_t lds_bytes = 0;              // march window
-  std::vector<void *> allocs;
+  Arena mem, *shared = nullptr;      // its device memory, or its batch's
   double *tau = nullptr, *Dx = nullptr, *Dy = nullptr, *gx = nullptr, *gy = nullptr,
          *diag = nullptr;
   double *out_T = nullptr, *out_qx = nullptr, *out_qy = nullptr;
@@ -233,17 +284,9 @@ struct InstHost {
   template <class T>
   hipError_t alloc(T **p, size_t n)
   {
-    *p = nullptr;
-    if (n == 0) n = 1;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(p), n * sizeof(T));
-    if (e == hipSuccess) allocs.push_back(*p);
-    return e;
+    return (shared ? shared : &mem)->alloc(p, n);
   }
-  void release()
-  {
-    for (void *p : allocs) (void)hipFree(p);
-    allocs.clear();
-  }
+  void release() { mem.release(); }
 };
 
 int check_problem(const iugkp_problem *p)
@@ -2952,6 +2995,7 @@ struct iugkp_batch {
   std::vector<unsigned long long> h_clk;
   iugkp::MGArgs *d_mg_args = nullptr;   // the multigrid jobs' arguments, per instance
   DevScalars *d_scs = nullptr;       // every instance's scalars, contiguous
+  Arena mem;                         // the instances' arrays
   unsigned int *d_bars = nullptr;    // every instance's CG barrier words, kBarStride apart
   DevScalars *hsc = nullptr;
   hipGraph_t graph = nullptr;
@@ -2966,7 +3010,7 @@ void free_batch(iugkp_batch *b)
   if (!b) return;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
-  for (auto &ih : b->insts) ih.release();
+  b->mem.release();
   if (b->d_insts) (void)hipFree(b->d_insts);
   if (b->d_tiles) (void)hipFree(b->d_tiles);
   if (b->hsc) (void)hipHostFree(b->hsc);
@@ -3270,6 +3314,7 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
       free_batch(b);
       return fail(IUGKP_E_INVALID_ARG, "all problems of a batch must use the same mem_kind");
     }
+    b->insts[i].shared = &b->mem;
     const int rc = setup_instance(problems[i], options[i], b->stream, false, b->insts[i]);
     if (rc) {
       free_batch(b);
