@@ -193,13 +193,15 @@ using iugkp::TileDesc;
 namespace {
 
 // The device memory of a handle or of a whole batch: arrays are cut, 256 bytes
-// apart, from chunks as large as all before together, up to kMax; an array of
-// more than half a chunk has an allocation of its own, as has any where no
+// apart, from chunks as large as all before together, up to `most` (a batch's
+// larger: what is left of the last one is small beside its instances); an array
+// of more than half a chunk has an allocation of its own, as has any where no
 // chunk is to be had.  (Each allocation and release is a call into the driver:
 // 64 cavities of 256 x 256 cells take about 60 arrays each, 45 of the 285 ms of
 // creating, solving and closing their batch.)
 struct Arena {
-  static constexpr size_t kMin = size_t{1} << 20, kMax = size_t{256} << 20;
+  static constexpr size_t kMin = size_t{1} << 20;
+  size_t most = size_t{8} << 20;
   std::vector<void *> allocs;
   unsigned char *next = nullptr;
   size_t left = 0, taken = 0;
@@ -208,7 +210,7 @@ struct Arena {
   hipError_t alloc(T **p, size_t n)
   {
     const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
-    const size_t chunk = std::min(kMax, std::max(kMin, taken));
+    const size_t chunk = std::min(most, std::max(kMin, taken));
     *p = nullptr;
     if (bytes > left && bytes <= chunk / 2) {
       void *q = nullptr;
@@ -3303,6 +3305,7 @@ int iugkp_batch_create(const iugkp_problem *const *problems, const iugkp_options
   iugkp_batch *b = new iugkp_batch();
   b->stream = static_cast<hipStream_t>(stream);
   b->insts.resize(n);
+  b->mem.most = size_t{256} << 20;
   int mem_kind = -1;
   for (int i = 0; i < n; ++i) {
     if (!problems[i] || !options[i]) {

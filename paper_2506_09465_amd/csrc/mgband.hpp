@@ -57,7 +57,7 @@ __host__ __device__ inline int band_up0_blocks(int words, int nx, int block)
   return ((rmax - 2) * nx + 1) / block;
 }
 
-template <int SPAN, bool FLAGS>
+template <int SPAN>
 __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid, double *lds,
                                                 double *red, MGLevel *s_lv)
 {
@@ -97,8 +97,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
       __syncthreads();
       return true;
     }
-    if (FLAGS) return flag_barrier<SPAN>(a.barrier, a.flags, bid, G, epoch);
-    return grid_barrier(a.barrier, epoch, G);
+    return flag_barrier<SPAN>(a.barrier, a.flags, bid, G, epoch);
   };
 
   // part w of nwin of the rows [lo, hi)

@@ -106,7 +106,7 @@ struct MGArgs {
   double tol2;
   int max_iters;
   unsigned int *barrier;                // zero at the start of the solve, as are
-  unsigned int *flags;                  // the group's barrier words (single solves)
+  unsigned int *flags;                  // the group's barrier words
   DevScalars *sc;
   // the banded form (mgband.hpp): second buffers of r and s, and the dynamic
   // LDS layout, [stage0) the coarse result kept across a band phase, then
@@ -830,7 +830,7 @@ __device__ __forceinline__ void mg_lds_cycle(const MGLevel *lv, int Lg, int L, d
 // The preconditioned CG of one system, run by the G workgroups of a group of
 // which this one is number bid (G = 1: one workgroup alone, its exchanges
 // through workgroup-scope memory operations and workgroup barriers).
-template <int SPAN, bool FLAGS>
+template <int SPAN>
 __device__ __forceinline__ void mgcg_solve(const MGArgs &in, int G, int bid, double *lds,
                                            double *red, MGLevel *s_lv)
 {
@@ -851,8 +851,7 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &in, int G, int bid, dou
       __syncthreads();
       return true;
     }
-    if (FLAGS) return flag_barrier<SPAN>(a.barrier, a.flags, bid, G, epoch);
-    return grid_barrier(a.barrier, epoch, G);
+    return flag_barrier<SPAN>(a.barrier, a.flags, bid, G, epoch);
   };
   // The cells of a grid level this thread owns, Q of a block at a time: the Q
   // are computed first (an index past the end replaced by the block's first
@@ -1189,8 +1188,8 @@ __global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
   int rank = blockIdx.x;
   bool one_xcd = false;
   if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
-  if (one_xcd) mgcg_solve<kSpanXcd, true>(a, G, rank, lds, red, s_lv);
-  else mgcg_solve<kSpanDevice, true>(a, G, rank, lds, red, s_lv);
+  if (one_xcd) mgcg_solve<kSpanXcd>(a, G, rank, lds, red, s_lv);
+  else mgcg_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
 }
 
 // the banded form (mgband.hpp), for the meshes whose rows fit its windows;
@@ -1215,8 +1214,8 @@ __global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int
   int rank = blockIdx.x;
   bool one_xcd = false;
   if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
-  if (one_xcd) mgcg_band_solve<kSpanXcd, true>(a, G, rank, lds, red, s_lv);
-  else mgcg_band_solve<kSpanDevice, true>(a, G, rank, lds, red, s_lv);
+  if (one_xcd) mgcg_band_solve<kSpanXcd>(a, G, rank, lds, red, s_lv);
+  else mgcg_band_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1284,8 +1283,8 @@ __global__ __launch_bounds__(64 * kMgPoolWaves) void mgcg_batch_kernel(const int
   for (int e = e0; e < e1; ++e) {
     const CgJob jb = jobs[e];
     const MGArgs &a = mg[jb.inst];
-    if (a.band) mgcg_band_solve<kSpanDevice, true>(a, jb.G, jb.rank, lds, red, s_lv);
-    else mgcg_solve<kSpanDevice, true>(a, jb.G, jb.rank, lds, red, s_lv);
+    if (a.band) mgcg_band_solve<kSpanDevice>(a, jb.G, jb.rank, lds, red, s_lv);
+    else mgcg_solve<kSpanDevice>(a, jb.G, jb.rank, lds, red, s_lv);
     __syncthreads();
   }
 }

@@ -216,3 +216,21 @@ def test_mg_launch_forms_bitwise(oracle_mod, gpu, name):
         assert np.array_equal(o.E(), E.cpu().numpy()), f"{name} iteration {i}: E differs"
         assert np.array_equal(o.G(), G.cpu().numpy()), f"{name} iteration {i}: G differs"
         assert o.info().cg_iters_last == s.stats()["cg_iters_last"], name
+
+
+@pytest.mark.parametrize("nx,ny", [(5, 1), (40, 36), (131, 129)])
+def test_emission_budget_overflow_status(oracle_mod, gpu, nx, ny):
+    """A Newton step whose emission leaves the fixed-point range (a group velocity
+    of 1e-96 under the same residual) reports what the oracle reports, with one
+    partial sum of the budget and with several per thread."""
+    w = cavity_2d(n=nx, ny=ny, kn=0.02, particles=20 * nx * ny)
+    rng = np.random.default_rng(nx * ny)
+    w.vg *= 1e-96
+    w.tau = w.tau / 1e-96
+    D = rng.uniform(0.5, 2.0, size=(2, w.n_cells)) * w.vg * 1e-2
+    kw = dict(newton=True, diff_x=D[0], diff_y=D[1], tally_faces=oracle_mod.FACES_OFF,
+              cg_precond=oracle_mod.PRECOND_MG, T_init=seeded_temperature(w.n_cells))
+    o = oracle_mod.Oracle(w, **kw)
+    s = gpu.Solver(w, **kw)
+    rc = o.step(1)
+    assert rc != 0 and s.step(1) == rc
