@@ -654,7 +654,7 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
     return static_cast<size_t>(vecs + rows + (from > 0 ? lv[from].n : 0)) * sizeof(double);
   };
   int Lg = 0;
-  while (Lg < L && lv[Lg].n > iugkp::kMgLocalMax) ++Lg;
+  while (Lg < L && lv[Lg].n > (single ? iugkp::kMgLocalMax : iugkp::kMgLocalMaxBatch)) ++Lg;
   while (Lg < L - 1 && local_bytes(Lg) > lds_budget) ++Lg;
   if (local_bytes(Lg) > lds_budget) return fail(IUGKP_E_DEVICE, "no LDS for the multigrid");
   const int waves = o->cg_waves != 0 ? std::abs(o->cg_waves) : kCgWavesDefault;

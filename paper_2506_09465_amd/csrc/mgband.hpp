@@ -57,7 +57,8 @@ __host__ __device__ inline int band_up0_blocks(int words, int nx, int block)
   return ((rmax - 2) * nx + 1) / block;
 }
 
-template <int SPAN>
+// (Q0, Q1: cells of a thread in flight in the passes that load vectors, and in the sweeps)
+template <int SPAN, int Q0, int Q1>
 __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid, double *lds,
                                                 double *red, MGLevel *s_lv)
 {
@@ -180,7 +181,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
               X1[j] = mg_sweep_first_z(v.b, v.d, v.rd);
             });
       } else if (k == 0) {
-        mg_cells<2>(
+        mg_cells<Q0>(
             nB,
             [&](int i) {
               const int c = by0 * nx + i, o = by0 * nx + (i >= ob0 && i < ob1 ? i : ob0);
@@ -203,7 +204,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
               X1[j] = mg_sweep_first_z(bv, v.d, v.rd);
             });
       } else {
-        mg_cells<1>(
+        mg_cells<Q1>(
             nB,
             [&](int i) {
               const int c = by0 * nx + i;
@@ -218,7 +219,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
       __syncthreads();
       const int dj = (xy0 - by0) * S1;               // X2's index to B's
       const int ox0 = (fy0 - xy0) * nx, ox1 = (fy1 - xy0) * nx;
-      mg_cells<1>(
+      mg_cells<Q1>(
           nX, [&](int i) { return row_at(F, xy0 * nx + i, xy0 + mg_row_of(i, F.rnx)); },
           [&](int i, const MGRowZ &rw) {
             const int r = mg_row_of(i, F.rnx), j = i + r + kMgFront;
@@ -284,7 +285,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
     const int ob0 = (py0 - cy0) * nx, ob1 = (py1 - cy0) * nx, dj = (py0 - cy0) * S1;
     pads(XC, cy1 - cy0, nx);
     auto cells = [&](auto e_of) {
-      mg_cells<2>(
+      mg_cells<Q0>(
           (cy1 - cy0) * nx,
           [&](int i) {
             const int r = mg_row_of(i, F.rnx), iy = cy0 + r, ix = i - r * nx;
@@ -306,7 +307,7 @@ __device__ __forceinline__ void mgcg_band_solve(const MGArgs &in, int G, int bid
   auto sweep = [&](const MGLevel &F, const double *V, int vy0, const double *B, int by0, int y0,
                    int y1, auto out) {
     const int nx = F.nx, S1 = nx + 1, dv = (y0 - vy0) * S1, db = (y0 - by0) * S1;
-    mg_cells<1>(
+    mg_cells<Q1>(
         (y1 - y0) * nx, [&](int i) { return row_at(F, y0 * nx + i, y0 + mg_row_of(i, F.rnx)); },
         [&](int i, const MGRowZ &rw) {
           const int r = mg_row_of(i, F.rnx), j = i + r + kMgFront;

@@ -39,7 +39,11 @@ namespace iugkp {
 constexpr double kMgOmega = 0.8;        // damped Jacobi weight
 constexpr double kMgScale = 1.8;        // coarse-correction scale
 constexpr int kMgLevelsMax = 40;
-constexpr int kMgLocalMax = 1024;       // levels up to this size live in LDS
+// Levels up to this size live in LDS: of single solves, whose groups save the
+// barriers of a level more (256 x 256 cells 778 us per solve, with 256 856), and
+// of a batch's, whose workgroups use the LDS for longer band windows (256 uneven
+// cavities: 256 / 512 / 1024 343 / 343 / 374 ms, eight of 128 x 128 68 / 64 / 61).
+constexpr int kMgLocalMax = 1024, kMgLocalMaxBatch = 512;
 
 struct MGLevel {
   int nx, ny, n, has_y;
@@ -1214,8 +1218,8 @@ __global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int
   int rank = blockIdx.x;
   bool one_xcd = false;
   if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
-  if (one_xcd) mgcg_band_solve<kSpanXcd>(a, G, rank, lds, red, s_lv);
-  else mgcg_band_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
+  if (one_xcd) mgcg_band_solve<kSpanXcd, 2, 1>(a, G, rank, lds, red, s_lv);
+  else mgcg_band_solve<kSpanDevice, 2, 1>(a, G, rank, lds, red, s_lv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,6 +1271,8 @@ __global__ __launch_bounds__(kCgThreadsMax) void cg_batch_kernel(const Inst *__r
   }
 }
 
+// (A batch's groups are small, their workgroups with many cells per thread: four
+// and two cells of them in flight.)
 // the multigrid instances' pool: job (instance, rank) runs member `rank` of
 // the instance's group of G workgroups (mg: the instances' arguments); 8-wave
 // workgroups, whose lanes have the registers the solve takes when its
@@ -1283,7 +1289,7 @@ __global__ __launch_bounds__(64 * kMgPoolWaves) void mgcg_batch_kernel(const int
   for (int e = e0; e < e1; ++e) {
     const CgJob jb = jobs[e];
     const MGArgs &a = mg[jb.inst];
-    if (a.band) mgcg_band_solve<kSpanDevice>(a, jb.G, jb.rank, lds, red, s_lv);
+    if (a.band) mgcg_band_solve<kSpanDevice, 4, 2>(a, jb.G, jb.rank, lds, red, s_lv);
     else mgcg_solve<kSpanDevice>(a, jb.G, jb.rank, lds, red, s_lv);
     __syncthreads();
   }
