@@ -50,12 +50,14 @@ constexpr int kCgGridMax = 64;               // workgroups of one CG group (barr
 // The banded multigrid CG of a single solve runs on a workgroup per two rows of
 // its level 1 (its phases wait for the loads of a few cells per thread one after
 // another): as many as one XCD holds while the solve's vectors stay in its L2
-// (up to kMgXcdBlocks blocks of 256 cells), beyond that kMgGroupMax anywhere.
-// us per solve on 32 in one XCD / up to 128 anywhere: 160 x 160 cells 577 / 667,
-// 224 x 224 776 / 789, 256 x 256 904 / 795, 512 x 512 1861 / 1478; 128 x 128 on 8 /
-// 32: 559 / 432.
+// (up to kMgXcdBlocks blocks of 256 cells), beyond that kMgGroupMax anywhere (a
+// workgroup fills a CU, and the groups of four hardware queues have to fit the
+// device at once).
+// us per solve on 32 in one XCD / more anywhere: 160 x 160 cells 577 / 667, 224 x
+// 224 776 / 789, 256 x 256 904 / 795; 512 x 512 on 32 / 64 / 128 3120 / 2600 / 2070;
+// 128 x 128 on 8 / 32 559 / 432.
 constexpr int kMgXcdBlocks = 200;
-constexpr int kMgGroupMax = 128;
+constexpr int kMgGroupMax = kCgGridMax;
 // tree blocks per CG workgroup of a single solve: a mesh of up to kCgAloneMax
 // blocks takes one workgroup (5 blocks 297 us per solve against 356 on two;
 // 12 blocks 6.9 ms against 6.6 on three), others kCgWavesMin, and up to

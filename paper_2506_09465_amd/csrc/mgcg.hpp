@@ -1207,7 +1207,7 @@ constexpr int kMgBandThreads = 512;
 // made 76000 instructions of it, and 70 us per iteration), levels' addresses are
 // scalars to global memory, the rows each workgroup takes are worked out once
 // per solve, and the small levels run from registers' addresses on records.
-// us per iteration, before and after: 512 x 512 cells 123 and 82, 256 x 256 68
+// us per iteration, before and after: 512 x 512 cells 123 and 100, 256 x 256 68
 // and 44, 128 x 128 50 and 24, 64 x 64 38 and 17, 30 x 20 20 and 13; the 256 x
 // 256 cavity to steady state 24.4 to 17.8 ms.
 __global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int G)

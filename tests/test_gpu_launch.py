@@ -234,3 +234,31 @@ def test_emission_budget_overflow_status(oracle_mod, gpu, nx, ny):
     s = gpu.Solver(w, **kw)
     rc = o.step(1)
     assert rc != 0 and s.step(1) == rc
+
+
+@pytest.mark.parametrize("n", [128, 256])
+def test_mg_groups_of_many_streams(gpu, oracle_mod, n):
+    """Newton steps with the multigrid CG from eight threads at once, each on a
+    stream of its own: what each solver returns alone."""
+    import threading
+
+    w = cavity_2d(n=n, kn=0.1, particles=100_000, newton=True)
+    kw = dict(tally_faces=oracle_mod.FACES_OFF, cg_precond=gpu.PRECOND_MG, own_stream=True)
+    one = gpu.Solver(w, **kw)
+    for _ in range(3):
+        assert one.step(1) == 0
+    ss = [gpu.Solver(w, **kw) for _ in range(8)]
+    rcs = [None] * 8
+
+    def work(i):
+        rcs[i] = [ss[i].step(1) for _ in range(3)]
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    for s, rc in zip(ss, rcs):
+        assert rc == [0, 0, 0]
+        assert torch.equal(s.state()[2], one.state()[2])
