@@ -1606,6 +1606,7 @@ int upload_inst(const InstHost &ih, int inst_index, Inst *d_inst, TileDesc *d_ti
 struct BlockHost {
   iugkp::BlockRun run{};
   int rounds = 0, grid = 0;
+  bool faces = false;              // the LDS has room for y-face tallies
   bool quiet = false;              // also for gray analog iterations without face tallies
   size_t lds = 0, plan_lds = 0;
   std::vector<void *> allocs;
@@ -1922,7 +1923,9 @@ int enqueue_iteration(iugkp_handle *h, int faces)
   iugkp::prepare_kernel<<<dim3(cdiv(nprep, 256), K), 256, 0, s>>>(h->d_inst, faces, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(h->ev[0], s));
-  bool by_blocks = h->blocks.rounds > 0;
+  // (blocks of a handle without face tallies have no room for those that
+  // iugkp_step_faces asks for)
+  bool by_blocks = h->blocks.rounds > 0 && (!faces || h->blocks.faces);
   if (by_blocks && K == 1 && !ih.d.estimator)
     by_blocks = faces ? (form = pick_form(h)) == kFormStripes : h->blocks.quiet;
   if (by_blocks) {
@@ -2187,6 +2190,7 @@ int plan_blocks(iugkp_handle *h)
   r.units0 = d_units0;
   r.n_units0 = static_cast<uint32_t>(units.size());
   b.grid = n_cu;
+  b.faces = faces != 0;
   b.quiet = h->ih.d.lam_min < kBlockQuietCells * std::min(m.dx, m.dy) &&
             (T == 1 || flights >= kBlockQuietFlights || m.n_cells > kBlockQuietMesh);
   b.lds = static_cast<size_t>(iugkp::block_words(ex_max, ey_max, has_null, faces, ratios)) * sizeof(long long);
