@@ -27,6 +27,7 @@
 #include "kernels.hpp"
 #include "mgcg.hpp"
 #include "blocks.hpp"
+#include "plan.hpp"
 
 namespace {
 
@@ -85,15 +86,6 @@ constexpr int kWindowHaloNull = 20;          // a single solve's with null colli
                                              // largest window's LDS for every workgroup)
 constexpr size_t kLdsWordsMax = 6144;        // 48 KB of 64-bit tallies per workgroup
 constexpr int kLdsWallsMax = 1024;
-// A tile's particles are split over several workgroups where the tiles alone
-// leave compute units idle (a 100-cell film has 15): up to kSplitTarget
-// workgroups per launch (four per compute unit), of at least kSplitMin
-// particles (one per lane) and of one particle per kSplitWords words of LDS
-// window, which every workgroup clears and flushes.  Measured: film of 100
-// cells, 1e5 particles, particle step 658 -> 30 us (512 / 2048 particles at
-// least: 27 / 38 us, but the two-time film's solve 1.85 ms against 2.2 / 3.0);
-// 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with null collisions,
-// 1e6 particles 1188 -> 729 us (one particle per 4 or 2 words: 806 / 1182).
 // The particle step by domain blocks (blocks.hpp) against emitter tiles.  An
 // expected-value step takes blocks from kBlockMinFlightsEv rays per iteration
 // (40 x 30 cells, 3e4 rays: 129 against 282 us by tiles).  An analog one with
@@ -115,9 +107,6 @@ constexpr int kBlockQuietMesh = 32768;
 // for fewer LDS images (512 / 1024 / 2048 units: two-material square 30.5 /
 // 31.5 / 33.0 ms, expected-value cavity 8.6 / 8.1 / 9.3 ms)
 constexpr int kBlockTarget = 512, kBlockTargetEv = 1024;
-constexpr int kSplitTarget = 1024;
-constexpr int kSplitMin = 256;
-constexpr int kSplitWords = 8;
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -386,25 +375,31 @@ int scale_exponent(const iugkp_problem *p, double tau_min, const std::vector<dou
   return 62 - ((mant == 0.5) ? e - 1 : e);
 }
 
-// Split the tiles' particles over `target` workgroups or more where the tiles
-// alone are fewer.
-void split_tiles(InstHost &ih, int target)
+// Split the tiles' particles over several workgroups where the tiles alone are
+// few (split_chunk): one of K launches together.
+int split_tiles(InstHost &ih, int K)
 {
   const Inst &d = ih.d;
-  const double all = static_cast<double>(d.m.n_emit) * d.N;
-  const double chunk = std::max({all / target, static_cast<double>(kSplitMin),
-                                 static_cast<double>(ih.lds_bytes / sizeof(long long)) / kSplitWords});
+  int dev = 0, n_cu = 0, lds_max = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  std::vector<double> tiles;
+  for (const TileDesc &t : ih.tiles)
+    tiles.push_back(static_cast<double>(t.kind == 0 ? t.ex * t.ey : t.ex) * d.N);
+  const double chunk = iugkp::split_chunk(tiles, ih.lds_bytes / sizeof(long long), d.has_null != 0,
+                                          K, n_cu, static_cast<size_t>(lds_max));
   std::vector<TileDesc> out;
-  for (const TileDesc &t : ih.tiles) {
-    const double p = static_cast<double>(t.kind == 0 ? t.ex * t.ey : t.ex) * d.N;
-    const int parts = std::max(1, static_cast<int>(p / chunk + 0.5));
+  for (size_t i = 0; i < tiles.size(); ++i) {
+    const int parts = iugkp::split_parts(tiles[i], chunk);
     for (int k = 0; k < parts; ++k) {
-      out.push_back(t);
+      out.push_back(ih.tiles[i]);
       out.back().part = k;
       out.back().parts = parts;
     }
   }
   ih.tiles.swap(out);
+  return IUGKP_OK;
 }
 
 // Tile table and LDS window: the whole domain when its tallies fit in LDS,
@@ -1012,7 +1007,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
     ih.blocks = multi_cg && blocks_wanted(p, o, n, flights_go_far(p, tau.data(), nc, tmin, d.lam_min) ? n : 0.0);
   }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
-  if (multi_cg) split_tiles(ih, kSplitTarget);
+  if (multi_cg && (rc = split_tiles(ih, 1))) return rc;
 
 #define ALLOC(ptr, n) \
   if (ih.alloc(&(ptr), (n)) != hipSuccess) return fail(IUGKP_E_NOMEM, "hipMalloc failed");
@@ -1388,7 +1383,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.n_bands = K;
     d.Gs = nullptr;
     plan_tiles(ih);
-    split_tiles(ih, std::max(1, kSplitTarget / K));
+    if ((rc = split_tiles(ih, K))) return rc;
     // row stripes for a band's face-tallied iterations when its free paths
     // reach half the domain's height (and 7 cells): a band with shorter ones
     // has long chains of null collisions wherever its relaxation time is

@@ -1,0 +1,70 @@
+"""The rules of the launch planning (csrc/plan.hpp, plain C++): compiled here
+with g++ and asked directly, no GPU."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2506_09465_amd", "csrc")
+
+SHIM = r"""
+#include <cstdint>
+#include "plan.hpp"
+using namespace iugkp;
+extern "C" {
+int64_t split_total(const double *t, int n, int64_t lds_words, int has_null, int K, int n_cu,
+                    int64_t lds_max)
+{
+  std::vector<double> v(t, t + n);
+  const double chunk = split_chunk(v, lds_words, has_null != 0, K, n_cu, lds_max);
+  int64_t total = 0;
+  for (double p : v) total += split_parts(p, chunk);
+  return total;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    if not shutil.which("g++"):
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    so = d / "libplan.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC,
+                    str(d / "shim.cpp"), "-o", str(so)], check=True)
+    lib = C.CDLL(str(so))
+    lib.split_total.restype = C.c_int64
+    lib.split_total.argtypes = [C.c_void_p, C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64]
+    return lib
+
+
+CUS, LDS = 256, 163840
+
+
+# (tiles of particles, LDS words of a window, null collisions, launches together)
+@pytest.mark.parametrize("n,particles,words,null,K", [
+    (165, 3072, 12700, 0, 1),       # 164 x 161 cells: a CU's LDS per workgroup
+    (174, 3120, 2158, 0, 1),        # a long film
+    (84, 6912, 12700, 0, 1), (15, 16000, 102, 0, 1), (15, 1600000, 204, 1, 1),
+    (90, 40000, 6000, 1, 3), (3, 1, 10, 0, 1),
+])
+def test_split_tiles_stay_resident_together(plan, n, particles, words, null, K):
+    """Tiles that fit the device at once are not split beyond it."""
+    t = np.full(n, float(particles))
+    total = plan.split_total(t.ctypes.data, n, words, null, K, CUS, LDS)
+    room = max(1, CUS * min(8, max(1, LDS // (8 * words))) // K)
+    assert n <= total <= room
+
+
+def test_split_tiles_fill_the_device(plan):
+    """A film of few tiles takes hundreds of workgroups, many tiles stay whole."""
+    t = np.full(15, 6.7e4)
+    assert 300 <= plan.split_total(t.ctypes.data, 15, 102, 0, 1, CUS, LDS) <= 1024
+    t = np.full(4000, 300.0)
+    assert plan.split_total(t.ctypes.data, 4000, 5000, 0, 1, CUS, LDS) == 4000
