@@ -326,7 +326,8 @@ def bench_nongray(P, dev, steps, warmup, ceil):
             "crossings_per_flight": round(cr / max(fl, 1), 2),
             "segments_per_flight": round(sg / max(fl, 1), 2),
             "march_GBs_algorithmic": round(mb / (ms_m / 1e3) / 1e9, 2) if ms_m else None,
-            "roofline": tally_roofline(ceil, cr + sg + fl, steps, ms_m, mb, "march_kernel")}
+            "roofline": tally_roofline(ceil, cr + sg + fl, steps, ms_m, mb,
+                                       FORM_KERNELS[s.march_form()])}
     s.close()
     return out
 
@@ -537,6 +538,12 @@ def bench_c0_time_to_steady(P, dev):
     return out
 
 
+# the kernel of each particle-step form
+FORM_KERNELS = {"tiles256": "march_kernel", "tiles512": "march_kernel",
+                "stripes": "march_stripes_kernel",
+                "stripes_pieces": "march_stripes_pieces_kernel", "blocks": "block_march_kernel"}
+
+
 def bench_c2_gray(P, dev, steps, ceil):
     """The 512 x 512 gray two-material square (left half's relaxation time 100x
     the right half's, Kn 0.01 on the right: about 99 of 100 candidate
@@ -573,9 +580,7 @@ def bench_c2_gray(P, dev, steps, ceil):
                               for f, v in form_ms.items()},
             "roofline": tally_roofline(ceil, cr + sg + fl, steps, ms_m,
                                        march_bytes(fl, cr, sg, b["n_emitters"] * steps, True) / steps,
-                                       {"stripes": "march_stripes_kernel",
-                                        "stripes_pieces": "march_stripes_pieces_kernel"}.get(
-                                           form, "march_kernel"))}
+                                       FORM_KERNELS[form])}
 
 
 def cpu_baseline_nongray():

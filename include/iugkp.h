@@ -299,16 +299,24 @@ int iugkp_get_stats(iugkp_handle *h, iugkp_stats *stats);
 /* The particle step's form for the face-tallied iterations (the A4 march of
  * Sec. 3.1; how it is run is an implementation choice, not the paper's): 0 =
  * emitter tiles of 256 threads, 1 = emitter tiles of 512 threads, 2 = row
- * stripes (with null collisions: domain blocks), 3 = row stripes with the y faces in pieces (without null
- * collisions); -1 while the handle still measures them.  A 2D gray single solve
- * with the automatic march and the default block size times one face-tallied
- * iteration in each form (after an untimed first one) and keeps the fastest;
- * later handles of the same mesh, particles per emitter, null-collision
- * setting and free path in cells (to half an octave) start with it.  Every
- * form gives the same tallies bit for bit.  ms (NULL or host float[4]): the
- * measured particle-step milliseconds per form, -1 where not measured.
+ * stripes, 3 = row stripes with the y faces in pieces (without null
+ * collisions), 4 = domain blocks; -1 while the handle still measures them.  A
+ * 2D gray single solve with the automatic march and the default block size
+ * times one face-tallied iteration in each form that may be the fastest (after
+ * an untimed first one) and keeps the fastest; later handles of the same mesh,
+ * particles per emitter, null-collision setting, free path in cells and mean
+ * relaxation time over the smallest (both to half an octave) start with it.
+ * Every form gives the same tallies bit for bit.  ms (NULL or host float[4]):
+ * the measured particle-step milliseconds, -1 where not measured: of forms 0 to
+ * 2, then of form 4 with null collisions, of form 3 without.
  * Returns 0, or IUGKP_E_INVALID_ARG for a NULL handle. */
 int iugkp_march_tuning(iugkp_handle *h, int *form, float *ms);
+
+/* The form (numbered as above) in which the last iteration's particle step ran,
+ * -1 before the first one and for the persistent scheme, and the form whose
+ * time iugkp_march_tuning gives last.  Either pointer may be NULL.
+ * Returns 0, or IUGKP_E_INVALID_ARG for a NULL handle. */
+int iugkp_march_form(iugkp_handle *h, int *last, int *fourth);
 
 /* Adjoint of the steady state reached by this handle (an addition to the
  * paper, which has no adjoint): given dL/dT per cell for a loss L(T), the

@@ -267,6 +267,7 @@ struct InstHost {
   int stripe_R = 0, stripe_S = 0, stripe_C = 0;
   size_t stripe_lds = 0;
   bool blocks = false;               // domain blocks wanted (the handle's step, all bands)
+  double mean_tau = 1.0;             // mean relaxation time over the smallest
   int stripe_pref = 0;               // the planner's choice (stripes set up for a search too)
   // the persistent scheme's row-stripe face pass (rows per stripe, stripes,
   // chunks, LDS bytes; 0 rows: y faces as global atomics in the move)
@@ -923,12 +924,10 @@ bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, double flight
 }
 
 // Whether flights with null collisions go far: free path lam on the smallest
-// relaxation time tmin, relaxation times tau[0, n).
-bool flights_go_far(const iugkp_problem *p, const double *tau, int n, double tmin, double lam)
+// relaxation time, mean relaxation time over the smallest.
+bool flights_go_far(const iugkp_problem *p, bool has_null, double mean, double lam)
 {
-  double sum = 0.0;
-  for (int c = 0; c < n; ++c) sum += tau[c] / tmin;
-  return sum > n && lam * (sum / n) > kWindowHalo * std::min(p->dx, p->dy);
+  return has_null && lam * mean > kWindowHalo * std::min(p->dx, p->dy);
 }
 
 int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, bool multi_cg,
@@ -947,11 +946,13 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   if (p->source && (rc = fetch_host(p->source, nc, p->mem_kind, src))) return rc;
   if ((rc = fetch_host(p->wall_T, nb, p->mem_kind, wall))) return rc;
   if (p->T_init && (rc = fetch_host(p->T_init, nc, p->mem_kind, T0))) return rc;
-  double tmin = INFINITY, tmax = 0.0;
+  double tmin = INFINITY, tmax = 0.0, tsum = 0.0;
+  const double inv_nc = 1.0 / nc;
   for (double t : tau) {
     if (!(t > 0.0) || !std::isfinite(t)) return fail(IUGKP_E_INVALID_ARG, "tau must be > 0 and finite");
     tmin = std::min(tmin, t);
     tmax = std::max(tmax, t);
+    tsum += t * inv_nc;
   }
   if (tmax > 1e6 * tmin) return fail(IUGKP_E_INVALID_ARG, "tau_max / tau_min exceeds 1e6");
   for (double t : wall)
@@ -1004,7 +1005,9 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   d.F = scale_exponent(p, tmin, wall, T0, src);
   {
     const double n = static_cast<double>(ne) * d.N;
-    ih.blocks = multi_cg && blocks_wanted(p, o, n, flights_go_far(p, tau.data(), nc, tmin, d.lam_min) ? n : 0.0);
+    ih.mean_tau = tsum / tmin;
+    ih.blocks = multi_cg &&
+                blocks_wanted(p, o, n, flights_go_far(p, d.has_null, ih.mean_tau, d.lam_min) ? n : 0.0);
   }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
   if (multi_cg && (rc = split_tiles(ih, 1))) return rc;
@@ -1151,11 +1154,13 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   // ray from its start, and that re-walk costs more than the tile kernel's
   // global atomics on the 256^2 cavity)
   // (an automatic march with the default block size also sets stripes up for
-  // the particle-step form search of the handle)
+  // the particle-step form search of the handle; beside blocks those of paths
+  // that stripes take by choice: on shorter ones they are the slowest form,
+  // 400 ms against 30 by blocks on the 512 x 512 two-material square)
   const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
   const bool lam_stripes = d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
   if (multi_cg && p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS &&
-      !ih.blocks &&
+      (!ih.blocks || lam_stripes) &&
       ((ev && o->march >= 2) ||
        (!ev && o->tally_faces != IUGKP_FACES_OFF &&
         (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0)))))) {
@@ -1254,15 +1259,19 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
       return fail(IUGKP_E_INVALID_ARG, "band_C and band_vg must be > 0 and finite");
   std::vector<double> ts(K), lam(K);
   std::vector<int> has_null(K);
+  std::vector<double> mean(K);
+  const double inv_nc = 1.0 / nc;
   for (int k = 0; k < K; ++k) {
-    double tmin = INFINITY, tmax = 0.0;
+    double tmin = INFINITY, tmax = 0.0, tsum = 0.0;
     for (int c = 0; c < nc; ++c) {
       const double t = tau[static_cast<size_t>(k) * nc + c];
       if (!(t > 0.0) || !std::isfinite(t)) return fail(IUGKP_E_INVALID_ARG, "tau must be > 0 and finite");
       tmin = std::min(tmin, t);
       tmax = std::max(tmax, t);
+      tsum += t * inv_nc;
     }
     if (tmax > 1e6 * tmin) return fail(IUGKP_E_INVALID_ARG, "tau_max / tau_min exceeds 1e6 in a band");
+    mean[k] = tsum / tmin;
     ts[k] = tmin;
     lam[k] = bv[k] * tmin;
     has_null[k] = (tmax != tmin);
@@ -1330,8 +1339,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   rest.assign(K - 1, InstHost{});
   double far = 0.0;
   for (int k = 0; k < K; ++k)
-    if (flights_go_far(p, tau.data() + static_cast<size_t>(k) * nc, nc, ts[k], lam[k]))
-      far += static_cast<double>(ne) * N;
+    if (flights_go_far(p, has_null[k], mean[k], lam[k])) far += static_cast<double>(ne) * N;
   const bool blocks = blocks_wanted(p, o, static_cast<double>(K) * ne * N, far);
   ih0.blocks = blocks;
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
@@ -1627,14 +1635,10 @@ struct iugkp_handle {
   std::vector<int> stripe_bands;  // bands whose face-tallied iterations run row stripes
   size_t lds = 0;                 // march window (largest over the bands)
   int block = 256;
-  // the particle-step form of face-tallied iterations (pick_form)
-  bool form_search = false;
-  int form = -1;                  // chosen (kForm*), -1 while searching
-  int form_default = 0;
-  bool form_warm = false;         // the first face-tallied iteration has run
-  int form_next = 0;              // candidates measured so far
-  int form_last = -1;             // candidate of the iteration in flight
-  float form_ms[4] = {-1.f, -1.f, -1.f, -1.f};
+  // the particle step's form in iterations without [0] and with [1] face
+  // tallies, and the last iteration's (kForm*; -1: none)
+  iugkp::FormSearch forms[2];
+  int form_faces = 0, form_ran = -1;
   DevScalars *hsc = nullptr;   // pinned host mirror
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   uint32_t iter = 0;
@@ -1760,69 +1764,46 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
   return IUGKP_OK;
 }
 
-// The particle step's form for the face-tallied iterations of a 2D gray
-// single solve with the automatic march and the default block size: emitter
-// tiles with 256 or 512 threads per workgroup, or row stripes (flights with
-// null collisions: domain blocks in their place).  Measured,
-// not guessed: the first face-tallied iteration runs the planner's choice
-// (not timed: first launches), the next three one candidate each (timed by
-// the step's events), then the fastest, which every later handle of the
-// same class (mesh, particles per emitter, null collisions, free path in
-// cells to half an octave) takes from its first iteration.  The forms give
-// the same tallies bit for bit, so the search changes only the time.
-enum : int { kFormTiles256 = 0, kFormTiles512 = 1, kFormStripes = 2, kFormPieces = 3, kForms = 4 };
-// (row stripes in pieces only without null collisions)
-int n_forms(const InstHost &ih) { return ih.d.has_null ? kFormPieces : kForms; }
-struct FormKey {
-  int nx, ny, N, has_null, lam2;
-  bool operator<(const FormKey &o) const
-  {
-    if (nx != o.nx) return nx < o.nx;
-    if (ny != o.ny) return ny < o.ny;
-    if (N != o.N) return N < o.N;
-    if (has_null != o.has_null) return has_null < o.has_null;
-    return lam2 < o.lam2;
-  }
-};
-std::mutex g_form_mu;
-std::map<FormKey, int> g_form_choice;
+using iugkp::kFormBlocks;
+using iugkp::kFormPieces;
+using iugkp::kFormStripes;
+using iugkp::kFormTiles256;
+using iugkp::kFormTiles512;
+
+// The class a measured choice holds for: the mesh, the particles per emitter,
+// null collisions, and the free path in cells to half an octave.
+using FormKey = std::vector<int>;
+int half_octaves(double v) { return static_cast<int>(std::lround(2.0 * std::log2(v))); }
 
 FormKey form_key(const InstHost &ih)
 {
   const Mesh &m = ih.d.m;
-  const double cells = ih.d.lam_min / std::min(m.dx, m.dy);
   return FormKey{m.nx, m.ny, static_cast<int>(ih.d.N), ih.d.has_null,
-                 static_cast<int>(std::lround(2.0 * std::log2(cells)))};
+                 half_octaves(ih.d.lam_min / std::min(m.dx, m.dy))};
 }
 
-// the form of the next face-tallied iteration (h->form_last: the candidate
-// it measures, or -1)
-int pick_form(iugkp_handle *h)
+std::mutex g_form_mu;
+std::map<FormKey, int> g_form_choice;
+
+// A single solve's: also the mean relaxation time over the smallest (how far
+// flights with null collisions go) and the candidates themselves.
+FormKey search_key(const iugkp_handle *h, int faces)
 {
-  h->form_last = -1;
-  if (h->form >= 0) return h->form;
-  if (!h->form_search) return h->form_default;
-  if (!h->form_warm) {
-    h->form_warm = true;
-    return h->form_default;
-  }
-  h->form_last = h->form_next;
-  return h->form_next;
+  FormKey k = form_key(h->ih);
+  k.push_back(half_octaves(h->ih.mean_tau));
+  k.push_back(faces);
+  for (int f : h->forms[faces].cand) k.push_back(f);
+  return k;
 }
 
-// after the iteration: its particle-step time for the candidate it measured
+// after an iteration: its particle-step time for the candidate it measured;
+// the choice is kept for later handles of the class
 void record_form(iugkp_handle *h, float ms)
 {
-  if (h->form_last < 0) return;
-  h->form_ms[h->form_last] = ms;
-  h->form_last = -1;
-  if (++h->form_next < n_forms(h->ih)) return;
-  int best = 0;
-  for (int f = 1; f < n_forms(h->ih); ++f)
-    if (h->form_ms[f] < h->form_ms[best]) best = f;
-  h->form = best;
+  iugkp::FormSearch &f = h->forms[h->form_faces];
+  if (!f.record(ms)) return;
   std::lock_guard<std::mutex> lock(g_form_mu);
-  g_form_choice[form_key(h->ih)] = best;
+  g_form_choice[search_key(h, h->form_faces)] = f.form;
 }
 
 // The row-stripe particle step of one instance (ih, its descriptor at
@@ -1886,8 +1867,7 @@ int enqueue_iteration(iugkp_handle *h, int faces)
                              (m.ny + 2) * m.nx);
   const int K = h->bh.K;
   int rc = IUGKP_OK;
-  int form = -1;
-  h->form_last = -1;
+  h->form_faces = faces ? 1 : 0;
   if (ih.d.persist) {
     const int nmax = std::max(std::max(std::max(m.n_cells, m.n_b), std::max(m.n_fx, m.n_fy)),
                               (m.ny + 2) * m.nx);
@@ -1918,19 +1898,16 @@ int enqueue_iteration(iugkp_handle *h, int faces)
   iugkp::prepare_kernel<<<dim3(cdiv(nprep, 256), K), 256, 0, s>>>(h->d_inst, faces, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(h->ev[0], s));
-  // (blocks of a handle without face tallies have no room for those that
-  // iugkp_step_faces asks for)
-  bool by_blocks = h->blocks.rounds > 0 && (!faces || h->blocks.faces);
-  if (by_blocks && K == 1 && !ih.d.estimator)
-    by_blocks = faces ? (form = pick_form(h)) == kFormStripes : h->blocks.quiet;
-  if (by_blocks) {
+  const int form = h->forms[h->form_faces].pick();
+  h->form_ran = form;
+  if (form == kFormBlocks) {
     if ((rc = launch_blocks(h->blocks, h->d_inst, ih.d.estimator != 0, faces, s))) return rc;
-  } else if (ih.d.estimator && ih.stripe_R > 0) {
+  } else if (form == kFormStripes && ih.d.estimator) {
     iugkp::march_stripes_ev_kernel<kStripeBlock>
         <<<dim3(ih.stripe_C, ih.stripe_S), kStripeBlock, ih.stripe_lds, s>>>(h->d_inst, ih.stripe_R,
                                                                               ih.stripe_C, faces);
     HIP_TRY(hipGetLastError());
-  } else if (K > 1 && faces && !h->stripe_bands.empty()) {
+  } else if (form == kFormStripes && K > 1) {
     // frequency bands: the long-path bands by row stripes, the others' tiles
     if (h->n_tiles_f > 0) {
       rc = launch_march(h->d_inst, h->d_tiles, h->n_tiles_f, h->lds, h->block, faces, 0, false, s);
@@ -1940,8 +1917,7 @@ int enqueue_iteration(iugkp_handle *h, int faces)
       const InstHost &bk = (k == 0) ? h->ih : h->xb[k - 1];
       if ((rc = launch_stripes(bk, h->d_inst + k, !bk.d.has_null, s))) return rc;
     }
-  } else if (faces && ih.stripe_R > 0 &&
-             ((form = pick_form(h)) == kFormStripes || form == kFormPieces)) {
+  } else if (form == kFormStripes || form == kFormPieces) {
     if ((rc = launch_stripes(ih, h->d_inst, form == kFormPieces, s))) return rc;
   } else {
     const int block = (form == kFormTiles512) ? 512 : h->block;
@@ -2197,6 +2173,48 @@ int plan_blocks(iugkp_handle *h)
   return IUGKP_OK;
 }
 
+// The forms a handle's iterations run in: the planner's choice, and what a 2D
+// gray analog solve with the automatic march and the default block size times
+// against it in its face-tallied iterations.
+void plan_forms(iugkp_handle *h)
+{
+  const InstHost &ih = h->ih;
+  const Mesh &m = ih.d.m;
+  const bool blocks = h->blocks.rounds > 0, stripes = ih.stripe_R > 0, null = ih.d.has_null != 0;
+  iugkp::FormSearch &off = h->forms[0], &on = h->forms[1];
+  if (ih.d.estimator || h->bh.K > 1) {
+    const bool more = h->bh.K > 1 ? !h->stripe_bands.empty() : stripes;
+    if (blocks) off.def = kFormBlocks;
+    else if (stripes && ih.d.estimator) off.def = kFormStripes;
+    // (blocks of a handle without face tallies have no room for those that
+    // iugkp_step_faces asks for)
+    if (blocks && h->blocks.faces) on.def = kFormBlocks;
+    else if (more) on.def = kFormStripes;
+    return;
+  }
+  if (blocks && h->blocks.quiet) off.def = kFormBlocks;
+  const bool fit = blocks && h->blocks.faces;
+  if (!stripes && !fit) return;
+  // flights that cross the mesh mostly in one flight: stripes (two materials,
+  // 324 x 324 cells, 4 particles per emitter, path 744 cells 0.15 ms against 0.65
+  // by blocks; 248 x 248, 86, 144 cells 2.6 against 1.8)
+  if (fit)
+    on.def = stripes && ih.d.lam_min >= 0.5 * m.ny * m.dy ? kFormStripes : kFormBlocks;
+  else
+    on.def = !ih.stripe_pref ? kFormTiles256 : (ih.opt.march == 3 && !null) ? kFormPieces : kFormStripes;
+  if (ih.opt.march != 0 || ih.opt.block_size != 0) return;
+  // (far flights outgrow the tiles' windows: of the tiles only the better form
+  // of 48 drawn problems, where stripes are timed too)
+  if (!(fit && stripes)) on.cand.push_back(kFormTiles256);
+  on.cand.push_back(kFormTiles512);
+  if (stripes) on.cand.push_back(kFormStripes);
+  if (stripes && !null) on.cand.push_back(kFormPieces);
+  if (fit) on.cand.push_back(kFormBlocks);
+  std::lock_guard<std::mutex> lock(g_form_mu);
+  const auto it = g_form_choice.find(search_key(h, 1));
+  if (it != g_form_choice.end()) on.form = it->second;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2232,24 +2250,13 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
     free_handle(h);
     return rc;
   }
-  const bool blocks = h->blocks.rounds > 0;
-  if (!bands && (h->ih.stripe_R > 0 || blocks) && !h->ih.d.estimator) {
-    h->form_default = blocks ? kFormStripes
-                      : !h->ih.stripe_pref ? kFormTiles256
-                      : (options->march == 3 && !h->ih.d.has_null) ? kFormPieces : kFormStripes;
-    h->form_search = (options->march == 0 && options->block_size == 0);
-    if (h->form_search) {
-      std::lock_guard<std::mutex> lock(g_form_mu);
-      const auto it = g_form_choice.find(form_key(h->ih));
-      if (it != g_form_choice.end()) h->form = it->second;
-    }
-  }
   h->n_tiles = 0;
   for (int k = 0; k < K; ++k) {
     h->n_tiles += static_cast<int>(band_of(h, k).tiles.size());
     h->lds = std::max(h->lds, band_of(h, k).lds_bytes);
     if (bands && band_of(h, k).stripe_R > 0) h->stripe_bands.push_back(k);
   }
+  plan_forms(h);
   if (hipMalloc(reinterpret_cast<void **>(&h->d_inst), K * sizeof(Inst)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void **>(&h->d_tiles), h->n_tiles * sizeof(TileDesc)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void **>(&h->hsc), sizeof(DevScalars)) != hipSuccess) {
@@ -2516,9 +2523,20 @@ int iugkp_get_stats(iugkp_handle *h, iugkp_stats *stats)
 int iugkp_march_tuning(iugkp_handle *h, int *form, float *ms)
 {
   if (!h) return fail(IUGKP_E_INVALID_ARG, "handle is NULL");
-  if (form) *form = h->form >= 0 ? h->form : (h->form_search ? -1 : h->form_default);
-  if (ms)
-    for (int f = 0; f < kForms; ++f) ms[f] = h->form_ms[f];
+  const iugkp::FormSearch &f = h->forms[1];
+  if (form) *form = f.kept();
+  if (ms) {
+    for (int i = 0; i < kFormPieces; ++i) ms[i] = f.ms[i];
+    ms[3] = f.ms[h->ih.d.has_null ? kFormBlocks : kFormPieces];
+  }
+  return IUGKP_OK;
+}
+
+int iugkp_march_form(iugkp_handle *h, int *last, int *fourth)
+{
+  if (!h) return fail(IUGKP_E_INVALID_ARG, "handle is NULL");
+  if (last) *last = h->form_ran;
+  if (fourth) *fourth = h->ih.d.has_null ? kFormBlocks : kFormPieces;
   return IUGKP_OK;
 }
 

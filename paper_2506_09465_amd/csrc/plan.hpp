@@ -54,4 +54,57 @@ inline double split_chunk(const std::vector<double> &tiles, size_t lds_words, bo
   return chunk;
 }
 
+// The forms of a handle's particle step.
+enum : int {
+  kFormTiles256 = 0,        // emitter tiles, 256 threads a workgroup (or the handle's block size)
+  kFormTiles512 = 1,        // emitter tiles, 512 threads
+  kFormStripes = 2,         // row stripes
+  kFormPieces = 3,          // row stripes with the y faces in pieces (without null collisions)
+  kFormBlocks = 4,          // domain blocks
+  kForms = 5
+};
+
+// Which form the iterations of one kind (with or without face tallies) take.
+// Measured, not guessed, where there are candidates: the first iteration runs
+// the planner's choice (not timed: first launches), the next ones a candidate
+// each, timed by the step's events, the others the fastest.  Every form gives
+// the same tallies bit for bit, so the search changes only the time.
+struct FormSearch {
+  std::vector<int> cand;    // forms to time (none: the planner's choice stays)
+  int def = kFormTiles256;  // the planner's choice
+  int form = -1;            // the fastest, once known
+  float ms[kForms] = {-1.f, -1.f, -1.f, -1.f, -1.f};
+  size_t next = 0;          // candidates timed
+  bool warm = false;        // the first iteration has run
+  bool timing = false;      // the iteration in flight is a candidate's
+
+  // the form of the next iteration
+  int pick()
+  {
+    timing = false;
+    if (form >= 0) return form;
+    if (cand.empty()) return def;
+    if (!warm) {
+      warm = true;
+      return def;
+    }
+    timing = true;
+    return cand[next];
+  }
+  // after it, with its time; whether that settled the choice
+  bool record(float t)
+  {
+    if (!timing) return false;
+    timing = false;
+    ms[cand[next]] = t;
+    if (++next < cand.size()) return false;
+    form = cand[0];
+    for (int f : cand)
+      if (ms[f] < ms[form]) form = f;
+    return true;
+  }
+  // the form kept, or -1 while it is searched
+  int kept() const { return form >= 0 ? form : cand.empty() ? def : -1; }
+};
+
 }  // namespace iugkp

@@ -221,17 +221,27 @@ class Solver:
         L.check(L.lib().iugkp_get_stats(self.h, C.byref(st)), "iugkp_get_stats")
         return st.as_dict()
 
+    _FORMS = ("tiles256", "tiles512", "stripes", "stripes_pieces", "blocks")
+
     def march_tuning(self):
         """(form, ms): the particle step's form for face-tallied iterations
-        ("tiles256", "tiles512", "stripes", "stripes_pieces", or None while the
-        handle still measures them) and the measured milliseconds per form
-        (None where not measured)."""
-        form = C.c_int(0)
+        ("tiles256", "tiles512", "stripes", "stripes_pieces", "blocks", or None
+        while the handle still measures them) and the measured milliseconds per
+        form (None where not measured)."""
+        form, fourth = C.c_int(0), C.c_int(0)
         ms = (C.c_float * 4)()
         L.check(L.lib().iugkp_march_tuning(self.h, C.byref(form), ms), "iugkp_march_tuning")
-        names = ("tiles256", "tiles512", "stripes", "stripes_pieces")
-        return (names[form.value] if form.value >= 0 else None,
+        L.check(L.lib().iugkp_march_form(self.h, None, C.byref(fourth)), "iugkp_march_form")
+        names = self._FORMS[:3] + (self._FORMS[fourth.value],)
+        return (self._FORMS[form.value] if form.value >= 0 else None,
                 {n: (float(v) if v >= 0 else None) for n, v in zip(names, ms)})
+
+    def march_form(self):
+        """The form in which the last iteration's particle step ran (as named by
+        march_tuning; None before the first one and for the persistent scheme)."""
+        last = C.c_int(0)
+        L.check(L.lib().iugkp_march_form(self.h, C.byref(last), None), "iugkp_march_form")
+        return self._FORMS[last.value] if last.value >= 0 else None
 
     def residuals(self) -> np.ndarray:
         n = self.stats()["iters"]

@@ -53,3 +53,47 @@ def test_faces_on_demand_without_face_tallies_bands(oracle_mod, gpu):
         assert o.step(1, faces=faces) == 0 and s.step(1, faces=faces) == 0
         if faces:
             _same_state(o, s, f"it{i}")
+
+
+def _settle(s, most=8):
+    for _ in range(most):
+        if s.march_tuning()[0] is not None:
+            return
+        assert s.step(1) == 0
+    assert s.march_tuning()[0] is not None
+
+
+@pytest.mark.parametrize("n,first,second", [(61, 3.0, 100.0), (63, 100.0, 3.0)])
+def test_a_measured_form_holds_for_its_own_class(gpu, n, first, second):
+    """Two problems that differ only in the ratio of their relaxation times: at 3
+    flights stay near and blocks are no candidate, at 100 they are.  Neither
+    takes the form measured for the other; a third of the second's class does."""
+    mk = lambda r: gpu.Solver(two_material_2d(n=n, kn_right=0.05, ratio=r, particles=200_000),
+                              tally_faces=gpu.FACES_EVERY, T_init=seeded_temperature(n * n))
+    a = mk(first)
+    _settle(a)
+    b = mk(second)
+    assert b.march_tuning()[0] is None
+    _settle(b)
+    for s, r in ((a, first), (b, second)):
+        measured = {k for k, v in s.march_tuning()[1].items() if v is not None}
+        assert ("blocks" in measured) == (r == 100.0)
+        assert s.step(1) == 0 and s.march_form() == s.march_tuning()[0]
+    assert mk(second).march_tuning()[0] == b.march_tuning()[0]
+
+
+def test_row_stripes_are_timed_beside_blocks(gpu):
+    """Far flights on paths of many cells: both forms are candidates, and every
+    iteration of the search gives the tiles' tallies."""
+    w = two_material_2d(n=75, kn_right=0.6, ratio=12.0, particles=150_000)
+    kw = dict(tally_faces=gpu.FACES_EVERY, T_init=seeded_temperature(w.n_cells))
+    s, ref = gpu.Solver(w, **kw), gpu.Solver(w, march=1, **kw)
+    ran = []
+    for _ in range(6):
+        assert s.step(1) == 0 and ref.step(1) == 0
+        ran.append(s.march_form())
+        ts, tr = s.tallies(), ref.tallies()
+        for k in ts:
+            assert torch.equal(ts[k], tr[k]), (ran, k)
+    assert {"stripes", "blocks"} <= set(ran)
+    assert {"stripes", "blocks"} <= {k for k, v in s.march_tuning()[1].items() if v is not None}

@@ -25,6 +25,19 @@ int64_t split_total(const double *t, int n, int64_t lds_words, int has_null, int
   for (double p : v) total += split_parts(p, chunk);
   return total;
 }
+// one search: the forms of `iters` iterations, form f taking t[f] (ran), and the
+// form kept after each (kept)
+void search(const int *cand, int n, int def, const float *t, int iters, int *ran, int *kept)
+{
+  FormSearch s;
+  s.cand.assign(cand, cand + n);
+  s.def = def;
+  for (int i = 0; i < iters; ++i) {
+    ran[i] = s.pick();
+    s.record(t[ran[i]]);
+    kept[i] = s.kept();
+  }
+}
 }
 """
 
@@ -41,6 +54,8 @@ def plan(tmp_path_factory):
     lib = C.CDLL(str(so))
     lib.split_total.restype = C.c_int64
     lib.split_total.argtypes = [C.c_void_p, C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int64]
+    lib.search.restype = None
+    lib.search.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p]
     return lib
 
 
@@ -68,3 +83,17 @@ def test_split_tiles_fill_the_device(plan):
     assert 300 <= plan.split_total(t.ctypes.data, 15, 102, 0, 1, CUS, LDS) <= 1024
     t = np.full(4000, 300.0)
     assert plan.split_total(t.ctypes.data, 4000, 5000, 0, 1, CUS, LDS) == 4000
+
+
+@pytest.mark.parametrize("cand,default,times,best", [
+    ([0, 1, 2, 3], 2, [4, 3, 1, 2, 9], 2), ([1, 2, 4], 4, [1, 5, 6, 1, 7], 1),
+    ([0, 4], 0, [5, 1, 1, 1, 2], 4), ([], 4, [1, 1, 1, 1, 2], 4), ([4], 0, [1, 1, 1, 1, 2], 4),
+])
+def test_form_search(plan, cand, default, times, best):
+    """The planner's choice first, every candidate once, then the fastest of them."""
+    c, t = np.array(cand + [0], np.int32), np.array(times, np.float32)
+    ran, kept = np.zeros(9, np.int32), np.zeros(9, np.int32)
+    plan.search(c.ctypes.data, len(cand), default, t.ctypes.data, 9, ran.ctypes.data, kept.ctypes.data)
+    head = ([default] + cand) if cand else []
+    assert ran.tolist() == head + [best] * (9 - len(head))
+    assert kept.tolist() == [-1] * len(cand) + [best] * (9 - len(cand))
