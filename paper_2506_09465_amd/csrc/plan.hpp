@@ -14,7 +14,9 @@ namespace iugkp {
 // (one per lane) and of one particle per kSplitWords words of LDS window, which
 // every workgroup clears and flushes; and where the tiles fit the device at
 // once, so do their shares (a second round of workgroups waits for the first:
-// 164 x 161 cells, 286 workgroups of a CU's LDS each, 47 us against 35 unsplit).
+// 164 x 161 cells, 286 workgroups of a CU's LDS each, 47 us against 35 unsplit;
+// with null collisions a second round evens the chains out: 53 x 181, path 26
+// cells, ratio 61, 380 us against 507 with the limit).
 // Measured: film of 100 cells, 1e5 particles, particle step 658 -> 30 us (512 /
 // 2048 particles at least: 27 / 38 us, but the two-time film's solve 1.85 ms
 // against 2.2 / 3.0); 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with
@@ -49,7 +51,7 @@ inline double split_chunk(const std::vector<double> &tiles, size_t lds_words, bo
     for (double p : tiles) n += split_parts(p, chunk);
     return n;
   };
-  if (tiles.size() <= room)
+  if (!has_null && tiles.size() <= room)
     while (total() > room) chunk *= 1.05;
   return chunk;
 }

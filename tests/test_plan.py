@@ -66,15 +66,16 @@ CUS, LDS = 256, 163840
 @pytest.mark.parametrize("n,particles,words,null,K", [
     (165, 3072, 12700, 0, 1),       # 164 x 161 cells: a CU's LDS per workgroup
     (174, 3120, 2158, 0, 1),        # a long film
-    (84, 6912, 12700, 0, 1), (15, 16000, 102, 0, 1), (15, 1600000, 204, 1, 1),
-    (90, 40000, 6000, 1, 3), (3, 1, 10, 0, 1),
+    (84, 6912, 12700, 0, 1), (15, 16000, 102, 0, 1), (90, 40000, 6000, 0, 3), (3, 1, 10, 0, 1),
 ])
 def test_split_tiles_stay_resident_together(plan, n, particles, words, null, K):
-    """Tiles that fit the device at once are not split beyond it."""
+    """Tiles that fit the device at once are not split beyond it, except with null
+    collisions, whose chains a second round evens out."""
     t = np.full(n, float(particles))
     total = plan.split_total(t.ctypes.data, n, words, null, K, CUS, LDS)
     room = max(1, CUS * min(8, max(1, LDS // (8 * words))) // K)
     assert n <= total <= room
+    assert plan.split_total(t.ctypes.data, n, words, 1, K, CUS, LDS) >= total
 
 
 def test_split_tiles_fill_the_device(plan):
