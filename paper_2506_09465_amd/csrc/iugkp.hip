@@ -93,16 +93,8 @@ constexpr int kLdsWallsMax = 1024;
 // flights whose mean free path, over the cells, exceeds the tiles' window
 // margin of kWindowHalo cells (three bands on 64 x 64, 4e4 flights, all far: 98
 // against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
-// One case is measured apart, a gray iteration without face tallies, whose tile
-// march resolves long segments in closed form and sends few tallies out of its
-// windows.  There blocks take free paths below kBlockQuietCells (256 x 256, 1e7
-// flights, 12.8 cells: 3.8 against 8.5 ms; 128 cells: 2.9 against 1.3) with
-// kBlockQuietFlights flights or a mesh beyond kBlockQuietMesh cells or of one
-// block (128 x 128, 1e6 / 3e6 flights: 1.07 / 1.48 against 0.71 / 1.43 ms; 256 x
-// 256, 1e6: 1.50 against 2.16; 60 x 60, 4e5: 0.41 against 0.53).
+// (Iterations without face tallies: quiet_blocks.)
 constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
-constexpr double kBlockQuietCells = 32.0, kBlockQuietFlights = 3e6;
-constexpr int kBlockQuietMesh = 32768;
 // units of work per round of the blocks' step: more balance better, fewer pay
 // for fewer LDS images (512 / 1024 / 2048 units: two-material square 30.5 /
 // 31.5 / 33.0 ms, expected-value cavity 8.6 / 8.1 / 9.3 ms)
@@ -925,9 +917,9 @@ bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, double flight
 
 // Whether flights with null collisions go far: free path lam on the smallest
 // relaxation time, mean relaxation time over the smallest.
-bool flights_go_far(const iugkp_problem *p, bool has_null, double mean, double lam)
+bool flights_go_far(bool has_null, double mean, double lam, double dx, double dy)
 {
-  return has_null && lam * mean > kWindowHalo * std::min(p->dx, p->dy);
+  return has_null && lam * mean > kWindowHalo * std::min(dx, dy);
 }
 
 int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, bool multi_cg,
@@ -1007,7 +999,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
     const double n = static_cast<double>(ne) * d.N;
     ih.mean_tau = tsum / tmin;
     ih.blocks = multi_cg &&
-                blocks_wanted(p, o, n, flights_go_far(p, d.has_null, ih.mean_tau, d.lam_min) ? n : 0.0);
+                blocks_wanted(p, o, n, flights_go_far(d.has_null, ih.mean_tau, d.lam_min, p->dx, p->dy) ? n : 0.0);
   }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
   if (multi_cg && (rc = split_tiles(ih, 1))) return rc;
@@ -1339,7 +1331,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   rest.assign(K - 1, InstHost{});
   double far = 0.0;
   for (int k = 0; k < K; ++k)
-    if (flights_go_far(p, has_null[k], mean[k], lam[k])) far += static_cast<double>(ne) * N;
+    if (flights_go_far(has_null[k], mean[k], lam[k], p->dx, p->dy)) far += static_cast<double>(ne) * N;
   const bool blocks = blocks_wanted(p, o, static_cast<double>(K) * ne * N, far);
   ih0.blocks = blocks;
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
@@ -1379,6 +1371,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.crn = (o->rng_mode == IUGKP_RNG_CRN);
     d.epoch = o->rng_epoch;
     d.has_null = has_null[k];
+    ih.mean_tau = mean[k];
     d.newton = 0;
     d.faces_each = (o->tally_faces == IUGKP_FACES_EVERY);
     d.faces_out = (o->tally_faces != IUGKP_FACES_OFF);
@@ -1610,7 +1603,6 @@ struct BlockHost {
   iugkp::BlockRun run{};
   int rounds = 0, grid = 0;
   bool faces = false;              // the LDS has room for y-face tallies
-  bool quiet = false;              // also for gray analog iterations without face tallies
   size_t lds = 0, plan_lds = 0;
   std::vector<void *> allocs;
   void release()
@@ -1786,11 +1778,16 @@ std::mutex g_form_mu;
 std::map<FormKey, int> g_form_choice;
 
 // A single solve's: also the mean relaxation time over the smallest (how far
-// flights with null collisions go) and the candidates themselves.
+// flights with null collisions go), every band's, and the candidates themselves.
 FormKey search_key(const iugkp_handle *h, int faces)
 {
   FormKey k = form_key(h->ih);
   k.push_back(half_octaves(h->ih.mean_tau));
+  for (const InstHost &b : h->xb) {
+    k.push_back(b.d.has_null);
+    k.push_back(half_octaves(b.d.lam_min / std::min(b.d.m.dx, b.d.m.dy)));
+    k.push_back(half_octaves(b.mean_tau));
+  }
   k.push_back(faces);
   for (int f : h->forms[faces].cand) k.push_back(f);
   return k;
@@ -1898,7 +1895,11 @@ int enqueue_iteration(iugkp_handle *h, int faces)
   iugkp::prepare_kernel<<<dim3(cdiv(nprep, 256), K), 256, 0, s>>>(h->d_inst, faces, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(h->ev[0], s));
-  const int form = h->forms[h->form_faces].pick();
+  // (without face tallies the search waits until most emitters fly: a solve's
+  // first iterations, from cold cells, are no measure)
+  const int form = h->forms[h->form_faces].pick(
+      faces || 2.0 * static_cast<double>(h->st.flights) >=
+                   static_cast<double>(K) * m.n_emit * static_cast<double>(ih.d.N));
   h->form_ran = form;
   if (form == kFormBlocks) {
     if ((rc = launch_blocks(h->blocks, h->d_inst, ih.d.estimator != 0, faces, s))) return rc;
@@ -2162,8 +2163,6 @@ int plan_blocks(iugkp_handle *h)
   r.n_units0 = static_cast<uint32_t>(units.size());
   b.grid = n_cu;
   b.faces = faces != 0;
-  b.quiet = h->ih.d.lam_min < kBlockQuietCells * std::min(m.dx, m.dy) &&
-            (T == 1 || flights >= kBlockQuietFlights || m.n_cells > kBlockQuietMesh);
   b.lds = static_cast<size_t>(iugkp::block_words(ex_max, ey_max, has_null, faces, ratios)) * sizeof(long long);
   b.plan_lds = static_cast<size_t>(T) * sizeof(unsigned long long);
   HIP_TRY(hipMemcpyAsync(d_blk, blk.data(), blk.size() * sizeof(blk[0]), hipMemcpyHostToDevice, h->stream));
@@ -2175,24 +2174,43 @@ int plan_blocks(iugkp_handle *h)
 
 // The forms a handle's iterations run in: the planner's choice, and what a 2D
 // gray analog solve with the automatic march and the default block size times
-// against it in its face-tallied iterations.
+// against it in its face-tallied iterations, any analog handle with blocks in
+// the others.
 void plan_forms(iugkp_handle *h)
 {
   const InstHost &ih = h->ih;
   const Mesh &m = ih.d.m;
   const bool blocks = h->blocks.rounds > 0, stripes = ih.stripe_R > 0, null = ih.d.has_null != 0;
   iugkp::FormSearch &off = h->forms[0], &on = h->forms[1];
+  auto known = [&](int faces) {
+    iugkp::FormSearch &f = h->forms[faces];
+    std::lock_guard<std::mutex> lock(g_form_mu);
+    const auto it = g_form_choice.find(search_key(h, faces));
+    if (it != g_form_choice.end()) f.form = it->second;
+  };
+  if (ih.d.estimator) {
+    off.def = blocks ? kFormBlocks : stripes ? kFormStripes : kFormTiles256;
+  } else if (blocks) {
+    std::vector<double> lam;
+    for (int k = 0; k < h->bh.K; ++k) lam.push_back(band_of(h, k).d.lam_min / std::min(m.dx, m.dy));
+    const double flights = static_cast<double>(m.n_emit) * ih.d.N;
+    if (iugkp::quiet_blocks(lam, flights, h->blocks.run.T)) {
+      off.def = iugkp::quiet_blocks_first(lam, flights) ? kFormBlocks : kFormTiles256;
+      off.cand = {kFormTiles256, kFormBlocks};
+      // (an iteration's longest chain of null collisions sets the tiles' time:
+      // 125 x 66 cells, ratio 187, 0.36 to 0.86 ms from one to the next)
+      off.rounds = 3;
+      known(0);
+    }
+  }
   if (ih.d.estimator || h->bh.K > 1) {
     const bool more = h->bh.K > 1 ? !h->stripe_bands.empty() : stripes;
-    if (blocks) off.def = kFormBlocks;
-    else if (stripes && ih.d.estimator) off.def = kFormStripes;
     // (blocks of a handle without face tallies have no room for those that
     // iugkp_step_faces asks for)
     if (blocks && h->blocks.faces) on.def = kFormBlocks;
     else if (more) on.def = kFormStripes;
     return;
   }
-  if (blocks && h->blocks.quiet) off.def = kFormBlocks;
   const bool fit = blocks && h->blocks.faces;
   if (!stripes && !fit) return;
   // flights that cross the mesh mostly in one flight: stripes (two materials,
@@ -2210,9 +2228,7 @@ void plan_forms(iugkp_handle *h)
   if (stripes) on.cand.push_back(kFormStripes);
   if (stripes && !null) on.cand.push_back(kFormPieces);
   if (fit) on.cand.push_back(kFormBlocks);
-  std::lock_guard<std::mutex> lock(g_form_mu);
-  const auto it = g_form_choice.find(search_key(h, 1));
-  if (it != g_form_choice.end()) on.form = it->second;
+  known(1);
 }
 
 }  // namespace

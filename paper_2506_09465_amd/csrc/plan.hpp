@@ -15,8 +15,9 @@ namespace iugkp {
 // every workgroup clears and flushes; and where the tiles fit the device at
 // once, so do their shares (a second round of workgroups waits for the first:
 // 164 x 161 cells, 286 workgroups of a CU's LDS each, 47 us against 35 unsplit;
-// with null collisions a second round evens the chains out: 53 x 181, path 26
-// cells, ratio 61, 380 us against 507 with the limit).
+// with null collisions a second round evens the chains out: 115 x 190, path 1.3
+// cells, ratio 180, 3.8 ms against 5.5 with the limit; 199 x 74, path 350, ratio
+// 23, with face tallies 0.50 against 0.80).
 // Measured: film of 100 cells, 1e5 particles, particle step 658 -> 30 us (512 /
 // 2048 particles at least: 27 / 38 us, but the two-time film's solve 1.85 ms
 // against 2.2 / 3.0); 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with
@@ -76,30 +77,32 @@ struct FormSearch {
   int def = kFormTiles256;  // the planner's choice
   int form = -1;            // the fastest, once known
   float ms[kForms] = {-1.f, -1.f, -1.f, -1.f, -1.f};
-  size_t next = 0;          // candidates timed
+  int rounds = 1;           // iterations timed per candidate, in turn
+  size_t next = 0;          // iterations timed
   bool warm = false;        // the first iteration has run
   bool timing = false;      // the iteration in flight is a candidate's
 
-  // the form of the next iteration
-  int pick()
+  // the form of the next iteration (ready: it is like those to come)
+  int pick(bool ready = true)
   {
     timing = false;
     if (form >= 0) return form;
     if (cand.empty()) return def;
-    if (!warm) {
+    if (!warm || !ready) {
       warm = true;
       return def;
     }
     timing = true;
-    return cand[next];
+    return cand[next % cand.size()];
   }
   // after it, with its time; whether that settled the choice
   bool record(float t)
   {
     if (!timing) return false;
     timing = false;
-    ms[cand[next]] = t;
-    if (++next < cand.size()) return false;
+    float &sum = ms[cand[next % cand.size()]];
+    sum = (next < cand.size() ? 0.f : sum) + t / static_cast<float>(rounds);
+    if (++next < cand.size() * rounds) return false;
     form = cand[0];
     for (int f : cand)
       if (ms[f] < ms[form]) form = f;
@@ -108,5 +111,38 @@ struct FormSearch {
   // the form kept, or -1 while it is searched
   int kept() const { return form >= 0 ? form : cand.empty() ? def : -1; }
 };
+
+// Iterations without face tallies: the tile march resolves long segments in
+// closed form and sends few tallies out of its windows, so blocks can only win
+// on short ones, and where the line lies depends on how evenly the tiles share
+// the work (two materials side by side, free path 10 cells, ratio 20, 60 flights
+// per emitter: 192 x 192 cells 1.14 ms by blocks against 0.88, 256 x 256 1.72
+// against 3.50, 262 x 262 1.80 against 1.84).  So both are timed where blocks may
+// win: half of the flights on paths below kQuietCells, and enough of them for a
+// block (of 1700 drawn problems blocks were more than 7% faster in none that
+// this leaves out).  The first iterations run by blocks where they mostly win:
+// half of the flights on paths below kQuietFirst, kQuietFlights in all.
+constexpr double kQuietCells = 24.0, kQuietPerBlock = 5e3;
+constexpr double kQuietFirst = 16.0, kQuietFlights = 3e6;
+
+// the share of the bands on paths (in cells) below `cells`
+inline double short_paths(const std::vector<double> &lam, double cells)
+{
+  double n = 0.0;
+  for (double l : lam) n += l < cells ? 1.0 : 0.0;
+  return n / static_cast<double>(lam.size());
+}
+// lam: each band's free path in cells (a gray problem: its only one); flights:
+// of each band; T: blocks of all bands
+inline bool quiet_blocks(const std::vector<double> &lam, double flights, int T)
+{
+  return short_paths(lam, kQuietCells) >= 0.5 &&
+         flights * static_cast<double>(lam.size()) >= kQuietPerBlock * T;
+}
+inline bool quiet_blocks_first(const std::vector<double> &lam, double flights)
+{
+  return short_paths(lam, kQuietFirst) >= 0.5 &&
+         flights * static_cast<double>(lam.size()) >= kQuietFlights;
+}
 
 }  // namespace iugkp

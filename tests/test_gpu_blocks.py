@@ -2,10 +2,12 @@
 take them, and that every form a handle chooses gives the oracle's tallies bit
 for bit (integer tallies and the same IEEE operations in the same order: no
 tolerance)."""
+import numpy as np
 import pytest
 
 from synth import cavity_2d, nongray_two_material_2d, seeded_temperature, two_material_2d
 from test_gpu_bands import _same_state
+from test_gpu_launch import _same_cells
 from test_gpu_parity import _pair, _same_iteration
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +99,43 @@ def test_row_stripes_are_timed_beside_blocks(gpu):
             assert torch.equal(ts[k], tr[k]), (ran, k)
     assert {"stripes", "blocks"} <= set(ran)
     assert {"stripes", "blocks"} <= {k for k, v in s.march_tuning()[1].items() if v is not None}
+
+
+def test_forms_without_face_tallies(oracle_mod, gpu):
+    """Short far flights: tiles and blocks are timed once most emitters fly, and
+    each iteration gives the oracle's tallies in either."""
+    w = two_material_2d(n=61, kn_right=0.05, ratio=30.0, particles=300_000)
+    o, s = _pair(oracle_mod, gpu, w, tally_faces=oracle_mod.FACES_OFF,
+                 T_init=seeded_temperature(w.n_cells))
+    ran = []
+    for i in range(9):
+        assert o.step(1) == 0 and s.step(1) == 0
+        ran.append(s.march_form())
+        _same_cells(o, s, f"it{i} {ran}")
+    assert ran[1:7] == ["tiles256", "blocks"] * 3 and ran[7] == ran[8]
+    # from cold cells the search has not begun while only the walls emit
+    c = gpu.Solver(two_material_2d(n=77, kn_right=0.02, ratio=30.0, particles=300_000),
+                   tally_faces=gpu.FACES_OFF, T_init=np.full(77 * 77, 1.0))
+    for _ in range(3):
+        assert c.step(1) == 0
+        if 2 * c.stats()["flights"] < c.stats()["n_emitters"] * c.stats()["n_per_emitter"]:
+            assert c.march_form() == "tiles256"
+
+
+@pytest.mark.parametrize("K,timed", [(2, False), (8, True)])
+def test_forms_of_bands_without_face_tallies(gpu, K, timed):
+    """Two bands on paths longer than the mesh keep to tiles, eight of which most
+    are short time blocks as well; every iteration gives the tiles' tallies."""
+    w = nongray_two_material_2d(n=64, K=K, ratio=20.0, particles=K * 16 * (64 * 64 + 256))
+    kw = dict(tally_faces=gpu.FACES_OFF, T_init=seeded_temperature(64 * 64))
+    s, ref = gpu.Solver(w, **kw), gpu.Solver(w, march=1, **kw)
+    ran = []
+    for _ in range(4):
+        assert s.step(1) == 0 and ref.step(1) == 0
+        ran.append(s.march_form())
+        ts, tr = s.tallies(), ref.tallies()
+        for k in ("D", "W", "B"):
+            assert torch.equal(ts[k], tr[k]), (ran, k)
+        assert torch.equal(s.state()[3], ref.state()[3])
+    assert ("blocks" in ran) == timed
+    assert ref.march_form() == "tiles256"
