@@ -27,40 +27,12 @@
 // waits for another.
 #pragma once
 
+#include "plan.hpp"
+
 namespace iugkp {
 
 constexpr int kBlockThreads = 1024;
 constexpr int kBlockWaves = kBlockThreads / 64;
-constexpr int kChunk = 64;                 // records per chunk
-constexpr int kRecBytes = 64;
-constexpr int kOpenChunks = 4;             // partly filled chunks a unit can leave
-constexpr int kUnitChunksMax = 256;        // chunks of one unit of work
-constexpr int kUnitChunksMin = 32;         // two per wavefront, fewer where that leaves CUs idle
-constexpr int kUnitChunksLow = 8;          // (256 x 256, 3e6 flights 2.25 -> 2.01 ms)
-constexpr int kBlocksMax = 4096;           // blocks of a launch, all bands
-
-// chunks of a unit where `total` chunks are to be cut
-__host__ __device__ inline uint32_t unit_chunks(uint32_t total, uint32_t target, uint32_t cus)
-{
-  const uint32_t want = (total + target - 1u) / target, each = (total + cus - 1u) / cus;
-  uint32_t lo = each < static_cast<uint32_t>(kUnitChunksMin) ? each : static_cast<uint32_t>(kUnitChunksMin);
-  if (lo < static_cast<uint32_t>(kUnitChunksLow)) lo = static_cast<uint32_t>(kUnitChunksLow);
-  const uint32_t n = want > lo ? want : lo;
-  return n < static_cast<uint32_t>(kUnitChunksMax) ? n : static_cast<uint32_t>(kUnitChunksMax);
-}
-
-struct BlockDesc {
-  int inst, x0, y0, ex, ey;
-  int n_e;                                 // emitters: the block's cells, then its wall faces
-  uint32_t base;                           // first chunk of the flights sampled here
-  int nb[4];                               // blocks entered at -x, +x, -y, +y
-};
-
-struct BlockUnit {
-  int t;                                   // block
-  uint32_t first, count;                   // chunks of its input
-  uint32_t slab, cap;                      // output chunks [slab, slab + cap)
-};
 
 struct BlockRun {
   const BlockDesc *blk;                    // [T + 1] (the last: the number of sampled chunks)
@@ -77,14 +49,6 @@ struct BlockRun {
   uint32_t *seg_off, *seg_pos, *seg_pre;   // a block's input: its list pieces, their first
                                            // chunk in the block's sequence
 };
-
-// LDS words of a block's tallies, and of its acceptance ratios rounded to 32
-// bits (analog flights with null collisions)
-__host__ __device__ inline int block_words(int ex, int ey, int has_w, int faces, int ratios)
-{
-  return ex * ey * (has_w ? 2 : 1) + (faces ? ex * (ey + 1) : 0) + 2 * (ex + ey) +
-         (ratios ? (ex * ey + 1) / 2 : 0);
-}
 
 // Walking lanes below which a wavefront serves its others (candidate collision
 // and next free path, or the next flight), and faces per lane between two

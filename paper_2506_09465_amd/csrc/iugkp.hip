@@ -27,7 +27,6 @@
 #include "kernels.hpp"
 #include "mgcg.hpp"
 #include "blocks.hpp"
-#include "plan.hpp"
 
 namespace {
 
@@ -95,10 +94,6 @@ constexpr int kLdsWallsMax = 1024;
 // against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
 // (Iterations without face tallies: quiet_blocks.)
 constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
-// units of work per round of the blocks' step: more balance better, fewer pay
-// for fewer LDS images (512 / 1024 / 2048 units: two-material square 30.5 /
-// 31.5 / 33.0 ms, expected-value cavity 8.6 / 8.1 / 9.3 ms)
-constexpr int kBlockTarget = 512, kBlockTargetEv = 1024;
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -258,7 +253,7 @@ struct InstHost {
   // row-stripe particle step for face-tallied iterations (single solves)
   int stripe_R = 0, stripe_S = 0, stripe_C = 0;
   size_t stripe_lds = 0;
-  bool blocks = false;               // domain blocks wanted (the handle's step, all bands)
+  iugkp::BlockPlan blocks;           // the handle's domain blocks (all bands)
   double mean_tau = 1.0;             // mean relaxation time over the smallest
   int stripe_pref = 0;               // the planner's choice (stripes set up for a search too)
   // the persistent scheme's row-stripe face pass (rows per stripe, stripes,
@@ -905,14 +900,62 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
   return IUGKP_OK;
 }
 
-// Whether a handle's particle step may run by domain blocks: 2D, enough
-// expected-value rays or far flights with null collisions (kBlockMinFlights).
-bool blocks_wanted(const iugkp_problem *p, const iugkp_options *o, double flights, double far)
+// Row stripes of a gray single solve: on request (march 2 or 3; expected-value
+// rays only so: every stripe follows a ray from its start, and that re-walk
+// costs more than the tile kernel's global atomics on the 256^2 cavity), or
+// with face tallies where the paths are long, and for the particle-step form
+// search of a handle with the automatic march and the default block size;
+// beside blocks only on paths that stripes take by choice: on shorter ones they
+// are the slowest form, 400 ms against 30 by blocks on the 512 x 512
+// two-material square.
+int plan_gray_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, InstHost &ih)
 {
+  const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
+  const bool lam_stripes = ih.d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
+  if (p->dim != 2 || o->scheme != IUGKP_SCHEME_EMITTERS || (ih.blocks.T > 0 && !lam_stripes) ||
+      !((ev && o->march >= 2) ||
+        (!ev && o->tally_faces != IUGKP_FACES_OFF &&
+         (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0))))))
+    return IUGKP_OK;
+  const int rc = plan_stripes(ih, s, ev, o->march >= 2 || lam_stripes);
+  if (rc) return rc;
+  if (o->march >= 2 && ih.stripe_R == 0)
+    return fail(IUGKP_E_INVALID_ARG, "row stripes do not fit this mesh");
+  return IUGKP_OK;
+}
+
+// Row stripes for a band's face-tallied iterations when its free paths reach
+// half the domain's height (and 7 cells): a band with shorter ones has long
+// chains of null collisions wherever its relaxation time is above the minimum,
+// which the tile march handles better (march 1 keeps every band on tiles)
+int plan_band_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, InstHost &ih)
+{
+  if (p->dim != 2 || o->tally_faces == IUGKP_FACES_OFF || o->march == 1 ||
+      o->estimator != IUGKP_EST_ANALOG ||
+      ih.d.lam_min < kStripeMinCells * std::min(p->dx, p->dy) || ih.d.lam_min < 0.5 * p->ny * p->dy)
+    return IUGKP_OK;
+  return plan_stripes(ih, s, false, true);
+}
+
+// The domain blocks of a handle of K bands with N flights per emitter: 2D,
+// enough expected-value rays or far flights with null collisions
+// (kBlockMinFlights), and a mesh that can be cut.
+int plan_blocks(const iugkp_problem *p, const iugkp_options *o, int K, uint32_t N, bool has_null,
+                double flights, double far, iugkp::BlockPlan &out)
+{
+  out = iugkp::BlockPlan{};
   if (p->dim != 2 || o->scheme != IUGKP_SCHEME_EMITTERS || o->march != 0 || o->block_size != 0 ||
       p->nx > 0xffff || p->ny > 0xffff)
-    return false;
-  return o->estimator == IUGKP_EST_EXPECTED ? flights >= kBlockMinFlightsEv : far >= kBlockMinFlights;
+    return IUGKP_OK;
+  const bool rays = o->estimator == IUGKP_EST_EXPECTED;
+  if (rays ? flights < kBlockMinFlightsEv : far < kBlockMinFlights) return IUGKP_OK;
+  int dev = 0, n_cu = 0, lds_max = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  out = iugkp::plan_block_step(p->nx, p->ny, K, N, has_null, o->tally_faces != IUGKP_FACES_OFF, rays,
+                               n_cu, static_cast<size_t>(lds_max));
+  return IUGKP_OK;
 }
 
 // Whether flights with null collisions go far: free path lam on the smallest
@@ -998,8 +1041,8 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
   {
     const double n = static_cast<double>(ne) * d.N;
     ih.mean_tau = tsum / tmin;
-    ih.blocks = multi_cg &&
-                blocks_wanted(p, o, n, flights_go_far(d.has_null, ih.mean_tau, d.lam_min, p->dx, p->dy) ? n : 0.0);
+    const bool far = flights_go_far(d.has_null, ih.mean_tau, d.lam_min, p->dx, p->dy);
+    if (multi_cg && (rc = plan_blocks(p, o, 1, d.N, d.has_null, n, far ? n : 0.0, ih.blocks))) return rc;
   }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
   if (multi_cg && (rc = split_tiles(ih, 1))) return rc;
@@ -1142,24 +1185,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
       if ((rc = setup_mg(ih, o, s, false))) return rc;
     }
   }
-  // (expected-value rays: only on request, march == 2; every stripe follows a
-  // ray from its start, and that re-walk costs more than the tile kernel's
-  // global atomics on the 256^2 cavity)
-  // (an automatic march with the default block size also sets stripes up for
-  // the particle-step form search of the handle; beside blocks those of paths
-  // that stripes take by choice: on shorter ones they are the slowest form,
-  // 400 ms against 30 by blocks on the 512 x 512 two-material square)
-  const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
-  const bool lam_stripes = d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
-  if (multi_cg && p->dim == 2 && o->scheme == IUGKP_SCHEME_EMITTERS &&
-      (!ih.blocks || lam_stripes) &&
-      ((ev && o->march >= 2) ||
-       (!ev && o->tally_faces != IUGKP_FACES_OFF &&
-        (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0)))))) {
-    if ((rc = plan_stripes(ih, s, ev, o->march >= 2 || lam_stripes))) return rc;
-    if (o->march >= 2 && ih.stripe_R == 0)
-      return fail(IUGKP_E_INVALID_ARG, "row stripes do not fit this mesh");
-  }
+  if (multi_cg && (rc = plan_gray_stripes(p, o, s, ih))) return rc;
   if (o->scheme == IUGKP_SCHEME_PERSISTENT) {
     if (!multi_cg) return fail(IUGKP_E_INVALID_ARG, "the persistent scheme is for single solves");
     if ((rc = setup_persistent(ih, T0, gw, s))) return rc;
@@ -1332,8 +1358,12 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   double far = 0.0;
   for (int k = 0; k < K; ++k)
     if (flights_go_far(has_null[k], mean[k], lam[k], p->dx, p->dy)) far += static_cast<double>(ne) * N;
-  const bool blocks = blocks_wanted(p, o, static_cast<double>(K) * ne * N, far);
-  ih0.blocks = blocks;
+  bool any_null = false;
+  for (int k = 0; k < K; ++k) any_null = any_null || has_null[k];
+  if ((rc = plan_blocks(p, o, K, static_cast<uint32_t>(N), any_null, static_cast<double>(K) * ne * N,
+                        far, ih0.blocks)))
+    return rc;
+  const bool blocks = ih0.blocks.T > 0;
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
   int ok = 1;
   unsigned long long acc = 0, wall_acc = 0;
@@ -1385,17 +1415,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.Gs = nullptr;
     plan_tiles(ih);
     if ((rc = split_tiles(ih, K))) return rc;
-    // row stripes for a band's face-tallied iterations when its free paths
-    // reach half the domain's height (and 7 cells): a band with shorter ones
-    // has long chains of null collisions wherever its relaxation time is
-    // above the minimum, which the tile march handles better (march 1 keeps
-    // every band on tiles)
-    if (!blocks && p->dim == 2 && o->tally_faces != IUGKP_FACES_OFF && o->march != 1 &&
-        o->estimator == IUGKP_EST_ANALOG && lam[k] >= kStripeMinCells * std::min(p->dx, p->dy) &&
-        lam[k] >= 0.5 * p->ny * p->dy) {
-      const int rc = plan_stripes(ih, s, false, true);
-      if (rc) return rc;
-    }
+    if (!blocks && (rc = plan_band_stripes(p, o, s, ih))) return rc;
     double *dratio = nullptr, *dshare = nullptr;
     ALLOC(ih, dratio, nc);
     ALLOC(ih, dshare, nc);
@@ -2033,141 +2053,62 @@ int write_band_outputs(iugkp_handle *h, double *T_out, double *qx_out, double *q
 
 const InstHost &band_of(const iugkp_handle *h, int k) { return k == 0 ? h->ih : h->xb[k - 1]; }
 
-// Cut every band's mesh into blocks whose tallies fit a workgroup's LDS (the
-// fewest rounds, then the fewest blocks), round 0's units, and the record
-// chunks of two rounds.  IUGKP_E_NOMEM without the memory (the caller falls
-// back to tiles).
-int plan_blocks(iugkp_handle *h)
+// Device memory for the planned blocks (h->ih.blocks): their descriptors and
+// round 0's units, and the record chunks, lists and units of two rounds.
+// IUGKP_E_NOMEM without it.
+int setup_blocks(iugkp_handle *h)
 {
   BlockHost &b = h->blocks;
-  const Mesh &m = h->ih.d.m;
-  const int K = h->bh.K;
-  int dev = 0, n_cu = 0, lds_max = 0;
+  const iugkp::BlockPlan &p = h->ih.blocks;
+  int dev = 0, n_cu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-  int has_null = 0;
-  for (int k = 0; k < K; ++k) has_null |= band_of(h, k).d.has_null;
-  const int faces = h->ih.opt.tally_faces != IUGKP_FACES_OFF;
-  const int ratios = has_null && !h->ih.d.estimator;
-  const int words = (lds_max - 6144) / 8;           // (less the kernel's static LDS)
-  int nbx = 0, nby = 0;
-  for (int sum = 2; nbx == 0 && sum <= m.nx + m.ny; ++sum)
-    for (int x = 1; x < sum; ++x) {
-      const int y = sum - x;
-      if (x > m.nx || y > m.ny) continue;
-      if (iugkp::block_words(cdiv(m.nx, x), cdiv(m.ny, y), has_null, faces, ratios) > words) continue;
-      if (nbx == 0 || x * y < nbx * nby) {
-        nbx = x;
-        nby = y;
-      }
-    }
-  const int T1 = nbx * nby;
-  if (nbx == 0 || T1 > iugkp::kBlocksMax / K) return IUGKP_E_NOMEM;
-  std::vector<iugkp::BlockDesc> blk(static_cast<size_t>(K) * T1 + 1);
-  std::vector<iugkp::BlockUnit> units;
-  double flights = 0.0;
-  for (int k = 0; k < K; ++k) flights += static_cast<double>(m.n_emit) * band_of(h, k).d.N;
-  const int target = h->ih.d.estimator ? kBlockTargetEv : kBlockTarget;
-  // chunks of a unit of round 0
-  const double share = static_cast<double>(iugkp::unit_chunks(
-      static_cast<uint32_t>(std::min(flights / iugkp::kChunk + K * T1, 4e9)),
-      static_cast<uint32_t>(target), static_cast<uint32_t>(n_cu)));
-  unsigned long long slab = 0, base = 0;
-  int ex_max = 1, ey_max = 1;
-  for (int k = 0; k < K; ++k)
-    for (int by = 0; by < nby; ++by)
-      for (int bx = 0; bx < nbx; ++bx) {
-        const int t = k * T1 + by * nbx + bx;
-        iugkp::BlockDesc &d = blk[t];
-        d.inst = k;
-        d.x0 = static_cast<int>(static_cast<long long>(m.nx) * bx / nbx);
-        d.y0 = static_cast<int>(static_cast<long long>(m.ny) * by / nby);
-        d.ex = static_cast<int>(static_cast<long long>(m.nx) * (bx + 1) / nbx) - d.x0;
-        d.ey = static_cast<int>(static_cast<long long>(m.ny) * (by + 1) / nby) - d.y0;
-        ex_max = std::max(ex_max, d.ex);
-        ey_max = std::max(ey_max, d.ey);
-        d.n_e = d.ex * d.ey + (bx == 0 ? d.ey : 0) + (bx == nbx - 1 ? d.ey : 0) +
-                (by == 0 ? d.ex : 0) + (by == nby - 1 ? d.ex : 0);
-        d.nb[0] = bx > 0 ? t - 1 : t;               // (the mesh's edge: never entered)
-        d.nb[1] = bx < nbx - 1 ? t + 1 : t;
-        d.nb[2] = by > 0 ? t - nbx : t;
-        d.nb[3] = by < nby - 1 ? t + nbx : t;
-        const unsigned long long P = static_cast<unsigned long long>(d.n_e) * band_of(h, k).d.N;
-        const unsigned long long nc = (P + iugkp::kChunk - 1) / iugkp::kChunk;
-        d.base = static_cast<uint32_t>(base);
-        base += nc;
-        if (base >= (1ull << 25)) return IUGKP_E_NOMEM;    // (25 bits of a list entry)
-        const unsigned long long parts =
-            static_cast<unsigned long long>(std::ceil(static_cast<double>(nc) / share));
-        for (unsigned long long i = 0; i < parts; ++i) {
-          iugkp::BlockUnit u;
-          u.t = t;
-          u.first = static_cast<uint32_t>(nc * i / parts);
-          u.count = static_cast<uint32_t>(nc * (i + 1) / parts) - u.first;
-          u.cap = u.count + iugkp::kOpenChunks;
-          u.slab = static_cast<uint32_t>(slab);
-          slab += u.cap;
-          units.push_back(u);
-        }
-      }
-  blk.back().base = static_cast<uint32_t>(base);
-  const int T = K * T1;
-  // most units of a round, and most chunks: at most one chunk per 64 flights
-  // and kOpenChunks partly filled ones per unit of the round that wrote them,
-  // again kOpenChunks per unit of the round that reads them
-  const double full = static_cast<double>(base) + 1.0;
-  const double u_max = std::max({static_cast<double>(units.size()), static_cast<double>(target + T),
-                                 (full / iugkp::kUnitChunksMax + T + 1.0) /
-                                     (1.0 - static_cast<double>(iugkp::kOpenChunks) / iugkp::kUnitChunksMax)});
-  const double chunks = std::max(static_cast<double>(slab), full + 2.0 * iugkp::kOpenChunks * (u_max + 1.0));
-  if (chunks >= static_cast<double>(1u << 25)) return IUGKP_E_NOMEM;
-  const size_t n_u = static_cast<size_t>(u_max) + 1, n_c = static_cast<size_t>(chunks) + 1;
-  b.rounds = nbx + nby - 1;
   bool ok = true;
-  auto get = [&](auto **p, size_t n) {
-    void *q = nullptr;
-    ok = ok && hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(**p)) == hipSuccess;
-    if (q) b.allocs.push_back(q);
-    *p = static_cast<std::remove_reference_t<decltype(**p)> *>(q);
+  auto get = [&](auto **q, size_t n) {
+    void *m = nullptr;
+    ok = ok && hipMalloc(&m, std::max<size_t>(n, 1) * sizeof(**q)) == hipSuccess;
+    if (m) b.allocs.push_back(m);
+    *q = static_cast<std::remove_reference_t<decltype(**q)> *>(m);
   };
   iugkp::BlockRun &r = b.run;
   iugkp::BlockDesc *d_blk = nullptr;
   iugkp::BlockUnit *d_units0 = nullptr;
-  get(&d_blk, blk.size());
-  get(&d_units0, units.size());
-  get(&r.next, b.rounds);
-  get(&r.rec[1], n_c * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
-  if (b.rounds > 1) {
+  get(&d_blk, p.blk.size());
+  get(&d_units0, p.units.size());
+  get(&r.next, p.rounds);
+  get(&r.rec[1], p.n_chunks * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
+  if (p.rounds > 1) {
     for (int i = 0; i < 2; ++i) {
-      get(&r.units[i], n_u);
-      get(&r.list[i], 4 * n_c);
+      get(&r.units[i], p.n_units);
+      get(&r.list[i], 4 * p.n_chunks);
     }
-    get(&r.rec[0], n_c * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
+    get(&r.rec[0], p.n_chunks * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
     get(&r.n_units, 2);
-    get(&r.seg_off, T + 1);
-    get(&r.seg_pos, 4 * n_u);
-    get(&r.seg_pre, 4 * n_u);
+    get(&r.seg_off, p.T + 1);
+    get(&r.seg_pos, 4 * p.n_units);
+    get(&r.seg_pre, 4 * p.n_units);
   }
-  get(&r.out_n, 4 * n_u);
+  get(&r.out_n, 4 * p.n_units);
   if (!ok) {
     (void)hipGetLastError();
     b.release();
     return IUGKP_E_NOMEM;
   }
   r.blk = d_blk;
-  r.T = T;
-  r.target = static_cast<uint32_t>(target);
+  r.T = p.T;
+  r.target = static_cast<uint32_t>(p.target);
   r.cus = static_cast<uint32_t>(n_cu);
   r.units0 = d_units0;
-  r.n_units0 = static_cast<uint32_t>(units.size());
+  r.n_units0 = static_cast<uint32_t>(p.units.size());
   b.grid = n_cu;
-  b.faces = faces != 0;
-  b.lds = static_cast<size_t>(iugkp::block_words(ex_max, ey_max, has_null, faces, ratios)) * sizeof(long long);
-  b.plan_lds = static_cast<size_t>(T) * sizeof(unsigned long long);
-  HIP_TRY(hipMemcpyAsync(d_blk, blk.data(), blk.size() * sizeof(blk[0]), hipMemcpyHostToDevice, h->stream));
-  HIP_TRY(hipMemcpyAsync(d_units0, units.data(), units.size() * sizeof(units[0]), hipMemcpyHostToDevice,
+  b.rounds = p.rounds;
+  b.faces = p.faces;
+  b.lds = p.lds;
+  b.plan_lds = static_cast<size_t>(p.T) * sizeof(unsigned long long);
+  HIP_TRY(hipMemcpyAsync(d_blk, p.blk.data(), p.blk.size() * sizeof(p.blk[0]), hipMemcpyHostToDevice,
                          h->stream));
+  HIP_TRY(hipMemcpyAsync(d_units0, p.units.data(), p.units.size() * sizeof(p.units[0]),
+                         hipMemcpyHostToDevice, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   return IUGKP_OK;
 }
@@ -2261,8 +2202,17 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
   }
   const int K = h->bh.K;
   h->block = options->block_size ? options->block_size : 256;
-  // by domain blocks where wanted; without the memory as without them
-  if (h->ih.blocks && (rc = plan_blocks(h)) && rc != IUGKP_E_NOMEM) {
+  // by domain blocks where planned; without the memory as without them
+  if (h->ih.blocks.T > 0 && (rc = setup_blocks(h)) == IUGKP_E_NOMEM) {
+    h->ih.blocks = iugkp::BlockPlan{};
+    if (!bands && h->ih.stripe_R == 0) rc = plan_gray_stripes(problem, options, h->stream, h->ih);
+    if (bands) {
+      rc = plan_band_stripes(problem, options, h->stream, h->ih);
+      for (size_t k = 0; k < h->xb.size() && !rc; ++k)
+        rc = plan_band_stripes(problem, options, h->stream, h->xb[k]);
+    }
+  }
+  if (rc) {
     free_handle(h);
     return rc;
   }

@@ -2,7 +2,9 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
+#include <cstdint>
 #include <vector>
 
 namespace iugkp {
@@ -143,6 +145,154 @@ inline bool quiet_blocks_first(const std::vector<double> &lam, double flights)
 {
   return short_paths(lam, kQuietFirst) >= 0.5 &&
          flights * static_cast<double>(lam.size()) >= kQuietFlights;
+}
+
+// ---------------------------------------------------------------------------
+// Domain blocks (blocks.hpp): how a mesh is cut, and what the rounds can need.
+// ---------------------------------------------------------------------------
+constexpr int kChunk = 64;                 // records per chunk
+constexpr int kRecBytes = 64;
+constexpr int kOpenChunks = 4;             // partly filled chunks a unit can leave
+constexpr int kUnitChunksMax = 256;        // chunks of one unit of work
+constexpr int kUnitChunksMin = 32;         // two per wavefront, fewer where that leaves CUs idle
+constexpr int kUnitChunksLow = 8;          // (256 x 256, 3e6 flights 2.25 -> 2.01 ms)
+constexpr int kBlocksMax = 4096;           // blocks of a launch, all bands
+constexpr uint32_t kChunksMax = 1u << 25;  // (a list entry holds 25 bits of a chunk's number)
+constexpr size_t kBlockStaticLds = 6144;   // static LDS of the march, rounded up
+// units of work per round: more balance better, fewer pay for fewer LDS images
+// (512 / 1024 / 2048 units: two-material square 30.5 / 31.5 / 33.0 ms,
+// expected-value cavity 8.6 / 8.1 / 9.3 ms)
+constexpr int kBlockTarget = 512, kBlockTargetEv = 1024;
+
+struct BlockDesc {
+  int inst, x0, y0, ex, ey;
+  int n_e;                                 // emitters: the block's cells, then its wall faces
+  uint32_t base;                           // first chunk of the flights sampled here
+  int nb[4];                               // blocks entered at -x, +x, -y, +y
+};
+
+struct BlockUnit {
+  int t;                                   // block
+  uint32_t first, count;                   // chunks of its input
+  uint32_t slab, cap;                      // output chunks [slab, slab + cap)
+};
+
+// chunks of a unit where `total` chunks are to be cut
+constexpr uint32_t unit_chunks(uint32_t total, uint32_t target, uint32_t cus)
+{
+  const uint32_t want = (total + target - 1u) / target, each = (total + cus - 1u) / cus;
+  uint32_t lo = each < static_cast<uint32_t>(kUnitChunksMin) ? each : static_cast<uint32_t>(kUnitChunksMin);
+  if (lo < static_cast<uint32_t>(kUnitChunksLow)) lo = static_cast<uint32_t>(kUnitChunksLow);
+  const uint32_t n = want > lo ? want : lo;
+  return n < static_cast<uint32_t>(kUnitChunksMax) ? n : static_cast<uint32_t>(kUnitChunksMax);
+}
+
+// LDS words of a block's tallies, and of its acceptance ratios rounded to 32
+// bits (analog flights with null collisions)
+constexpr int block_words(int ex, int ey, int has_w, int faces, int ratios)
+{
+  return ex * ey * (has_w ? 2 : 1) + (faces ? ex * (ey + 1) : 0) + 2 * (ex + ey) +
+         (ratios ? (ex * ey + 1) / 2 : 0);
+}
+
+struct BlockPlan {
+  int T = 0;                               // blocks of all bands (0: no blocks)
+  int rounds = 0, target = 0;
+  bool faces = false;                      // the LDS has room for y-face tallies
+  size_t lds = 0;                          // bytes of a workgroup's dynamic LDS
+  std::vector<BlockDesc> blk;              // [T + 1] (the last: the number of sampled chunks)
+  std::vector<BlockUnit> units;            // round 0's
+  size_t n_units = 0, n_chunks = 0;        // most units of a round, most output chunks
+};
+
+// The mesh of each of K bands cut into blocks whose tallies fit a workgroup's
+// LDS (the fewest rounds, then the fewest blocks), round 0's units of work for N
+// flights per emitter, and the most that a later round can need.  No blocks
+// beyond kBlocksMax of them or kChunksMax chunks.
+inline BlockPlan plan_block_step(int nx, int ny, int K, uint32_t N, bool has_null, bool faces,
+                                 bool rays, int n_cu, size_t lds_max)
+{
+  auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
+  const int ratios = has_null && !rays;
+  const int words = static_cast<int>((lds_max - kBlockStaticLds) / 8);
+  int nbx = 0, nby = 0;
+  for (int sum = 2; nbx == 0 && sum <= nx + ny; ++sum)
+    for (int x = 1; x < sum; ++x) {
+      const int y = sum - x;
+      if (x > nx || y > ny) continue;
+      if (block_words(cdiv(nx, x), cdiv(ny, y), has_null, faces, ratios) > words) continue;
+      if (nbx == 0 || x * y < nbx * nby) {
+        nbx = x;
+        nby = y;
+      }
+    }
+  const int T1 = nbx * nby;
+  BlockPlan p;
+  if (nbx == 0 || T1 > kBlocksMax / K) return p;
+  const int T = K * T1;
+  p.target = rays ? kBlockTargetEv : kBlockTarget;
+  const double flights = (static_cast<double>(nx) * ny + 2.0 * (nx + ny)) * N * K;
+  // chunks of a unit of round 0
+  const double share = static_cast<double>(
+      unit_chunks(static_cast<uint32_t>(std::min(flights / kChunk + T, 4e9)),
+                  static_cast<uint32_t>(p.target), static_cast<uint32_t>(n_cu)));
+  p.blk.resize(static_cast<size_t>(T) + 1);
+  unsigned long long slab = 0, base = 0;
+  int ex_max = 1, ey_max = 1;
+  for (int k = 0; k < K; ++k)
+    for (int by = 0; by < nby; ++by)
+      for (int bx = 0; bx < nbx; ++bx) {
+        const int t = k * T1 + by * nbx + bx;
+        BlockDesc &d = p.blk[t];
+        d.inst = k;
+        d.x0 = static_cast<int>(static_cast<long long>(nx) * bx / nbx);
+        d.y0 = static_cast<int>(static_cast<long long>(ny) * by / nby);
+        d.ex = static_cast<int>(static_cast<long long>(nx) * (bx + 1) / nbx) - d.x0;
+        d.ey = static_cast<int>(static_cast<long long>(ny) * (by + 1) / nby) - d.y0;
+        ex_max = std::max(ex_max, d.ex);
+        ey_max = std::max(ey_max, d.ey);
+        d.n_e = d.ex * d.ey + (bx == 0 ? d.ey : 0) + (bx == nbx - 1 ? d.ey : 0) +
+                (by == 0 ? d.ex : 0) + (by == nby - 1 ? d.ex : 0);
+        d.nb[0] = bx > 0 ? t - 1 : t;               // (the mesh's edge: never entered)
+        d.nb[1] = bx < nbx - 1 ? t + 1 : t;
+        d.nb[2] = by > 0 ? t - nbx : t;
+        d.nb[3] = by < nby - 1 ? t + nbx : t;
+        const unsigned long long P = static_cast<unsigned long long>(d.n_e) * N;
+        const unsigned long long nc = (P + kChunk - 1) / kChunk;
+        d.base = static_cast<uint32_t>(base);
+        base += nc;
+        if (base >= kChunksMax) return BlockPlan{};
+        const unsigned long long parts =
+            static_cast<unsigned long long>(std::ceil(static_cast<double>(nc) / share));
+        for (unsigned long long i = 0; i < parts; ++i) {
+          BlockUnit u;
+          u.t = t;
+          u.first = static_cast<uint32_t>(nc * i / parts);
+          u.count = static_cast<uint32_t>(nc * (i + 1) / parts) - u.first;
+          u.cap = u.count + kOpenChunks;
+          u.slab = static_cast<uint32_t>(slab);
+          slab += u.cap;
+          p.units.push_back(u);
+        }
+      }
+  p.blk.back().base = static_cast<uint32_t>(base);
+  // most units of a round, and most chunks: at most one chunk per 64 flights
+  // and kOpenChunks partly filled ones per unit of the round that wrote them,
+  // again kOpenChunks per unit of the round that reads them
+  const double full = static_cast<double>(base) + 1.0;
+  const double u_max =
+      std::max({static_cast<double>(p.units.size()), static_cast<double>(p.target + T),
+                (full / kUnitChunksMax + T + 1.0) /
+                    (1.0 - static_cast<double>(kOpenChunks) / kUnitChunksMax)});
+  const double chunks = std::max(static_cast<double>(slab), full + 2.0 * kOpenChunks * (u_max + 1.0));
+  if (chunks >= static_cast<double>(kChunksMax)) return BlockPlan{};
+  p.n_units = static_cast<size_t>(u_max) + 1;
+  p.n_chunks = static_cast<size_t>(chunks) + 1;
+  p.rounds = nbx + nby - 1;
+  p.faces = faces;
+  p.lds = static_cast<size_t>(block_words(ex_max, ey_max, has_null, faces, ratios)) * 8;
+  p.T = T;
+  return p;
 }
 
 }  // namespace iugkp

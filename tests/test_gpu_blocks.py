@@ -139,3 +139,16 @@ def test_forms_of_bands_without_face_tallies(gpu, K, timed):
         assert torch.equal(s.state()[3], ref.state()[3])
     assert ("blocks" in ran) == timed
     assert ref.march_form() == "tiles256"
+
+
+def test_bands_beyond_the_blocks_tables_keep_row_stripes(gpu):
+    """Eighty bands of 560 x 560 cells are more blocks than a launch holds: the
+    bands with long paths run by row stripes, as without blocks."""
+    w = nongray_two_material_2d(n=560, K=80, particles=1)
+    s = gpu.Solver(w, tally_faces=gpu.FACES_EVERY)
+    ref = gpu.Solver(w, tally_faces=gpu.FACES_EVERY, march=1)
+    assert s.step(1) == 0 and ref.step(1) == 0
+    assert s.march_form() == "stripes" and ref.march_form() == "tiles256"
+    ts, tr = s.tallies(), ref.tallies()
+    for k in ts:
+        assert torch.equal(ts[k], tr[k]), k

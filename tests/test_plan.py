@@ -13,6 +13,8 @@ CSRC = os.path.join(ROOT, "paper_2506_09465_amd", "csrc")
 
 SHIM = r"""
 #include <cstdint>
+#include <map>
+#include <random>
 #include "plan.hpp"
 using namespace iugkp;
 extern "C" {
@@ -46,6 +48,99 @@ int quiet(const double *lam, int K, double flights, int T)
   const std::vector<double> b(lam, lam + K);
   return (quiet_blocks(b, flights, T) ? 1 : 0) | (quiet_blocks_first(b, flights) ? 2 : 0);
 }
+
+// out: blocks of all bands, rounds, LDS bytes, round 0's units
+void blocks(int nx, int ny, int K, uint32_t N, int null, int faces, int rays, int64_t *out)
+{
+  const BlockPlan p = plan_block_step(nx, ny, K, N, null != 0, faces != 0, rays != 0, 256, 163840);
+  out[0] = p.T;
+  out[1] = p.rounds;
+  out[2] = static_cast<int64_t>(p.lds);
+  out[3] = static_cast<int64_t>(p.units.size());
+}
+
+// The rounds of a planned step with the kernels' bookkeeping, a share `stay` of
+// each unit's flights ending in it and the rest leaving in uneven shares over
+// the four sides: 0, or the first bound that does not hold.
+int rounds(int nx, int ny, int K, uint32_t N, int null, int faces, int rays, double stay, int seed,
+           int64_t *most)
+{
+  const BlockPlan p = plan_block_step(nx, ny, K, N, null != 0, faces != 0, rays != 0, 256, 163840);
+  if (p.T == 0) return 1;
+  std::mt19937 gen(seed);
+  std::uniform_real_distribution<double> uni(0.0, 1.0);
+  // every cell and wall face in one block, every chunk of a block in one unit
+  int64_t emitters = 0, chunks0 = 0;
+  std::map<int, int64_t> next;
+  for (int t = 0; t < p.T; ++t) {
+    const BlockDesc &d = p.blk[t];
+    emitters += d.n_e;
+    if (d.ex < 1 || d.ey < 1 || d.base != chunks0) return 2;
+    chunks0 += (static_cast<int64_t>(d.n_e) * N + kChunk - 1) / kChunk;
+    if (8 * static_cast<size_t>(block_words(d.ex, d.ey, null, faces, null && !rays)) > p.lds) return 3;
+  }
+  if (p.blk[p.T].base != chunks0) return 4;
+  if (emitters != static_cast<int64_t>(K) * (static_cast<int64_t>(nx) * ny + 2 * (nx + ny))) return 5;
+  if (p.lds + kBlockStaticLds > 163840) return 6;
+  // a unit: its block and its chunks (records each)
+  struct U { int t; std::vector<int> ch; uint32_t slab, cap; };
+  std::vector<U> units;
+  for (const BlockUnit &u : p.units) {
+    const BlockDesc &d = p.blk[u.t];
+    const int64_t P = static_cast<int64_t>(d.n_e) * N;
+    U v{u.t, {}, u.slab, u.cap};
+    if (u.first != next[u.t]) return 7;
+    next[u.t] += u.count;
+    for (uint32_t i = 0; i < u.count; ++i)
+      v.ch.push_back(static_cast<int>(std::min<int64_t>(kChunk, P - static_cast<int64_t>(u.first + i) * kChunk)));
+    units.push_back(v);
+  }
+  most[0] = most[1] = most[2] = 0;
+  for (int r = 0; r < p.rounds && !units.empty(); ++r) {
+    std::map<int, std::vector<int>> in;                   // a block's chunks of the next round
+    if (units.size() > p.n_units) return 10;
+    most[0] = std::max<int64_t>(most[0], units.size());
+    for (const U &u : units) {
+      if (u.ch.size() > kUnitChunksMax || u.ch.empty()) return 11;
+      most[2] = std::max<int64_t>(most[2], u.ch.size());
+      if (static_cast<size_t>(u.slab) + u.cap > p.n_chunks) return 12;
+      most[1] = std::max<int64_t>(most[1], u.slab + u.cap);
+      int64_t n = 0;
+      for (int c : u.ch) n += c;
+      n = static_cast<int64_t>(n * (1.0 - stay));
+      double w[4], sum = 0.0;
+      for (double &x : w) sum += x = std::pow(uni(gen), 6.0);
+      int64_t opened = 0, left = n;
+      for (int d = 0; d < 4; ++d) {
+        const int64_t m = d < 3 ? std::min<int64_t>(left, static_cast<int64_t>(n * w[d] / sum)) : left;
+        left -= m;
+        const int64_t nc = (m + kChunk - 1) / kChunk;
+        if (nc > u.cap || nc > kUnitChunksMax) return 13;
+        opened += nc;
+        const int to = p.blk[u.t].nb[d];
+        for (int64_t i = 0; i < nc; ++i)
+          in[to].push_back(static_cast<int>(std::min<int64_t>(kChunk, m - i * kChunk)));
+      }
+      if (opened > u.cap) return 14;
+    }
+    int64_t total = 0;
+    for (auto &b : in) total += b.second.size();
+    const uint32_t share = unit_chunks(static_cast<uint32_t>(total), p.target, 256);
+    units.clear();
+    uint32_t before = 0;
+    for (auto &b : in) {
+      for (size_t c = 0; c < b.second.size(); c += share) {
+        U v{b.first, {}, 0, 0};
+        v.ch.assign(b.second.begin() + c, b.second.begin() + std::min<size_t>(b.second.size(), c + share));
+        v.slab = before + static_cast<uint32_t>(c + units.size() * kOpenChunks);
+        v.cap = static_cast<uint32_t>(v.ch.size()) + kOpenChunks;
+        units.push_back(v);
+      }
+      before += static_cast<uint32_t>(b.second.size());
+    }
+  }
+  return 0;
+}
 }
 """
 
@@ -67,6 +162,10 @@ def plan(tmp_path_factory):
                            C.c_void_p]
     lib.quiet.restype = C.c_int
     lib.quiet.argtypes = [C.c_void_p, C.c_int, C.c_double, C.c_int]
+    lib.blocks.restype = None
+    lib.blocks.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_void_p]
+    lib.rounds.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_double,
+                           C.c_int, C.c_void_p]
     return lib
 
 
@@ -127,3 +226,29 @@ def test_form_search(plan, cand, default, rounds, times, best):
 def test_blocks_without_face_tallies(plan, lam, flights, blocks, want):
     a = np.array(lam)
     assert plan.quiet(a.ctypes.data, len(lam), flights, blocks * len(lam)) == want
+
+
+@pytest.mark.parametrize("shape", [
+    # nx, ny, bands, flights per emitter, null collisions, face tallies, rays
+    (61, 61, 1, 80, 1, 1, 0), (1, 400, 1, 50, 1, 1, 0), (301, 71, 1, 19, 1, 0, 0),
+    (90, 77, 1, 31, 0, 0, 1), (150, 141, 1, 10, 1, 1, 1), (120, 120, 3, 9, 1, 1, 0),
+    (48, 48, 40, 1, 1, 1, 0), (512, 512, 1, 60, 1, 1, 0), (256, 256, 1, 600, 1, 1, 0),
+])
+def test_block_rounds_stay_in_bounds(plan, shape):
+    """Units, chunks, lists and LDS of every round, wherever the flights go."""
+    for stay, seed in ((0.0, 1), (0.0, 2), (0.3, 3), (0.9, 4)):
+        most = np.zeros(3, np.int64)
+        assert plan.rounds(*shape, stay, seed, most.ctypes.data) == 0
+    if shape[3] == 600:
+        assert most[2] == 256            # (units of the largest size)
+
+
+def test_blocks_beyond_their_tables(plan):
+    """No blocks where they would be more than a launch holds, or their chunks more
+    than a list entry can number."""
+    out = np.zeros(4, np.int64)
+    for args in ((800, 800, 40, 1, 1, 1, 0), (560, 560, 80, 1, 1, 1, 0), (512, 512, 1, 8100, 1, 1, 0)):
+        plan.blocks(*args, out.ctypes.data)
+        assert out[0] == 0
+    plan.blocks(700, 700, 40, 1, 1, 1, 0, out.ctypes.data)
+    assert 0 < out[0] <= 4096
