@@ -45,6 +45,12 @@ int fail(int code, const std::string &msg)
       return fail(IUGKP_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(_e));   \
   } while (0)
 
+using iugkp::kFormBlocks;
+using iugkp::kFormPieces;
+using iugkp::kFormStripes;
+using iugkp::kFormTiles256;
+using iugkp::kFormTiles512;
+
 constexpr int kCgGroupMax = 256;             // workgroups of a group, at most one per CU
 constexpr int kCgGridMax = 64;               // workgroups of one CG group (barrier arrivals)
 // The banded multigrid CG of a single solve runs on a workgroup per two rows of
@@ -254,6 +260,8 @@ struct InstHost {
   int stripe_R = 0, stripe_S = 0, stripe_C = 0;
   size_t stripe_lds = 0;
   iugkp::BlockPlan blocks;           // the handle's domain blocks (all bands)
+  int band_form = 0;                 // frequency bands with blocks: bands_form,
+  bool band_timed = false;           // and whether the forms are timed
   double mean_tau = 1.0;             // mean relaxation time over the smallest
   int stripe_pref = 0;               // the planner's choice (stripes set up for a search too)
   // the persistent scheme's row-stripe face pass (rows per stripe, stripes,
@@ -928,11 +936,14 @@ int plan_gray_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_
 // half the domain's height (and 7 cells): a band with shorter ones has long
 // chains of null collisions wherever its relaxation time is above the minimum,
 // which the tile march handles better (march 1 keeps every band on tiles)
+bool stripe_paths(const iugkp_problem *p, double lam)
+{
+  return lam >= kStripeMinCells * std::min(p->dx, p->dy) && lam >= 0.5 * p->ny * p->dy;
+}
 int plan_band_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, InstHost &ih)
 {
   if (p->dim != 2 || o->tally_faces == IUGKP_FACES_OFF || o->march == 1 ||
-      o->estimator != IUGKP_EST_ANALOG ||
-      ih.d.lam_min < kStripeMinCells * std::min(p->dx, p->dy) || ih.d.lam_min < 0.5 * p->ny * p->dy)
+      o->estimator != IUGKP_EST_ANALOG || !stripe_paths(p, ih.d.lam_min))
     return IUGKP_OK;
   return plan_stripes(ih, s, false, true);
 }
@@ -1363,7 +1374,15 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
   if ((rc = plan_blocks(p, o, K, static_cast<uint32_t>(N), any_null, static_cast<double>(K) * ne * N,
                         far, ih0.blocks)))
     return rc;
-  const bool blocks = ih0.blocks.T > 0;
+  bool stripes = true;               // (beside blocks: for all bands or none)
+  if (ih0.blocks.T > 0) {
+    const double all = static_cast<double>(K) * ne * N;
+    bool all_long = true;
+    for (int k = 0; k < K; ++k) all_long = all_long && stripe_paths(p, lam[k]);
+    ih0.band_form = iugkp::bands_form(all_long, all, ih0.blocks.T, ih0.blocks.rounds);
+    ih0.band_timed = iugkp::bands_timed(all, ih0.blocks.T);
+    stripes = all_long && ih0.band_timed;
+  }
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
   int ok = 1;
   unsigned long long acc = 0, wall_acc = 0;
@@ -1415,7 +1434,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.Gs = nullptr;
     plan_tiles(ih);
     if ((rc = split_tiles(ih, K))) return rc;
-    if (!blocks && (rc = plan_band_stripes(p, o, s, ih))) return rc;
+    if (stripes && (rc = plan_band_stripes(p, o, s, ih))) return rc;
     double *dratio = nullptr, *dshare = nullptr;
     ALLOC(ih, dratio, nc);
     ALLOC(ih, dshare, nc);
@@ -1776,12 +1795,6 @@ int enqueue_cg(const InstHost &ih, const double *b, double *x, DevScalars *sc, h
   return IUGKP_OK;
 }
 
-using iugkp::kFormBlocks;
-using iugkp::kFormPieces;
-using iugkp::kFormStripes;
-using iugkp::kFormTiles256;
-using iugkp::kFormTiles512;
-
 // The class a measured choice holds for: the mesh, the particles per emitter,
 // null collisions, and the free path in cells to half an octave.
 using FormKey = std::vector<int>;
@@ -1915,10 +1928,11 @@ int enqueue_iteration(iugkp_handle *h, int faces)
   iugkp::prepare_kernel<<<dim3(cdiv(nprep, 256), K), 256, 0, s>>>(h->d_inst, faces, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(h->ev[0], s));
-  // (without face tallies the search waits until most emitters fly: a solve's
-  // first iterations, from cold cells, are no measure)
+  // (the search waits until most emitters fly: a solve's first iterations, from
+  // cold cells, are no measure; a gray one with face tallies, whose choice was
+  // there before, does not)
   const int form = h->forms[h->form_faces].pick(
-      faces || 2.0 * static_cast<double>(h->st.flights) >=
+      (faces && K == 1) || 2.0 * static_cast<double>(h->st.flights) >=
                    static_cast<double>(K) * m.n_emit * static_cast<double>(ih.d.N));
   h->form_ran = form;
   if (form == kFormBlocks) {
@@ -2116,7 +2130,7 @@ int setup_blocks(iugkp_handle *h)
 // The forms a handle's iterations run in: the planner's choice, and what a 2D
 // gray analog solve with the automatic march and the default block size times
 // against it in its face-tallied iterations, any analog handle with blocks in
-// the others.
+// the others, and bands with few flights for their blocks in both.
 void plan_forms(iugkp_handle *h)
 {
   const InstHost &ih = h->ih;
@@ -2145,11 +2159,20 @@ void plan_forms(iugkp_handle *h)
     }
   }
   if (ih.d.estimator || h->bh.K > 1) {
-    const bool more = h->bh.K > 1 ? !h->stripe_bands.empty() : stripes;
     // (blocks of a handle without face tallies have no room for those that
     // iugkp_step_faces asks for)
     if (blocks && h->blocks.faces) on.def = kFormBlocks;
-    else if (more) on.def = kFormStripes;
+    else if (stripes || !h->stripe_bands.empty()) on.def = kFormStripes;
+    if (h->bh.K > 1 && on.def == kFormBlocks) {
+      const bool all = h->stripe_bands.size() == static_cast<size_t>(h->bh.K);
+      if (ih.band_form != kFormStripes || all) on.def = ih.band_form;
+      if (ih.band_timed) {
+        on.cand = {kFormTiles256, kFormBlocks};
+        if (all) on.cand.push_back(kFormStripes);
+        on.rounds = 3;
+        known(1);
+      }
+    }
     return;
   }
   const bool fit = blocks && h->blocks.faces;
@@ -2170,6 +2193,12 @@ void plan_forms(iugkp_handle *h)
   if (stripes && !null) on.cand.push_back(kFormPieces);
   if (fit) on.cand.push_back(kFormBlocks);
   known(1);
+}
+
+// a candidate's form that has no place among the first three (iugkp_march_tuning)
+int fourth_form(const iugkp_handle *h)
+{
+  return h->ih.d.has_null || h->bh.K > 1 ? kFormBlocks : kFormPieces;
 }
 
 }  // namespace
@@ -2493,7 +2522,7 @@ int iugkp_march_tuning(iugkp_handle *h, int *form, float *ms)
   if (form) *form = f.kept();
   if (ms) {
     for (int i = 0; i < kFormPieces; ++i) ms[i] = f.ms[i];
-    ms[3] = f.ms[h->ih.d.has_null ? kFormBlocks : kFormPieces];
+    ms[3] = f.ms[fourth_form(h)];
   }
   return IUGKP_OK;
 }
@@ -2502,7 +2531,7 @@ int iugkp_march_form(iugkp_handle *h, int *last, int *fourth)
 {
   if (!h) return fail(IUGKP_E_INVALID_ARG, "handle is NULL");
   if (last) *last = h->form_ran;
-  if (fourth) *fourth = h->ih.d.has_null ? kFormBlocks : kFormPieces;
+  if (fourth) *fourth = fourth_form(h);
   return IUGKP_OK;
 }
 

@@ -152,3 +152,37 @@ def test_bands_beyond_the_blocks_tables_keep_row_stripes(gpu):
     ts, tr = s.tallies(), ref.tallies()
     for k in ts:
         assert torch.equal(ts[k], tr[k]), k
+
+
+def _bands_2d(nx, ny, lam, ratio, per):
+    """Bands of free paths lam (in cells; right half, ratio times that left)."""
+    K = len(lam)
+    w = nongray_two_material_2d(n=ny, K=K, particles=per * K * (nx * ny + 2 * (nx + ny)))
+    w.nx, w.dx = nx, w.dy
+    left = np.tile(np.arange(nx) < nx // 2, ny)
+    w.tau = np.concatenate([np.where(left, v * ratio, v) * w.dx / g for v, g in zip(lam, w.band_vg)])
+    w.wall_T = np.concatenate([np.full(2 * ny + nx, 0.99), np.full(nx, 1.01)])
+    w.source = None
+    return w
+
+
+@pytest.mark.parametrize("nx,ny,lam,per,first,timed", [
+    # (long paths, many rounds of few flights; long paths, few rounds)
+    (376, 97, (2734.0, 242.0), 10, "stripes", {"tiles256", "blocks", "stripes"}),
+    (96, 90, (700.0, 80.0), 20, "blocks", {"tiles256", "blocks", "stripes"}),
+    (43, 215, (93.0, 40.0, 20.0, 10.0, 5.0, 2.0), 3, "tiles256", {"tiles256", "blocks"}),
+    (60, 61, (90.0, 10.0), 60, "blocks", set()),
+])
+def test_form_of_bands_with_face_tallies(gpu, nx, ny, lam, per, first, timed):
+    w = _bands_2d(nx, ny, lam, 20.0, per)
+    kw = dict(tally_faces=gpu.FACES_EVERY, T_init=seeded_temperature(nx * ny))
+    s, ref = gpu.Solver(w, **kw), gpu.Solver(w, march=1, **kw)
+    ran = []
+    for _ in range(2 + 3 * len(timed)):
+        assert s.step(1) == 0 and ref.step(1) == 0
+        ran.append(s.march_form())
+        ts, tr = s.tallies(), ref.tallies()
+        for k in ts:
+            assert torch.equal(ts[k], tr[k]), (ran, k)
+    assert ran[0] == first and set(ran[1:]) == (timed or {first})
+    assert {k for k, v in s.march_tuning()[1].items() if v is not None} == timed

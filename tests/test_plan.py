@@ -49,6 +49,8 @@ int quiet(const double *lam, int K, double flights, int T)
   return (quiet_blocks(b, flights, T) ? 1 : 0) | (quiet_blocks_first(b, flights) ? 2 : 0);
 }
 
+int bands(int stripes, double flights, int T, int rounds) { return bands_form(stripes != 0, flights, T, rounds); }
+
 // out: blocks of all bands, rounds, LDS bytes, round 0's units
 void blocks(int nx, int ny, int K, uint32_t N, int null, int faces, int rays, int64_t *out)
 {
@@ -162,6 +164,8 @@ def plan(tmp_path_factory):
                            C.c_void_p]
     lib.quiet.restype = C.c_int
     lib.quiet.argtypes = [C.c_void_p, C.c_int, C.c_double, C.c_int]
+    lib.bands.restype = C.c_int
+    lib.bands.argtypes = [C.c_int, C.c_double, C.c_int, C.c_int]
     lib.blocks.restype = None
     lib.blocks.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_void_p]
     lib.rounds.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_double,
@@ -226,6 +230,14 @@ def test_form_search(plan, cand, default, rounds, times, best):
 def test_blocks_without_face_tallies(plan, lam, flights, blocks, want):
     a = np.array(lam)
     assert plan.quiet(a.ctypes.data, len(lam), flights, blocks * len(lam)) == want
+
+
+@pytest.mark.parametrize("stripes,flights,blocks,rounds,form", [
+    (1, 7.5e5, 16, 5, 2), (1, 3e6, 16, 5, 4), (1, 6e4, 2, 1, 4), (1, 7e4, 4, 2, 0),
+    (0, 2.3e5, 16, 2, 0), (0, 5e7, 1440, 11, 4), (0, 8.6e5, 56, 10, 4), (0, 4e5, 8, 1, 4),
+])
+def test_form_of_bands_with_face_tallies(plan, stripes, flights, blocks, rounds, form):
+    assert plan.bands(stripes, flights, blocks, rounds) == form
 
 
 @pytest.mark.parametrize("shape", [
