@@ -100,6 +100,7 @@ constexpr int kLdsWallsMax = 1024;
 // against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
 // (Iterations without face tallies: quiet_blocks.)
 constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
+constexpr size_t kRecordsFree = size_t{256} << 20;   // records below this: the free memory is not asked for
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -237,6 +238,7 @@ struct InstHost {
   std::vector<TileDesc> tiles;       // inst field filled by the owner
   size_t lds_bytes = 0;              // march window
   Arena mem, *shared = nullptr;      // its device memory, or its batch's
+  Arena stripe_mem;                  // the row stripes' records
   double *tau = nullptr, *Dx = nullptr, *Dy = nullptr, *gx = nullptr, *gy = nullptr,
          *diag = nullptr;
   double *out_T = nullptr, *out_qx = nullptr, *out_qy = nullptr;
@@ -275,7 +277,11 @@ struct InstHost {
   {
     return (shared ? shared : &mem)->alloc(p, n);
   }
-  void release() { mem.release(); }
+  void release()
+  {
+    mem.release();
+    stripe_mem.release();
+  }
 };
 
 int check_problem(const iugkp_problem *p)
@@ -884,9 +890,10 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
       for (size_t i = 0; i < cap.size(); ++i) base[i + 1] = base[i] + static_cast<uint32_t>(cap[i]);
       unsigned char *r = nullptr;
       uint32_t *db = nullptr;
-      recs = ih.alloc(&r, np * rb) == hipSuccess && ih.alloc(&ih.rec.key, np) == hipSuccess &&
-             ih.alloc(&ih.rec.cnt, 2 * cap.size()) == hipSuccess &&
-             ih.alloc(&db, base.size()) == hipSuccess;
+      Arena &mem = ih.stripe_mem;
+      recs = mem.alloc(&r, np * rb) == hipSuccess && mem.alloc(&ih.rec.key, np) == hipSuccess &&
+             mem.alloc(&ih.rec.cnt, 2 * cap.size()) == hipSuccess &&
+             mem.alloc(&db, base.size()) == hipSuccess;
       if (recs && base.back() != np) return fail(IUGKP_E_DEVICE, "stripe bins do not cover the particles");
       if (recs) HIP_TRY(hipMemcpyAsync(db, base.data(), base.size() * sizeof(uint32_t),
                                        hipMemcpyHostToDevice, s));
@@ -895,7 +902,10 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
       ih.rec.R = R;
       ih.rec.S = S;
       ih.rec.K = K;
-      if (!recs) (void)hipGetLastError();
+      if (!recs) {
+        (void)hipGetLastError();
+        mem.release();
+      }
     }
     if (per_cu >= 1 && recs) {
       ih.stripe_R = R;
@@ -948,12 +958,14 @@ int plan_band_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_
   return plan_stripes(ih, s, false, true);
 }
 
-// The domain blocks of a handle of K bands with N flights per emitter: 2D,
-// enough expected-value rays or far flights with null collisions
-// (kBlockMinFlights), and a mesh that can be cut.
-int plan_blocks(const iugkp_problem *p, const iugkp_options *o, int K, uint32_t N, bool has_null,
-                double flights, double far, iugkp::BlockPlan &out)
+// The domain blocks of a handle of bands with free paths lam and N flights per
+// emitter: 2D, enough expected-value rays or far flights with null collisions
+// (kBlockMinFlights), iterations that may run by them, a mesh that can be cut,
+// and room for the records.
+int plan_blocks(const iugkp_problem *p, const iugkp_options *o, const std::vector<double> &lam,
+                uint32_t N, bool has_null, double flights, double far, iugkp::BlockPlan &out)
 {
+  const int K = static_cast<int>(lam.size());
   out = iugkp::BlockPlan{};
   if (p->dim != 2 || o->scheme != IUGKP_SCHEME_EMITTERS || o->march != 0 || o->block_size != 0 ||
       p->nx > 0xffff || p->ny > 0xffff)
@@ -966,6 +978,18 @@ int plan_blocks(const iugkp_problem *p, const iugkp_options *o, int K, uint32_t 
   HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
   out = iugkp::plan_block_step(p->nx, p->ny, K, N, has_null, o->tally_faces != IUGKP_FACES_OFF, rays,
                                n_cu, static_cast<size_t>(lds_max));
+  if (out.T == 0) return IUGKP_OK;
+  std::vector<double> cells;
+  for (double l : lam) cells.push_back(l / std::min(p->dx, p->dy));
+  if (!rays && !out.faces && !iugkp::quiet_blocks(cells, flights / K, out.T)) {
+    out = iugkp::BlockPlan{};
+    return IUGKP_OK;
+  }
+  if (out.record_bytes() > kRecordsFree) {
+    size_t free_bytes = 0, total = 0;
+    HIP_TRY(hipMemGetInfo(&free_bytes, &total));
+    if (!iugkp::records_fit(out, free_bytes)) out = iugkp::BlockPlan{};
+  }
   return IUGKP_OK;
 }
 
@@ -1053,7 +1077,9 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
     const double n = static_cast<double>(ne) * d.N;
     ih.mean_tau = tsum / tmin;
     const bool far = flights_go_far(d.has_null, ih.mean_tau, d.lam_min, p->dx, p->dy);
-    if (multi_cg && (rc = plan_blocks(p, o, 1, d.N, d.has_null, n, far ? n : 0.0, ih.blocks))) return rc;
+    if (multi_cg &&
+        (rc = plan_blocks(p, o, {d.lam_min}, d.N, d.has_null, n, far ? n : 0.0, ih.blocks)))
+      return rc;
   }
   plan_tiles(ih, kTileX, (multi_cg && d.has_null) ? kWindowHaloNull : kWindowHalo);
   if (multi_cg && (rc = split_tiles(ih, 1))) return rc;
@@ -1371,7 +1397,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     if (flights_go_far(has_null[k], mean[k], lam[k], p->dx, p->dy)) far += static_cast<double>(ne) * N;
   bool any_null = false;
   for (int k = 0; k < K; ++k) any_null = any_null || has_null[k];
-  if ((rc = plan_blocks(p, o, K, static_cast<uint32_t>(N), any_null, static_cast<double>(K) * ne * N,
+  if ((rc = plan_blocks(p, o, lam, static_cast<uint32_t>(N), any_null, static_cast<double>(K) * ne * N,
                         far, ih0.blocks)))
     return rc;
   bool stripes = true;               // (beside blocks: for all bands or none)
@@ -1641,7 +1667,6 @@ int upload_inst(const InstHost &ih, int inst_index, Inst *d_inst, TileDesc *d_ti
 struct BlockHost {
   iugkp::BlockRun run{};
   int rounds = 0, grid = 0;
-  bool faces = false;              // the LDS has room for y-face tallies
   size_t lds = 0, plan_lds = 0;
   std::vector<void *> allocs;
   void release()
@@ -1826,14 +1851,36 @@ FormKey search_key(const iugkp_handle *h, int faces)
   return k;
 }
 
+// The memory of forms that no iteration of the handle takes any more, once its
+// forms with face tallies are known (one that tallies them every iteration: what
+// it might run by without them is tiles then, if it has not done so yet).
+void release_forms(iugkp_handle *h)
+{
+  iugkp::FormSearch &off = h->forms[0], &on = h->forms[1];
+  if (on.kept() < 0) return;
+  if (h->ih.d.faces_each && on.kept() != kFormBlocks && !off.warm && off.form < 0) {
+    off.cand.clear();
+    off.def = kFormTiles256;
+  }
+  if (h->blocks.rounds > 0 && !on.may_run(kFormBlocks) && !off.may_run(kFormBlocks)) h->blocks.release();
+  if (h->bh.K == 1 && !h->ih.d.estimator && h->ih.stripe_R > 0 && !on.may_run(kFormStripes) &&
+      !on.may_run(kFormPieces)) {
+    h->ih.stripe_mem.release();
+    h->ih.stripe_R = 0;
+  }
+}
+
 // after an iteration: its particle-step time for the candidate it measured;
 // the choice is kept for later handles of the class
 void record_form(iugkp_handle *h, float ms)
 {
   iugkp::FormSearch &f = h->forms[h->form_faces];
   if (!f.record(ms)) return;
-  std::lock_guard<std::mutex> lock(g_form_mu);
-  g_form_choice[search_key(h, h->form_faces)] = f.form;
+  {
+    std::lock_guard<std::mutex> lock(g_form_mu);
+    g_form_choice[search_key(h, h->form_faces)] = f.form;
+  }
+  release_forms(h);
 }
 
 // The row-stripe particle step of one instance (ih, its descriptor at
@@ -2116,7 +2163,6 @@ int setup_blocks(iugkp_handle *h)
   r.n_units0 = static_cast<uint32_t>(p.units.size());
   b.grid = n_cu;
   b.rounds = p.rounds;
-  b.faces = p.faces;
   b.lds = p.lds;
   b.plan_lds = static_cast<size_t>(p.T) * sizeof(unsigned long long);
   HIP_TRY(hipMemcpyAsync(d_blk, p.blk.data(), p.blk.size() * sizeof(p.blk[0]), hipMemcpyHostToDevice,
@@ -2135,8 +2181,10 @@ void plan_forms(iugkp_handle *h)
 {
   const InstHost &ih = h->ih;
   const Mesh &m = ih.d.m;
-  const bool blocks = h->blocks.rounds > 0, stripes = ih.stripe_R > 0, null = ih.d.has_null != 0;
+  const bool blocks = ih.blocks.T > 0, stripes = ih.stripe_R > 0, null = ih.d.has_null != 0;
   iugkp::FormSearch &off = h->forms[0], &on = h->forms[1];
+  off = iugkp::FormSearch{};
+  on = iugkp::FormSearch{};
   auto known = [&](int faces) {
     iugkp::FormSearch &f = h->forms[faces];
     std::lock_guard<std::mutex> lock(g_form_mu);
@@ -2149,7 +2197,7 @@ void plan_forms(iugkp_handle *h)
     std::vector<double> lam;
     for (int k = 0; k < h->bh.K; ++k) lam.push_back(band_of(h, k).d.lam_min / std::min(m.dx, m.dy));
     const double flights = static_cast<double>(m.n_emit) * ih.d.N;
-    if (iugkp::quiet_blocks(lam, flights, h->blocks.run.T)) {
+    if (iugkp::quiet_blocks(lam, flights, ih.blocks.T)) {
       off.def = iugkp::quiet_blocks_first(lam, flights) ? kFormBlocks : kFormTiles256;
       off.cand = {kFormTiles256, kFormBlocks};
       // (an iteration's longest chain of null collisions sets the tiles' time:
@@ -2161,7 +2209,7 @@ void plan_forms(iugkp_handle *h)
   if (ih.d.estimator || h->bh.K > 1) {
     // (blocks of a handle without face tallies have no room for those that
     // iugkp_step_faces asks for)
-    if (blocks && h->blocks.faces) on.def = kFormBlocks;
+    if (blocks && ih.blocks.faces) on.def = kFormBlocks;
     else if (stripes || !h->stripe_bands.empty()) on.def = kFormStripes;
     if (h->bh.K > 1 && on.def == kFormBlocks) {
       const bool all = h->stripe_bands.size() == static_cast<size_t>(h->bh.K);
@@ -2175,7 +2223,7 @@ void plan_forms(iugkp_handle *h)
     }
     return;
   }
-  const bool fit = blocks && h->blocks.faces;
+  const bool fit = blocks && ih.blocks.faces;
   if (!stripes && !fit) return;
   // flights that cross the mesh mostly in one flight: stripes (two materials,
   // 324 x 324 cells, 4 particles per emitter, path 744 cells 0.15 ms against 0.65
@@ -2231,15 +2279,24 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
   }
   const int K = h->bh.K;
   h->block = options->block_size ? options->block_size : 256;
+  auto choose = [&] {
+    h->stripe_bands.clear();
+    for (int k = 0; bands && k < K; ++k)
+      if (band_of(h, k).stripe_R > 0) h->stripe_bands.push_back(k);
+    plan_forms(h);
+    release_forms(h);
+  };
+  choose();
   // by domain blocks where planned; without the memory as without them
-  if (h->ih.blocks.T > 0 && (rc = setup_blocks(h)) == IUGKP_E_NOMEM) {
+  if ((h->forms[0].may_run(kFormBlocks) || h->forms[1].may_run(kFormBlocks)) &&
+      (rc = setup_blocks(h)) == IUGKP_E_NOMEM) {
     h->ih.blocks = iugkp::BlockPlan{};
+    rc = IUGKP_OK;
     if (!bands && h->ih.stripe_R == 0) rc = plan_gray_stripes(problem, options, h->stream, h->ih);
-    if (bands) {
-      rc = plan_band_stripes(problem, options, h->stream, h->ih);
-      for (size_t k = 0; k < h->xb.size() && !rc; ++k)
-        rc = plan_band_stripes(problem, options, h->stream, h->xb[k]);
-    }
+    for (int k = 0; bands && k < K && !rc; ++k)
+      if (band_of(h, k).stripe_R == 0)
+        rc = plan_band_stripes(problem, options, h->stream, k == 0 ? h->ih : h->xb[k - 1]);
+    choose();
   }
   if (rc) {
     free_handle(h);
@@ -2249,9 +2306,7 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
   for (int k = 0; k < K; ++k) {
     h->n_tiles += static_cast<int>(band_of(h, k).tiles.size());
     h->lds = std::max(h->lds, band_of(h, k).lds_bytes);
-    if (bands && band_of(h, k).stripe_R > 0) h->stripe_bands.push_back(k);
   }
-  plan_forms(h);
   if (hipMalloc(reinterpret_cast<void **>(&h->d_inst), K * sizeof(Inst)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void **>(&h->d_tiles), h->n_tiles * sizeof(TileDesc)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void **>(&h->hsc), sizeof(DevScalars)) != hipSuccess) {

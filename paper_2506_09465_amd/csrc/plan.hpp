@@ -112,6 +112,11 @@ struct FormSearch {
   }
   // the form kept, or -1 while it is searched
   int kept() const { return form >= 0 ? form : cand.empty() ? def : -1; }
+  // whether a later iteration may run in form f
+  bool may_run(int f) const
+  {
+    return kept() >= 0 ? kept() == f : def == f || std::find(cand.begin(), cand.end(), f) != cand.end();
+  }
 };
 
 // Iterations without face tallies: the tile march resolves long segments in
@@ -225,7 +230,17 @@ struct BlockPlan {
   std::vector<BlockDesc> blk;              // [T + 1] (the last: the number of sampled chunks)
   std::vector<BlockUnit> units;            // round 0's
   size_t n_units = 0, n_chunks = 0;        // most units of a round, most output chunks
+  // device memory of the records, which is nearly all of it
+  size_t record_bytes() const { return (rounds > 1 ? 2 : 1) * n_chunks * (kChunk * kRecBytes); }
 };
+
+// The records (128 bytes a flight) may take an eighth of the device's free
+// memory: they stay for the handle's life beside its other arrays, other
+// handles and the caller's own.
+inline bool records_fit(const BlockPlan &p, size_t free_bytes)
+{
+  return p.record_bytes() <= free_bytes / 8;
+}
 
 // The mesh of each of K bands cut into blocks whose tallies fit a workgroup's
 // LDS (the fewest rounds, then the fewest blocks), round 0's units of work for N

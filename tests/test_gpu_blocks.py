@@ -186,3 +186,34 @@ def test_form_of_bands_with_face_tallies(gpu, nx, ny, lam, per, first, timed):
             assert torch.equal(ts[k], tr[k]), (ran, k)
     assert ran[0] == first and set(ran[1:]) == (timed or {first})
     assert {k for k, v in s.march_tuning()[1].items() if v is not None} == timed
+
+
+def _free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_records_are_held_only_while_a_form_needs_them(gpu):
+    """Two materials, 1e6 flights: 128 MB of block records, 84 MB of stripe records.
+    None where no iteration runs by blocks; only the kept form's after a search."""
+    def held(steps, n=140, **kw):
+        w = two_material_2d(n=n, kn_right=kw.pop("kn"), ratio=30.0, particles=1_000_000)
+        kw = dict(dict(T_init=seeded_temperature(w.n_cells)), **kw)
+        before = _free()
+        s = gpu.Solver(w, **kw)
+        for _ in range(steps):
+            assert s.step(1) == 0
+        mb = (before - _free()) / 2 ** 20
+        form = s.march_form()
+        s.close()
+        return mb, form
+
+    held(1, kn=0.3, tally_faces=gpu.FACES_EVERY)                        # (first launches)
+    mb, form = held(1, kn=0.3, tally_faces=gpu.FACES_OFF)               # paths of 42 cells: tiles
+    assert form == "tiles256" and mb < 40
+    mb, _ = held(1, kn=0.3, tally_faces=gpu.FACES_EVERY, n=141)         # searching
+    assert mb > 190
+    mb, form = held(6, kn=0.3, tally_faces=gpu.FACES_EVERY, n=142)      # settled
+    assert mb < {"blocks": 170, "stripes": 125, "tiles512": 40}[form]
+    mb, again = held(1, kn=0.3, tally_faces=gpu.FACES_EVERY, n=142)     # known from the start
+    assert again == form and mb < {"blocks": 170, "stripes": 125, "tiles512": 40}[form]

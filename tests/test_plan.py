@@ -49,6 +49,14 @@ int quiet(const double *lam, int K, double flights, int T)
   return (quiet_blocks(b, flights, T) ? 1 : 0) | (quiet_blocks_first(b, flights) ? 2 : 0);
 }
 
+// record bytes of a step, and whether they fit this much free memory
+int64_t records(int nx, int ny, int K, uint32_t N, int64_t free_bytes, int *fit)
+{
+  const BlockPlan p = plan_block_step(nx, ny, K, N, true, true, false, 256, 163840);
+  *fit = records_fit(p, static_cast<size_t>(free_bytes));
+  return static_cast<int64_t>(p.record_bytes());
+}
+
 int bands(int stripes, double flights, int T, int rounds) { return bands_form(stripes != 0, flights, T, rounds); }
 
 // out: blocks of all bands, rounds, LDS bytes, round 0's units
@@ -164,6 +172,8 @@ def plan(tmp_path_factory):
                            C.c_void_p]
     lib.quiet.restype = C.c_int
     lib.quiet.argtypes = [C.c_void_p, C.c_int, C.c_double, C.c_int]
+    lib.records.restype = C.c_int64
+    lib.records.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int64, C.POINTER(C.c_int)]
     lib.bands.restype = C.c_int
     lib.bands.argtypes = [C.c_int, C.c_double, C.c_int, C.c_int]
     lib.blocks.restype = None
@@ -264,3 +274,14 @@ def test_blocks_beyond_their_tables(plan):
         assert out[0] == 0
     plan.blocks(700, 700, 40, 1, 1, 1, 0, out.ctypes.data)
     assert 0 < out[0] <= 4096
+
+
+def test_block_records_leave_room(plan):
+    """About 128 bytes a flight; a step whose records would take more than an
+    eighth of the free memory has no blocks (1e9 flights on an empty 288 GB)."""
+    fit = C.c_int(0)
+    ne = 512 * 512 + 4 * 512
+    for N, free, want in ((190, 288 << 30, 1), (3800, 288 << 30, 0), (190, 40 << 30, 0)):
+        b = plan.records(512, 512, 1, N, free, C.byref(fit))
+        assert 1.0 <= b / (128.0 * ne * N) < 1.1
+        assert fit.value == want == (b <= free // 8)
