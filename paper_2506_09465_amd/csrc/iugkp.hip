@@ -100,6 +100,7 @@ constexpr int kLdsWallsMax = 1024;
 // against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
 // (Iterations without face tallies: quiet_blocks.)
 constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
+constexpr size_t kCheapBytes = size_t{32} << 20;
 constexpr size_t kRecordsFree = size_t{256} << 20;   // records below this: the free memory is not asked for
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
@@ -238,7 +239,8 @@ struct InstHost {
   std::vector<TileDesc> tiles;       // inst field filled by the owner
   size_t lds_bytes = 0;              // march window
   Arena mem, *shared = nullptr;      // its device memory, or its batch's
-  Arena stripe_mem;                  // the row stripes' records
+  Arena stripe_mem;                  // the row stripes' records,
+  std::vector<uint32_t> stripe_base; // and their bins' first ones
   double *tau = nullptr, *Dx = nullptr, *Dy = nullptr, *gx = nullptr, *gy = nullptr,
          *diag = nullptr;
   double *out_T = nullptr, *out_qx = nullptr, *out_qy = nullptr;
@@ -816,7 +818,7 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
 // analog particle step the records and their bins (ih.stripe_*, ih.rec);
 // stripe_R stays 0 where they do not fit (tiles are used).  pref: the
 // planner's choice for the form search.
-int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
+int plan_stripes(InstHost &ih, bool ev, bool pref)
 {
   Inst &d = ih.d;
   const Mesh &m = d.m;
@@ -859,7 +861,6 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
                 np > 0xffffffffull))
       recs = false;   // (16-bit rows and columns, 32-bit slots)
     else if (!ev) {
-      const size_t rb = d.has_null ? sizeof(iugkp::PRecN) : sizeof(iugkp::PRec);
       const int K = std::max(1, std::min(32, iugkp::kStripeSegMax / (S + 1)));
       const long long per_block = static_cast<long long>(iugkp::kPresampleBlock) * iugkp::kPresamplePer;
       const long long nblk = (static_cast<long long>(np) + per_block - 1) / per_block;
@@ -886,26 +887,13 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
           p += e1 - e0;
         }
       }
-      std::vector<uint32_t> base(static_cast<size_t>(S) * K + 1, 0);
+      std::vector<uint32_t> &base = ih.stripe_base;
+      base.assign(static_cast<size_t>(S) * K + 1, 0);
       for (size_t i = 0; i < cap.size(); ++i) base[i + 1] = base[i] + static_cast<uint32_t>(cap[i]);
-      unsigned char *r = nullptr;
-      uint32_t *db = nullptr;
-      Arena &mem = ih.stripe_mem;
-      recs = mem.alloc(&r, np * rb) == hipSuccess && mem.alloc(&ih.rec.key, np) == hipSuccess &&
-             mem.alloc(&ih.rec.cnt, 2 * cap.size()) == hipSuccess &&
-             mem.alloc(&db, base.size()) == hipSuccess;
-      if (recs && base.back() != np) return fail(IUGKP_E_DEVICE, "stripe bins do not cover the particles");
-      if (recs) HIP_TRY(hipMemcpyAsync(db, base.data(), base.size() * sizeof(uint32_t),
-                                       hipMemcpyHostToDevice, s));
-      ih.rec.r = r;
-      ih.rec.base = db;
+      if (base.back() != np) return fail(IUGKP_E_DEVICE, "stripe bins do not cover the particles");
       ih.rec.R = R;
       ih.rec.S = S;
       ih.rec.K = K;
-      if (!recs) {
-        (void)hipGetLastError();
-        mem.release();
-      }
     }
     if (per_cu >= 1 && recs) {
       ih.stripe_R = R;
@@ -918,6 +906,39 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
   return IUGKP_OK;
 }
 
+// The records of planned stripes (rays have none); without the memory no
+// stripes (tiles are used).
+int setup_stripes(InstHost &ih, hipStream_t s)
+{
+  if (ih.stripe_R == 0 || ih.d.estimator) return IUGKP_OK;
+  const size_t np = static_cast<size_t>(ih.d.m.n_emit) * static_cast<size_t>(ih.d.N);
+  unsigned char *r = nullptr;
+  uint32_t *db = nullptr;
+  Arena &mem = ih.stripe_mem;
+  if (mem.alloc(&r, np * (ih.d.has_null ? sizeof(iugkp::PRecN) : sizeof(iugkp::PRec))) != hipSuccess ||
+      mem.alloc(&ih.rec.key, np) != hipSuccess ||
+      mem.alloc(&ih.rec.cnt, 2 * static_cast<size_t>(ih.rec.S) * ih.rec.K) != hipSuccess ||
+      mem.alloc(&db, ih.stripe_base.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    mem.release();
+    ih.stripe_R = 0;
+    return IUGKP_OK;
+  }
+  HIP_TRY(hipMemcpyAsync(db, ih.stripe_base.data(), ih.stripe_base.size() * sizeof(uint32_t),
+                         hipMemcpyHostToDevice, s));
+  ih.rec.r = r;
+  ih.rec.base = db;
+  return IUGKP_OK;
+}
+
+// march 2 and 3 are refused without stripes
+int stripes_asked(const iugkp_options *o, const InstHost &ih)
+{
+  if (o->march >= 2 && ih.stripe_R == 0)
+    return fail(IUGKP_E_INVALID_ARG, "row stripes do not fit this mesh");
+  return IUGKP_OK;
+}
+
 // Row stripes of a gray single solve: on request (march 2 or 3; expected-value
 // rays only so: every stripe follows a ray from its start, and that re-walk
 // costs more than the tile kernel's global atomics on the 256^2 cavity), or
@@ -926,7 +947,7 @@ int plan_stripes(InstHost &ih, hipStream_t s, bool ev, bool pref)
 // beside blocks only on paths that stripes take by choice: on shorter ones they
 // are the slowest form, 400 ms against 30 by blocks on the 512 x 512
 // two-material square.
-int plan_gray_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, InstHost &ih)
+int plan_gray_stripes(const iugkp_problem *p, const iugkp_options *o, InstHost &ih)
 {
   const bool ev = (o->estimator == IUGKP_EST_EXPECTED);
   const bool lam_stripes = ih.d.lam_min >= kStripeMinCells * std::min(p->dx, p->dy);
@@ -935,11 +956,8 @@ int plan_gray_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_
         (!ev && o->tally_faces != IUGKP_FACES_OFF &&
          (o->march >= 2 || (o->march == 0 && (lam_stripes || o->block_size == 0))))))
     return IUGKP_OK;
-  const int rc = plan_stripes(ih, s, ev, o->march >= 2 || lam_stripes);
-  if (rc) return rc;
-  if (o->march >= 2 && ih.stripe_R == 0)
-    return fail(IUGKP_E_INVALID_ARG, "row stripes do not fit this mesh");
-  return IUGKP_OK;
+  const int rc = plan_stripes(ih, ev, o->march >= 2 || lam_stripes);
+  return rc ? rc : stripes_asked(o, ih);
 }
 
 // Row stripes for a band's face-tallied iterations when its free paths reach
@@ -950,12 +968,12 @@ bool stripe_paths(const iugkp_problem *p, double lam)
 {
   return lam >= kStripeMinCells * std::min(p->dx, p->dy) && lam >= 0.5 * p->ny * p->dy;
 }
-int plan_band_stripes(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, InstHost &ih)
+int plan_band_stripes(const iugkp_problem *p, const iugkp_options *o, InstHost &ih)
 {
   if (p->dim != 2 || o->tally_faces == IUGKP_FACES_OFF || o->march == 1 ||
       o->estimator != IUGKP_EST_ANALOG || !stripe_paths(p, ih.d.lam_min))
     return IUGKP_OK;
-  return plan_stripes(ih, s, false, true);
+  return plan_stripes(ih, false, true);
 }
 
 // The domain blocks of a handle of bands with free paths lam and N flights per
@@ -1222,7 +1240,7 @@ int setup_instance(const iugkp_problem *p, const iugkp_options *o, hipStream_t s
       if ((rc = setup_mg(ih, o, s, false))) return rc;
     }
   }
-  if (multi_cg && (rc = plan_gray_stripes(p, o, s, ih))) return rc;
+  if (multi_cg && (rc = plan_gray_stripes(p, o, ih))) return rc;
   if (o->scheme == IUGKP_SCHEME_PERSISTENT) {
     if (!multi_cg) return fail(IUGKP_E_INVALID_ARG, "the persistent scheme is for single solves");
     if ((rc = setup_persistent(ih, T0, gw, s))) return rc;
@@ -1460,7 +1478,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     d.Gs = nullptr;
     plan_tiles(ih);
     if ((rc = split_tiles(ih, K))) return rc;
-    if (stripes && (rc = plan_band_stripes(p, o, s, ih))) return rc;
+    if (stripes && (rc = plan_band_stripes(p, o, ih))) return rc;
     double *dratio = nullptr, *dshare = nullptr;
     ALLOC(ih, dratio, nc);
     ALLOC(ih, dshare, nc);
@@ -1668,11 +1686,13 @@ struct BlockHost {
   iugkp::BlockRun run{};
   int rounds = 0, grid = 0;
   size_t lds = 0, plan_lds = 0;
-  std::vector<void *> allocs;
+  void *mem[3] = {nullptr, nullptr, nullptr};
   void release()
   {
-    for (void *p : allocs) (void)hipFree(p);
-    allocs.clear();
+    for (void *&m : mem) {
+      if (m) (void)hipFree(m);
+      m = nullptr;
+    }
     rounds = 0;
   }
 };
@@ -2124,37 +2144,52 @@ int setup_blocks(iugkp_handle *h)
   int dev = 0, n_cu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  bool ok = true;
+  // one allocation, the arrays 256 bytes apart (each is a driver call, as is its
+  // release); the two record buffers apart from it where that keeps every one
+  // below kCheapBytes, beyond which a release takes 0.3 ms
+  const bool apart = p.record_bytes() > kCheapBytes && p.record_bytes() <= 2 * kCheapBytes;
+  unsigned char *base = nullptr;
+  size_t bytes = 0;
   auto get = [&](auto **q, size_t n) {
-    void *m = nullptr;
-    ok = ok && hipMalloc(&m, std::max<size_t>(n, 1) * sizeof(**q)) == hipSuccess;
-    if (m) b.allocs.push_back(m);
-    *q = static_cast<std::remove_reference_t<decltype(**q)> *>(m);
+    if (base) *q = reinterpret_cast<std::remove_reference_t<decltype(*q)>>(base + bytes);
+    bytes += (std::max<size_t>(n, 1) * sizeof(**q) + 255) / 256 * 256;
   };
   iugkp::BlockRun &r = b.run;
   iugkp::BlockDesc *d_blk = nullptr;
   iugkp::BlockUnit *d_units0 = nullptr;
-  get(&d_blk, p.blk.size());
-  get(&d_units0, p.units.size());
-  get(&r.next, p.rounds);
-  get(&r.rec[1], p.n_chunks * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
-  if (p.rounds > 1) {
-    for (int i = 0; i < 2; ++i) {
-      get(&r.units[i], p.n_units);
-      get(&r.list[i], 4 * p.n_chunks);
+  const size_t rec = p.n_chunks * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4));
+  auto carve = [&] {
+    bytes = 0;
+    get(&d_blk, p.blk.size());
+    get(&d_units0, p.units.size());
+    get(&r.next, p.rounds);
+    if (!apart) get(&r.rec[1], rec);
+    if (p.rounds > 1) {
+      for (int i = 0; i < 2; ++i) {
+        get(&r.units[i], p.n_units);
+        get(&r.list[i], 4 * p.n_chunks);
+      }
+      if (!apart) get(&r.rec[0], rec);
+      get(&r.n_units, 2);
+      get(&r.seg_off, p.T + 1);
+      get(&r.seg_pos, 4 * p.n_units);
+      get(&r.seg_pre, 4 * p.n_units);
     }
-    get(&r.rec[0], p.n_chunks * (iugkp::kChunk * iugkp::kRecBytes / sizeof(uint4)));
-    get(&r.n_units, 2);
-    get(&r.seg_off, p.T + 1);
-    get(&r.seg_pos, 4 * p.n_units);
-    get(&r.seg_pre, 4 * p.n_units);
+    get(&r.out_n, 4 * p.n_units);
+  };
+  carve();
+  bool ok = hipMalloc(&b.mem[0], bytes) == hipSuccess;
+  for (int i = 0; ok && apart && i < (p.rounds > 1 ? 2 : 1); ++i) {
+    ok = hipMalloc(&b.mem[1 + i], rec * sizeof(uint4)) == hipSuccess;
+    r.rec[1 - i] = static_cast<uint4 *>(b.mem[1 + i]);
   }
-  get(&r.out_n, 4 * p.n_units);
   if (!ok) {
     (void)hipGetLastError();
     b.release();
     return IUGKP_E_NOMEM;
   }
+  base = static_cast<unsigned char *>(b.mem[0]);
+  carve();
   r.blk = d_blk;
   r.T = p.T;
   r.target = static_cast<uint32_t>(p.target);
@@ -2292,11 +2327,24 @@ int iugkp_create(const iugkp_problem *problem, const iugkp_options *options, voi
       (rc = setup_blocks(h)) == IUGKP_E_NOMEM) {
     h->ih.blocks = iugkp::BlockPlan{};
     rc = IUGKP_OK;
-    if (!bands && h->ih.stripe_R == 0) rc = plan_gray_stripes(problem, options, h->stream, h->ih);
+    if (!bands && h->ih.stripe_R == 0) rc = plan_gray_stripes(problem, options, h->ih);
     for (int k = 0; bands && k < K && !rc; ++k)
       if (band_of(h, k).stripe_R == 0)
-        rc = plan_band_stripes(problem, options, h->stream, k == 0 ? h->ih : h->xb[k - 1]);
+        rc = plan_band_stripes(problem, options, k == 0 ? h->ih : h->xb[k - 1]);
     choose();
+  }
+  // the stripes' records likewise
+  if (!rc && (h->forms[1].may_run(kFormStripes) || h->forms[1].may_run(kFormPieces))) {
+    bool all = true;
+    for (int k = 0; k < K && !rc; ++k) {
+      InstHost &ih = k == 0 ? h->ih : h->xb[k - 1];
+      const bool had = ih.stripe_R > 0;
+      rc = setup_stripes(ih, h->stream);
+      all = all && (!had || ih.stripe_R > 0);
+    }
+    if (!all) choose();
+    if (!rc && !bands && options->scheme == IUGKP_SCHEME_EMITTERS && problem->dim == 2)
+      rc = stripes_asked(options, h->ih);
   }
   if (rc) {
     free_handle(h);
