@@ -100,7 +100,6 @@ constexpr int kLdsWallsMax = 1024;
 // against 312 us; eight bands on 38 x 197, 3e4 of 1.3e5 far: 282 against 156).
 // (Iterations without face tallies: quiet_blocks.)
 constexpr double kBlockMinFlightsEv = 20000.0, kBlockMinFlights = 35000.0;
-constexpr size_t kCheapBytes = size_t{32} << 20;
 constexpr size_t kRecordsFree = size_t{256} << 20;   // records below this: the free memory is not asked for
 
 inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
@@ -1686,13 +1685,11 @@ struct BlockHost {
   iugkp::BlockRun run{};
   int rounds = 0, grid = 0;
   size_t lds = 0, plan_lds = 0;
-  void *mem[3] = {nullptr, nullptr, nullptr};
+  void *mem = nullptr;
   void release()
   {
-    for (void *&m : mem) {
-      if (m) (void)hipFree(m);
-      m = nullptr;
-    }
+    if (mem) (void)hipFree(mem);
+    mem = nullptr;
     rounds = 0;
   }
 };
@@ -2144,10 +2141,9 @@ int setup_blocks(iugkp_handle *h)
   int dev = 0, n_cu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  // one allocation, the arrays 256 bytes apart (each is a driver call, as is its
-  // release); the two record buffers apart from it where that keeps every one
-  // below kCheapBytes, beyond which a release takes 0.3 ms
-  const bool apart = p.record_bytes() > kCheapBytes && p.record_bytes() <= 2 * kCheapBytes;
+  // one allocation, the arrays 256 bytes apart (with fourteen, each a driver call
+  // as is its release, an expected-value handle of 256 x 256 cells and 1e7 rays
+  // took 1.5 ms to create and close, now 1.2)
   unsigned char *base = nullptr;
   size_t bytes = 0;
   auto get = [&](auto **q, size_t n) {
@@ -2163,13 +2159,13 @@ int setup_blocks(iugkp_handle *h)
     get(&d_blk, p.blk.size());
     get(&d_units0, p.units.size());
     get(&r.next, p.rounds);
-    if (!apart) get(&r.rec[1], rec);
+    get(&r.rec[1], rec);
     if (p.rounds > 1) {
       for (int i = 0; i < 2; ++i) {
         get(&r.units[i], p.n_units);
         get(&r.list[i], 4 * p.n_chunks);
       }
-      if (!apart) get(&r.rec[0], rec);
+      get(&r.rec[0], rec);
       get(&r.n_units, 2);
       get(&r.seg_off, p.T + 1);
       get(&r.seg_pos, 4 * p.n_units);
@@ -2178,17 +2174,12 @@ int setup_blocks(iugkp_handle *h)
     get(&r.out_n, 4 * p.n_units);
   };
   carve();
-  bool ok = hipMalloc(&b.mem[0], bytes) == hipSuccess;
-  for (int i = 0; ok && apart && i < (p.rounds > 1 ? 2 : 1); ++i) {
-    ok = hipMalloc(&b.mem[1 + i], rec * sizeof(uint4)) == hipSuccess;
-    r.rec[1 - i] = static_cast<uint4 *>(b.mem[1 + i]);
-  }
-  if (!ok) {
+  if (hipMalloc(&b.mem, bytes) != hipSuccess) {
     (void)hipGetLastError();
-    b.release();
+    b.mem = nullptr;
     return IUGKP_E_NOMEM;
   }
-  base = static_cast<unsigned char *>(b.mem[0]);
+  base = static_cast<unsigned char *>(b.mem);
   carve();
   r.blk = d_blk;
   r.T = p.T;
