@@ -57,8 +57,8 @@ constexpr int kCgGridMax = 64;               // workgroups of one CG group (barr
 // its level 1 (its phases wait for the loads of a few cells per thread one after
 // another): as many as one XCD holds while the solve's vectors stay in its L2
 // (up to kMgXcdBlocks blocks of 256 cells), beyond that kMgGroupMax anywhere (a
-// workgroup fills a CU, and the groups of four hardware queues have to fit the
-// device at once).
+// workgroup fills a CU: the groups of four hardware queues fit the device at
+// once, and where more ask for it those that wait run on fewer, elect_group).
 // us per solve on 32 in one XCD / more anywhere: 160 x 160 cells 577 / 667, 224 x
 // 224 776 / 789, 256 x 256 904 / 795; 512 x 512 on 32 / 64 / 128 3120 / 2600 / 2070;
 // 128 x 128 on 8 / 32 559 / 432.

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "device_core.hpp"
+#include "plan.hpp"
 
 namespace iugkp {
 
@@ -2367,26 +2368,31 @@ __device__ __forceinline__ bool flag_barrier(unsigned int *words, unsigned int *
 // every XCD a chance to hold a whole group: the first XCD on which G of them
 // have arrived takes the solve and the others leave.  Where none gets there
 // within kElectTicks (other kernels hold CUs), the first G to arrive anywhere
-// take it, with device-wide stores.  Members are resident when they are
-// chosen, so no group waits for a workgroup that has not been dispatched; an
-// election without G arrivals ends after the barrier's spin limit.
+// take it, with device-wide stores; of a launch of G, all of them.  Members are
+// resident when they are chosen, so no group waits for a workgroup that has not
+// been dispatched.
+// Groups that are partly there can keep each other waiting (many streams, or
+// processes that share the device).  A solve that any number of workgroups can
+// run (fewer: the multigrid CG, whose values do not depend on its group) is then
+// taken by those that have come within kElectPatience, longer than another
+// kernel's workgroups usually hold their CUs; any other election without G
+// arrivals ends after the barrier's spin limit.
 // words (zero at the launch): [2] the choice, [3] arrivals, [4 + xcc] arrivals
 // on that XCD; [0] and [1] are the group barrier's.
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;
 constexpr int kCusPerXcd = 32;
 constexpr int kGroupWords = 32;
-constexpr unsigned int kElectSpread = 0x100u, kElectFailed = 0x200u;
-constexpr unsigned long long kElectTicks = 2000;     // 20 us of the 100 MHz clock
 
-__device__ __forceinline__ bool elect_group(unsigned int *words, int G, int &rank, bool &one_xcd,
-                                            DevScalars *sc)
+__device__ __forceinline__ bool elect_group(unsigned int *words, int &G, bool fewer, int &rank,
+                                            bool &one_xcd, DevScalars *sc)
 {
-  __shared__ int s_rank, s_one;
+  __shared__ int s_rank, s_one, s_size;
   if (threadIdx.x == 0) {
     unsigned int xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     xcc &= 15u;
+    const bool may_xcd = static_cast<int>(gridDim.x) > G;
     const int ta = static_cast<int>(__hip_atomic_fetch_add(words + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     const int tx = static_cast<int>(__hip_atomic_fetch_add(words + 4 + xcc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     auto propose = [&](unsigned int v) {
@@ -2394,32 +2400,31 @@ __device__ __forceinline__ bool elect_group(unsigned int *words, int G, int &ran
       return __hip_atomic_compare_exchange_strong(words + 2, &none, v, __ATOMIC_RELAXED,
                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    if (tx == G - 1) propose(1u + xcc);
     const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
-    unsigned int choice = 0u;
+    unsigned int v = elect_proposal(xcc, ta, tx, G, may_xcd, fewer, 0ull, 0u), choice = 0u;
     long spins = 0;
     for (;;) {
+      if (v) propose(v);
       choice = __hip_atomic_load(words + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (choice) break;
-      if (static_cast<unsigned long long>(wall_clock64()) - t0 > kElectTicks &&
-          __hip_atomic_load(words + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
-              static_cast<unsigned int>(G))
-        propose(kElectSpread);
+      const unsigned long long waited = static_cast<unsigned long long>(wall_clock64()) - t0;
+      if (waited > kElectTicks)
+        v = elect_proposal(xcc, ta, tx, G, may_xcd, fewer, waited,
+                           __hip_atomic_load(words + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       if (++spins > kBarrierSpinLimit && propose(kElectFailed)) {
         sc->cg_iters = 0;
         sc->cg_status = -3;
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    int r = -1;
-    if (choice == kElectSpread) r = ta < G ? ta : -1;
-    else if (choice == 1u + xcc) r = tx < G ? tx : -1;
-    s_rank = r;
-    s_one = choice != kElectSpread;
+    s_rank = elect_rank(choice, xcc, ta, tx, G);
+    s_one = choice < kElectSpread;
+    s_size = elect_size(choice, G);
   }
   __syncthreads();
-  rank = s_rank;
-  one_xcd = s_one != 0;
+  rank = __builtin_amdgcn_readfirstlane(s_rank);
+  one_xcd = __builtin_amdgcn_readfirstlane(s_one) != 0;
+  G = __builtin_amdgcn_readfirstlane(s_size);
   return rank >= 0;
 }
 
@@ -2987,7 +2992,7 @@ __global__ __launch_bounds__(kCgThreadsMax) void cg_kernel(CGArgs a, int G)
 {
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, false, rank, one_xcd, a.sc)) return;
   if (one_xcd) cg_reg_run<kSpanXcd, true>(a, rank, G);
   else cg_reg_run<kSpanDevice, true>(a, rank, G);
 }

@@ -1182,8 +1182,8 @@ __device__ __forceinline__ void mgcg_solve(const MGArgs &in, int G, int bid, dou
 
 namespace iugkp {
 
-// The single solve's group of G workgroups; more are launched where the group
-// may find room on one XCD (elect_group).
+// The single solve's group of G workgroups, elected (elect_group), of more where
+// the group may find room on one XCD; of fewer than G where they do not come.
 __global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
 {
   extern __shared__ double lds[];
@@ -1191,7 +1191,7 @@ __global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
   __shared__ MGLevel s_lv[kMgLevelsMax];
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (G > 1 && !elect_group(a.barrier, G, true, rank, one_xcd, a.sc)) return;
   if (one_xcd) mgcg_solve<kSpanXcd>(a, G, rank, lds, red, s_lv);
   else mgcg_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
 }
@@ -1217,7 +1217,7 @@ __global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int
   __shared__ MGLevel s_lv[kMgLevelsMax];
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, rank, one_xcd, a.sc)) return;
+  if (G > 1 && !elect_group(a.barrier, G, true, rank, one_xcd, a.sc)) return;
   if (one_xcd) mgcg_band_solve<kSpanXcd, 2, 1>(a, G, rank, lds, red, s_lv);
   else mgcg_band_solve<kSpanDevice, 2, 1>(a, G, rank, lds, red, s_lv);
 }

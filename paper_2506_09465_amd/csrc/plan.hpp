@@ -175,6 +175,40 @@ inline int bands_form(bool stripes, double flights, int T, int rounds)
 }
 
 // ---------------------------------------------------------------------------
+// The workgroups of a CG solve's group, elected on the device (elect_group in
+// kernels.hpp): what a workgroup proposes, and who belongs to the group.  The
+// first proposal holds.
+// ---------------------------------------------------------------------------
+constexpr unsigned kElectSpread = 0x100u, kElectFailed = 0x200u, kElectFewer = 0x10000u;
+constexpr unsigned long long kElectTicks = 2000;         // 20 us of the 100 MHz clock
+constexpr unsigned long long kElectPatience = 1000000;   // 10 ms
+
+// A workgroup's proposal after `waited` ticks, 0 for none: the ta-th to arrive
+// anywhere and the tx-th on its XCD xcc, `arrivals` of a group of G being there.
+// may_xcd: enough workgroups are launched for a whole group on one XCD; fewer:
+// any number of workgroups can run the solve.
+constexpr unsigned elect_proposal(unsigned xcc, int ta, int tx, int G, bool may_xcd, bool fewer,
+                                  unsigned long long waited, unsigned arrivals)
+{
+  if (tx == G - 1) return 1u + xcc;
+  if (!may_xcd && ta == G - 1) return kElectSpread;
+  if (waited > kElectTicks && arrivals >= static_cast<unsigned>(G)) return kElectSpread;
+  if (fewer && waited > kElectPatience) return kElectFewer + arrivals;
+  return 0u;
+}
+// its rank in the group chosen, -1: it leaves
+constexpr int elect_rank(unsigned choice, unsigned xcc, int ta, int tx, int G)
+{
+  if (choice >= kElectFewer) return ta < static_cast<int>(choice - kElectFewer) ? ta : -1;
+  if (choice == kElectSpread) return ta < G ? ta : -1;
+  return choice == 1u + xcc && tx < G ? tx : -1;
+}
+constexpr int elect_size(unsigned choice, int G)
+{
+  return choice >= kElectFewer ? static_cast<int>(choice - kElectFewer) : G;
+}
+
+// ---------------------------------------------------------------------------
 // Domain blocks (blocks.hpp): how a mesh is cut, and what the rounds can need.
 // ---------------------------------------------------------------------------
 constexpr int kChunk = 64;                 // records per chunk

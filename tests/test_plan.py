@@ -2,6 +2,7 @@
 with g++ and asked directly, no GPU."""
 import ctypes as C
 import os
+import random
 import shutil
 import subprocess
 
@@ -48,6 +49,14 @@ int quiet(const double *lam, int K, double flights, int T)
   const std::vector<double> b(lam, lam + K);
   return (quiet_blocks(b, flights, T) ? 1 : 0) | (quiet_blocks_first(b, flights) ? 2 : 0);
 }
+
+unsigned propose(unsigned xcc, int ta, int tx, int G, int may_xcd, int fewer, uint64_t waited,
+                 unsigned arrivals)
+{
+  return elect_proposal(xcc, ta, tx, G, may_xcd != 0, fewer != 0, waited, arrivals);
+}
+int rank(unsigned choice, unsigned xcc, int ta, int tx, int G) { return elect_rank(choice, xcc, ta, tx, G); }
+int size(unsigned choice, int G) { return elect_size(choice, G); }
 
 // record bytes of a step, and whether they fit this much free memory
 int64_t records(int nx, int ny, int K, uint32_t N, int64_t free_bytes, int *fit)
@@ -172,6 +181,10 @@ def plan(tmp_path_factory):
                            C.c_void_p]
     lib.quiet.restype = C.c_int
     lib.quiet.argtypes = [C.c_void_p, C.c_int, C.c_double, C.c_int]
+    lib.propose.restype = C.c_uint
+    lib.propose.argtypes = [C.c_uint, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_uint64, C.c_uint]
+    lib.rank.argtypes = [C.c_uint, C.c_uint, C.c_int, C.c_int, C.c_int]
+    lib.size.argtypes = [C.c_uint, C.c_int]
     lib.records.restype = C.c_int64
     lib.records.argtypes = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int64, C.POINTER(C.c_int)]
     lib.bands.restype = C.c_int
@@ -285,3 +298,66 @@ def test_block_records_leave_room(plan):
         b = plan.records(512, 512, 1, N, free, C.byref(fit))
         assert 1.0 <= b / (128.0 * ne * N) < 1.1
         assert fit.value == want == (b <= free // 8)
+
+
+def _run_groups(plan, groups, fewer, seed, slots=256, xcds=8, ticks=1000, steps=4000):
+    """Groups (launched, wanted) of workgroups of a CU each on one device, their
+    dispatches interleaved at random, `ticks` of the clock a step: the sizes that
+    ran, or None for a group that never did."""
+    rng = random.Random(seed)
+    queue = [g for g, (launch, _) in enumerate(groups) for _ in range(launch)]
+    rng.shuffle(queue)
+    free = [slots // xcds] * xcds
+    ran = [None] * len(groups)
+    choice, arrived, on_xcd = [0] * len(groups), [0] * len(groups), [[0] * xcds for _ in groups]
+    waiting, members = [], [[] for _ in groups]
+    for step in range(steps):
+        for x in range(xcds):
+            while free[x] and queue:
+                g = queue.pop()
+                free[x] -= 1
+                waiting.append((g, x, arrived[g], on_xcd[g][x], step))
+                arrived[g] += 1
+                on_xcd[g][x] += 1
+        still = []
+        for g, x, ta, tx, t0 in waiting:
+            launch, want = groups[g]
+            if not choice[g]:
+                choice[g] = plan.propose(x, ta, tx, want, int(launch > want), fewer, ticks * (step - t0),
+                                         arrived[g])
+            if not choice[g]:
+                still.append((g, x, ta, tx, t0))
+            elif plan.rank(choice[g], x, ta, tx, want) >= 0:
+                members[g].append((x, plan.rank(choice[g], x, ta, tx, want)))
+            else:
+                free[x] += 1
+        waiting = still
+        for g, (launch, want) in enumerate(groups):
+            n = plan.size(choice[g], want) if choice[g] else 0
+            if n and len(members[g]) == n:                       # (every barrier is met)
+                assert sorted(r for _, r in members[g]) == list(range(n))
+                if choice[g] < 0x100:
+                    assert len({x for x, _ in members[g]}) == 1
+                for x, _ in members[g]:
+                    free[x] += 1
+                members[g], ran[g] = [], n
+        if all(ran):
+            break
+    return ran
+
+
+@pytest.mark.parametrize("groups", [
+    [(64, 64)] * 4, [(64, 64)] * 9, [(256, 32)] * 9, [(64, 64)] * 5 + [(256, 32)] * 6 + [(128, 16)] * 4,
+    [(200, 200)] * 3,
+])
+def test_elected_groups_never_keep_each_other_waiting(plan, groups):
+    """However the workgroups of several solves are dispatched, each solve runs:
+    whole where they fit together, on fewer workgroups where they do not."""
+    for seed in range(6):
+        ran = _run_groups(plan, groups, 1, seed)
+        assert all(ran), (seed, ran)
+        assert all(1 <= n <= want for n, (_, want) in zip(ran, groups))
+        if sum(launch for launch, _ in groups) <= 256:
+            assert ran == [want for _, want in groups]
+    if groups == [(200, 200)] * 3:          # (only whole groups: they never run)
+        assert not all(_run_groups(plan, groups, 0, 0))
