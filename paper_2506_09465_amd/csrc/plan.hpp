@@ -11,24 +11,27 @@ namespace iugkp {
 
 // A tile's particles are split over several workgroups where the tiles alone
 // leave compute units idle (a 100-cell film has 15): up to kSplitTarget
-// workgroups per launch (two per compute unit), kSplitTargetNull with null
-// collisions, whose chains differ in length, of at least kSplitMin particles
-// (one per lane) and of one particle per kSplitWords words of LDS window, which
-// every workgroup clears and flushes; and where the tiles fit the device at
-// once, so do their shares (a second round of workgroups waits for the first:
-// 164 x 161 cells, 286 workgroups of a CU's LDS each, 47 us against 35 unsplit;
-// with null collisions a second round evens the chains out: 115 x 190, path 1.3
-// cells, ratio 180, 3.8 ms against 5.5 with the limit; 199 x 74, path 350, ratio
-// 23, with face tallies 0.50 against 0.80).
+// workgroups per launch (two per compute unit), kSplitTargetMore where their
+// shares are heavy (of half a particle per word of LDS window, which every
+// workgroup clears and flushes: 192 x 192 cells, 60 particles per emitter 111 us
+// against 121, with 15 61 against 81) and with null collisions, whose chains
+// differ in length; of at least kSplitMin particles (one per lane) and of one per
+// kSplitWords words.  Where the tiles fit the device at once, so do their shares:
+// a second round of workgroups waits for the first (164 x 161 cells, 286
+// workgroups of a CU's LDS each, 47 us against 35 unsplit; with null collisions a
+// second round evens the chains out: 115 x 190, path 1.3 cells, ratio 180, 3.8
+// ms against 5.5 with the limit; 199 x 74, path 350, ratio 23, with face tallies
+// 0.50 against 0.80).
 // Measured: film of 100 cells, 1e5 particles, particle step 658 -> 30 us (512 /
 // 2048 particles at least: 27 / 38 us, but the two-time film's solve 1.85 ms
 // against 2.2 / 3.0); 61 x 45 cells, 3e5 particles 104 -> 46 us; 128 x 100 with
 // null collisions, 1e6 particles 1188 -> 729 us (one particle per 4 or 2 words:
 // 806 / 1182).  Cavities of 24 .. 400 cells a side without null collisions,
 // time against unsplit tiles, geometric mean and worst: without face tallies
-// 0.88 and 1.24 (target 1024 and no limit: 0.92 and 1.41), with them 0.93 and
-// 1.11 (0.94 and 1.13).
-constexpr int kSplitTarget = 512, kSplitTargetNull = 1024;
+// 0.89 and 1.25 (target 1024 and no limit: 0.92 and 1.42), with them 0.93 and
+// 1.08 (0.94 and 1.24).
+constexpr int kSplitTarget = 512, kSplitTargetMore = 1024;
+constexpr double kSplitHeavy = 0.5;
 constexpr int kSplitMin = 256;
 constexpr int kSplitWords = 8;
 
@@ -44,7 +47,8 @@ inline double split_chunk(const std::vector<double> &tiles, size_t lds_words, bo
 {
   double all = 0.0;
   for (double p : tiles) all += p;
-  const int target = std::max(1, (has_null ? kSplitTargetNull : kSplitTarget) / K);
+  const bool more = has_null || all * K >= kSplitTargetMore * kSplitHeavy * static_cast<double>(lds_words);
+  const int target = std::max(1, (more ? kSplitTargetMore : kSplitTarget) / K);
   double chunk = std::max({all / target, static_cast<double>(kSplitMin),
                            static_cast<double>(lds_words) / kSplitWords});
   const size_t per_cu = std::min<size_t>(8, std::max<size_t>(1, lds_max / std::max<size_t>(1, 8 * lds_words)));
