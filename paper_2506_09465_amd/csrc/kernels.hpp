@@ -2373,7 +2373,7 @@ __device__ __forceinline__ bool flag_barrier(unsigned int *words, unsigned int *
 // been dispatched.
 // Groups that are partly there can keep each other waiting (many streams, or
 // processes that share the device).  A solve that any number of workgroups can
-// run (fewer: the multigrid CG, whose values do not depend on its group) is then
+// run (FEWER: the multigrid CG, whose values do not depend on its group) is then
 // taken by those that have come within kElectPatience, longer than another
 // kernel's workgroups usually hold their CUs; any other election without G
 // arrivals ends after the barrier's spin limit.
@@ -2384,33 +2384,40 @@ constexpr int kXcds = 8;
 constexpr int kCusPerXcd = 32;
 constexpr int kGroupWords = 32;
 
-__device__ __forceinline__ bool elect_group(unsigned int *words, int &G, bool fewer, int &rank,
-                                            bool &one_xcd, DevScalars *sc)
+template <bool FEWER>
+__device__ __forceinline__ bool elect_group(unsigned int *words, int &G, int &rank, bool &one_xcd,
+                                            DevScalars *sc)
 {
   __shared__ int s_rank, s_one, s_size;
   if (threadIdx.x == 0) {
     unsigned int xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     xcc &= 15u;
-    const bool may_xcd = static_cast<int>(gridDim.x) > G;
+    // (places on an XCD are counted where one may hold the group)
+    const bool may_xcd = !FEWER || static_cast<int>(gridDim.x) > G;
     const int ta = static_cast<int>(__hip_atomic_fetch_add(words + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const int tx = static_cast<int>(__hip_atomic_fetch_add(words + 4 + xcc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    int tx = -1;
+    if (may_xcd)
+      tx = static_cast<int>(__hip_atomic_fetch_add(words + 4 + xcc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     auto propose = [&](unsigned int v) {
       unsigned int none = 0u;
       return __hip_atomic_compare_exchange_strong(words + 2, &none, v, __ATOMIC_RELAXED,
                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    if (const unsigned int v = elect_proposal(xcc, ta, tx, G, may_xcd, FEWER, 0ull, 0u)) propose(v);
     const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
-    unsigned int v = elect_proposal(xcc, ta, tx, G, may_xcd, fewer, 0ull, 0u), choice = 0u;
+    unsigned int choice = 0u;
     long spins = 0;
     for (;;) {
-      if (v) propose(v);
       choice = __hip_atomic_load(words + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (choice) break;
       const unsigned long long waited = static_cast<unsigned long long>(wall_clock64()) - t0;
-      if (waited > kElectTicks)
-        v = elect_proposal(xcc, ta, tx, G, may_xcd, fewer, waited,
+      if (waited > kElectTicks) {
+        const unsigned int v =
+            elect_proposal(xcc, ta, tx, G, may_xcd, FEWER, waited,
                            __hip_atomic_load(words + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (v) propose(v);
+      }
       if (++spins > kBarrierSpinLimit && propose(kElectFailed)) {
         sc->cg_iters = 0;
         sc->cg_status = -3;
@@ -2419,12 +2426,12 @@ __device__ __forceinline__ bool elect_group(unsigned int *words, int &G, bool fe
     }
     s_rank = elect_rank(choice, xcc, ta, tx, G);
     s_one = choice < kElectSpread;
-    s_size = elect_size(choice, G);
+    if (FEWER) s_size = elect_size(choice, G);
   }
   __syncthreads();
-  rank = __builtin_amdgcn_readfirstlane(s_rank);
-  one_xcd = __builtin_amdgcn_readfirstlane(s_one) != 0;
-  G = __builtin_amdgcn_readfirstlane(s_size);
+  rank = s_rank;
+  one_xcd = s_one != 0;
+  if (FEWER) G = __builtin_amdgcn_readfirstlane(s_size);
   return rank >= 0;
 }
 
@@ -2992,7 +2999,7 @@ __global__ __launch_bounds__(kCgThreadsMax) void cg_kernel(CGArgs a, int G)
 {
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (static_cast<int>(gridDim.x) > G && !elect_group(a.barrier, G, false, rank, one_xcd, a.sc)) return;
+  if (static_cast<int>(gridDim.x) > G && !elect_group<false>(a.barrier, G, rank, one_xcd, a.sc)) return;
   if (one_xcd) cg_reg_run<kSpanXcd, true>(a, rank, G);
   else cg_reg_run<kSpanDevice, true>(a, rank, G);
 }

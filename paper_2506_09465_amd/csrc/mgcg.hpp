@@ -1191,7 +1191,7 @@ __global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
   __shared__ MGLevel s_lv[kMgLevelsMax];
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (G > 1 && !elect_group(a.barrier, G, true, rank, one_xcd, a.sc)) return;
+  if (G > 1 && !elect_group<true>(a.barrier, G, rank, one_xcd, a.sc)) return;
   if (one_xcd) mgcg_solve<kSpanXcd>(a, G, rank, lds, red, s_lv);
   else mgcg_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
 }
@@ -1217,7 +1217,7 @@ __global__ __launch_bounds__(kMgBandThreads) void mgcg_band_kernel(MGArgs a, int
   __shared__ MGLevel s_lv[kMgLevelsMax];
   int rank = blockIdx.x;
   bool one_xcd = false;
-  if (G > 1 && !elect_group(a.barrier, G, true, rank, one_xcd, a.sc)) return;
+  if (G > 1 && !elect_group<true>(a.barrier, G, rank, one_xcd, a.sc)) return;
   if (one_xcd) mgcg_band_solve<kSpanXcd, 2, 1>(a, G, rank, lds, red, s_lv);
   else mgcg_band_solve<kSpanDevice, 2, 1>(a, G, rank, lds, red, s_lv);
 }
