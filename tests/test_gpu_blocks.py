@@ -7,7 +7,7 @@ import pytest
 
 from synth import cavity_2d, nongray_two_material_2d, seeded_temperature, two_material_2d
 from test_gpu_bands import _same_state
-from test_gpu_launch import _same_cells
+from test_gpu_launch import BLOCKS, _same_cells
 from test_gpu_parity import _pair, _same_iteration
 
 pytestmark = pytest.mark.gpu
@@ -217,3 +217,30 @@ def test_records_are_held_only_while_a_form_needs_them(gpu):
     assert mb < {"blocks": 170, "stripes": 125, "tiles512": 40}[form]
     mb, again = held(1, kn=0.3, tally_faces=gpu.FACES_EVERY, n=142)     # known from the start
     assert again == form and mb < {"blocks": 170, "stripes": 125, "tiles512": 40}[form]
+
+
+@pytest.mark.parametrize("name", list(BLOCKS))
+@pytest.mark.parametrize("faces", [True, False])
+def test_blocks_run_where_they_are_meant_to(oracle_mod, gpu, name, faces):
+    """The domain-block cases again, over enough iterations that blocks run twice
+    (rays: in every one), on states that blocks have made as well."""
+    make, kw = BLOCKS[name]
+    w = make()
+    kw = dict({"T_init": seeded_temperature(w.n_cells)}, **kw)
+    if isinstance(kw["T_init"], str):       # (only the walls emit at first)
+        kw["T_init"] = np.full(w.n_cells, w.t_ref)
+    mode = oracle_mod.FACES_EVERY if faces else oracle_mod.FACES_OFF
+    o, s = _pair(oracle_mod, gpu, w, tally_faces=mode, **kw)
+    ran = []
+    for i in range(5):
+        assert o.step(1) == 0 and s.step(1) == 0
+        ran.append(s.march_form())
+        (_same_iteration if faces else _same_cells)(o, s, f"{name} it{i} {ran}")
+    if "estimator" in kw:
+        assert ran == ["blocks"] * 5
+    elif faces:
+        assert ran.count("blocks") >= 2 or set(ran) >= {"stripes", "blocks"}, ran
+    elif name in ("null_few_flights", "null_no_weight"):    # (paths of 14 cells, cold at first)
+        assert ran[0] == "tiles256"
+    else:
+        assert ran.count("blocks") >= 1, ran
