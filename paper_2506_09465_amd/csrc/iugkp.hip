@@ -1423,7 +1423,7 @@ int setup_bands(const iugkp_problem *p, const iugkp_options *o, hipStream_t s, I
     bool all_long = true;
     for (int k = 0; k < K; ++k) all_long = all_long && stripe_paths(p, lam[k]);
     ih0.band_form = iugkp::bands_form(all_long, all, ih0.blocks.T, ih0.blocks.rounds);
-    ih0.band_timed = iugkp::bands_timed(all, ih0.blocks.T);
+    ih0.band_timed = iugkp::bands_timed(all_long, all, ih0.blocks.T);
     stripes = all_long && ih0.band_timed;
   }
   auto band = [&](int k) -> InstHost & { return k == 0 ? ih0 : rest[k - 1]; };
@@ -2226,9 +2226,7 @@ void plan_forms(iugkp_handle *h)
     if (iugkp::quiet_blocks(lam, flights, ih.blocks.T)) {
       off.def = iugkp::quiet_blocks_first(lam, flights) ? kFormBlocks : kFormTiles256;
       off.cand = {kFormTiles256, kFormBlocks};
-      // (an iteration's longest chain of null collisions sets the tiles' time:
-      // 125 x 66 cells, ratio 187, 0.36 to 0.86 ms from one to the next)
-      off.rounds = 3;
+      off.rounds = iugkp::timed_rounds(flights * h->bh.K);
       known(0);
     }
   }
@@ -2243,7 +2241,7 @@ void plan_forms(iugkp_handle *h)
       if (ih.band_timed) {
         on.cand = {kFormTiles256, kFormBlocks};
         if (all) on.cand.push_back(kFormStripes);
-        on.rounds = 3;
+        on.rounds = iugkp::timed_rounds(static_cast<double>(h->bh.K) * m.n_emit * ih.d.N);
         known(1);
       }
     }

@@ -123,6 +123,12 @@ struct FormSearch {
   }
 };
 
+// An iteration of fewer flights takes a few ms in any form, and its longest chain
+// of null collisions sets its time (125 x 66 cells, ratio 187, by tiles 0.36 to
+// 0.86 ms from one to the next): its forms are timed three times over.
+constexpr double kFewFlights = 3e6;
+inline int timed_rounds(double flights) { return flights < kFewFlights ? 3 : 1; }
+
 // Iterations without face tallies: the tile march resolves long segments in
 // closed form and sends few tallies out of its windows, so blocks can only win
 // on short ones, and where the line lies depends on how evenly the tiles share
@@ -132,9 +138,9 @@ struct FormSearch {
 // win: half of the flights on paths below kQuietCells, and enough of them for a
 // block (of 1700 drawn problems blocks were more than 7% faster in none that
 // this leaves out).  The first iterations run by blocks where they mostly win:
-// half of the flights on paths below kQuietFirst, kQuietFlights in all.
+// half of the flights on paths below kQuietFirst, kFewFlights in all.
 constexpr double kQuietCells = 24.0, kQuietPerBlock = 5e3;
-constexpr double kQuietFirst = 16.0, kQuietFlights = 3e6;
+constexpr double kQuietFirst = 16.0;
 
 // the share of the bands on paths (in cells) below `cells`
 inline double short_paths(const std::vector<double> &lam, double cells)
@@ -153,7 +159,7 @@ inline bool quiet_blocks(const std::vector<double> &lam, double flights, int T)
 inline bool quiet_blocks_first(const std::vector<double> &lam, double flights)
 {
   return short_paths(lam, kQuietFirst) >= 0.5 &&
-         flights * static_cast<double>(lam.size()) >= kQuietFlights;
+         flights * static_cast<double>(lam.size()) >= kFewFlights;
 }
 
 // Frequency bands, iterations with face tallies: blocks, row stripes for the bands
@@ -166,15 +172,22 @@ inline bool quiet_blocks_first(const std::vector<double> &lam, double flights)
 // against 1.23).  Over 127 drawn problems 1.6% from the fastest of the three in
 // the geometric mean, always blocks 8%, never blocks 54%.  With few flights a
 // block the lines are not sharp (40 bands of 78 x 179, 1.9e4 a block, ratio 3:
-// 0.41 ms by blocks, 0.59 by tiles): there the forms are timed, at little cost.
+// 0.41 ms by blocks, 0.59 by tiles): there the forms are timed, at little cost;
+// with kFewFlights or more, blocks were the fastest in every problem whose bands
+// do not all have long paths (where they do, also with more flights a block: two
+// bands of 290 x 34, 1.5e5 a block, 0.31 ms with stripes, 0.41 by blocks).
 constexpr int kBandRounds = 4;
 constexpr double kBandPerBlock = 2e4, kBandPerBlockTimed = 1e5;
 
 // flights: of all bands; T: blocks of all bands
-inline bool bands_timed(double flights, int T) { return flights < kBandPerBlockTimed * T; }
+inline bool bands_timed(bool stripes, double flights, int T)
+{
+  const bool few = flights < kBandPerBlockTimed * T;
+  return stripes ? few || flights < kFewFlights : few && flights < kFewFlights;
+}
 inline int bands_form(bool stripes, double flights, int T, int rounds)
 {
-  if (stripes && rounds >= kBandRounds && bands_timed(flights, T)) return kFormStripes;
+  if (stripes && rounds >= kBandRounds && flights < kBandPerBlockTimed * T) return kFormStripes;
   return rounds >= kBandRounds || flights >= kBandPerBlock * T ? kFormBlocks : kFormTiles256;
 }
 

@@ -66,7 +66,10 @@ int64_t records(int nx, int ny, int K, uint32_t N, int64_t free_bytes, int *fit)
   return static_cast<int64_t>(p.record_bytes());
 }
 
-int bands(int stripes, double flights, int T, int rounds) { return bands_form(stripes != 0, flights, T, rounds); }
+int bands(int stripes, double flights, int T, int rounds)
+{
+  return bands_form(stripes != 0, flights, T, rounds) + 10 * bands_timed(stripes != 0, flights, T);
+}
 
 // out: blocks of all bands, rounds, LDS bytes, round 0's units
 void blocks(int nx, int ny, int K, uint32_t N, int null, int faces, int rays, int64_t *out)
@@ -256,10 +259,12 @@ def test_blocks_without_face_tallies(plan, lam, flights, blocks, want):
 
 
 @pytest.mark.parametrize("stripes,flights,blocks,rounds,form", [
-    (1, 7.5e5, 16, 5, 2), (1, 3e6, 16, 5, 4), (1, 6e4, 2, 1, 4), (1, 7e4, 4, 2, 0),
-    (0, 2.3e5, 16, 2, 0), (0, 5e7, 1440, 11, 4), (0, 8.6e5, 56, 10, 4), (0, 4e5, 8, 1, 4),
+    (1, 7.5e5, 16, 5, 12), (1, 2e6, 16, 5, 14), (1, 3.1e6, 16, 5, 4), (1, 6e4, 2, 1, 14), (1, 7e4, 4, 2, 10),
+    (0, 2.3e5, 16, 2, 10), (0, 4.2e7, 1960, 13, 4), (0, 8.6e5, 56, 10, 14), (0, 4e5, 8, 1, 14),
+    (0, 1.1e6, 8, 1, 4), (1, 8e6, 98, 13, 12),
 ])
 def test_form_of_bands_with_face_tallies(plan, stripes, flights, blocks, rounds, form):
+    """(form + 10 where the forms are timed)"""
     assert plan.bands(stripes, flights, blocks, rounds) == form
 
 
