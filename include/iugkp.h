@@ -122,19 +122,21 @@ typedef struct iugkp_options {
   int tally_faces;              /* IUGKP_FACES_* */
   int avg_iters;                /* iterations averaged for the outputs after stopping (>= 0) */
   int block_size;               /* transport kernel workgroup size: 0 (= 256), 64..1024 */
-  int march;                    /* single solves on 2D meshes: 0 automatic (row stripes for
-                                   face-tallied iterations with long free paths, tiles
-                                   otherwise; see iugkp_march_tuning; with null collisions or
-                                   expected-value rays, domain blocks), 1 emitter tiles, 2 row
+  int march;                    /* single solves on 2D meshes: 0 automatic (emitter tiles, row
+                                   stripes for face-tallied iterations with long free paths,
+                                   or domain blocks from 2e4 expected-value rays or 3.5e4
+                                   flights that null collisions take far; measured where that
+                                   is open, see iugkp_march_tuning), 1 emitter tiles, 2 row
                                    stripes (also for the expected-value estimator, with or
                                    without face tallies), 3 row stripes with the y faces cut
                                    into pieces (without null collisions; else as 2).
                                    Persistent scheme: the y faces of face-tallied moves by a
                                    row-stripe pass (2 or 3, or 0 with long free paths) or as
-                                   global atomics in the move (1).  Frequency bands: domain
-                                   blocks where a band has null collisions, else bands
-                                   whose free paths reach half the domain's height run their
-                                   face-tallied iterations by row stripes; march 1: tiles.
+                                   global atomics in the move (1).  Frequency bands: 0 domain
+                                   blocks where enough flights go far and they are not nearly
+                                   empty, else as 2: bands whose free paths reach half the
+                                   domain's height run their face-tallied iterations by row
+                                   stripes, the others by tiles; 1 tiles.
                                    The result does not depend on it */
   int cg_waves;                 /* single solves: 256-cell tree blocks per CG workgroup, 0
                                    (= 4 to 8) or 1..12 with the CG state in registers, -1..-12 with
@@ -303,12 +305,15 @@ int iugkp_get_stats(iugkp_handle *h, iugkp_stats *stats);
  * collisions), 4 = domain blocks; -1 while the handle still measures them.  A
  * 2D gray single solve with the automatic march and the default block size
  * times one face-tallied iteration in each form that may be the fastest (after
- * an untimed first one) and keeps the fastest; later handles of the same mesh,
- * particles per emitter, null-collision setting, free path in cells and mean
- * relaxation time over the smallest (both to half an octave) start with it.
+ * an untimed first one) and keeps the fastest, and bands with few flights for
+ * their blocks three; later handles of the same mesh, particles per emitter,
+ * null-collision setting, free path in cells and mean relaxation time over the
+ * smallest (both to half an octave, of every band) start with it.  (Iterations
+ * without face tallies have a choice of their own, tiles or domain blocks,
+ * measured in the same way.)
  * Every form gives the same tallies bit for bit.  ms (NULL or host float[4]):
  * the measured particle-step milliseconds, -1 where not measured: of forms 0 to
- * 2, then of form 4 with null collisions, of form 3 without.
+ * 2, then of form 4 with null collisions or bands, of form 3 without.
  * Returns 0, or IUGKP_E_INVALID_ARG for a NULL handle. */
 int iugkp_march_tuning(iugkp_handle *h, int *form, float *ms);
 

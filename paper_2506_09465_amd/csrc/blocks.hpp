@@ -13,7 +13,8 @@
 //
 // Why: an emitter tile's window holds the cells around the emitters, and
 // flights that go further (expected-value rays, chains of null collisions)
-// tally through global atomics, which bound the step (2.1e10 of them a second).
+// tally through global atomics, which bound the step (2.1e10 of them a second,
+// of the 2.4e10 that random words of a small array take).
 // Here every tally is an LDS atomic, and a hop costs 128 bytes of traffic.
 //
 // Records are kept in chunks of 64 (a wavefront's load), field by field

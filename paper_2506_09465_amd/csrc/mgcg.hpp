@@ -832,8 +832,8 @@ __device__ __forceinline__ void mg_lds_cycle(const MGLevel *lv, int Lg, int L, d
 }
 
 // The preconditioned CG of one system, run by the G workgroups of a group of
-// which this one is number bid (G = 1: one workgroup alone, its exchanges
-// through workgroup-scope memory operations and workgroup barriers).
+// which this one is number bid (G = 1: one workgroup alone, with workgroup
+// barriers in place of the group's).
 template <int SPAN>
 __device__ __forceinline__ void mgcg_solve(const MGArgs &in, int G, int bid, double *lds,
                                            double *red, MGLevel *s_lv)
