@@ -692,16 +692,27 @@ int setup_mg(InstHost &ih, const iugkp_options *o, hipStream_t s, bool single)
     band_budget = static_cast<long long>(lds_budget / sizeof(double)) - e_words - rows_words;
     return band_need(1 << 20) <= band_budget;
   };
-  // (rows too long for a window beside the LDS levels: fewer of those)
-  const bool may_band = (Lg == 0 || has_y) && 64 * waves <= iugkp::kMgBandThreads;
+  // (a batch's group: the largest the pool gives it)
+  const int Gw = single ? G : std::min(std::max(G, (m.ny + 1) / 4), kMgPoolGroupMax);
   const int Lg0 = Lg;
-  while (may_band && !band_fits() && Lg > 0 && Lg < L - 1) ++Lg;
-  const bool band = may_band && band_fits();
+  int win[iugkp::kMgBandLevels] = {};
+  if ((Lg == 0 || has_y) && 64 * waves <= iugkp::kMgBandThreads)
+    for (int k = 0; k < iugkp::kMgBandLevels && (k == 0 || (Lg0 > 0 && Lg0 + k < L)); ++k) {
+      Lg = Lg0 + k;
+      if (!band_fits()) continue;
+      const int rows = Lg > 0 ? iugkp::band_up0_blocks(static_cast<int>(band_budget), lv[0].nx, iugkp::kTree) : nb0;
+      win[k] = cdiv(cdiv(nb0, Gw), std::max(rows, 1));
+    }
+  const int more = iugkp::mg_band_level(win, iugkp::kMgBandLevels, nb0);
+  const bool band = more >= 0;
+  Lg = Lg0 + std::max(more, 0);
   if (!band) {
-    Lg = Lg0;
+    // (without windows a batch has the LDS levels of a single solve)
+    for (Lg = 0; Lg < L && lv[Lg].n > iugkp::kMgLocalMax;) ++Lg;
+    while (Lg < L - 1 && local_bytes(Lg) > lds_budget) ++Lg;
     G = G0;
-    band_fits();
   }
+  band_fits();
   const int stage0 = static_cast<int>(e_words + rows_words);
   const long long stage_n =
       band ? std::min(band_budget, band_need(single ? G : 1)) : 0;

@@ -192,6 +192,33 @@ inline int bands_form(bool stripes, double flights, int T, int rounds)
 }
 
 // ---------------------------------------------------------------------------
+// The banded multigrid's first level in LDS.  With more levels there its group
+// passes fewer barriers, but the levels' rows leave less LDS for the windows of a
+// band phase; a window more in the longest phase (the finest prolongation) costs a
+// solve about as much as a level fewer in LDS (460 x 460 cells, the first level
+// that may be / the next: 13 windows and 2, 3.46 / 1.99 ms; 467 x 664: 3 and 2,
+// 2.83 / 2.96).  So the level is taken with the fewest of both together, of at most
+// kMgBandLevels, and where even that is more than kMgBandCost, or kMgBandCostFew on
+// a group that is small, the phases run without bands (banded / not: 720 x 20 cells
+// with 3 levels and 3 windows more 1.71 / 1.11 ms, 720 x 128 with 1 and 3 2.14 /
+// 1.85, 600 x 100 with 2 and 1 1.48 / 1.42; 648 x 256 with 2 and 2 2.02 / 2.35).
+// ---------------------------------------------------------------------------
+constexpr int kMgBandLevels = 3, kMgBandCost = 5, kMgBandCostFew = 3, kMgBandFewBlocks = 400;
+
+// windows[k]: of the finest prolongation, with k levels fewer in LDS than could be
+// there, 0 where no row fits; blocks: of the mesh.  The k to take, -1 for no bands.
+inline int mg_band_level(const int *windows, int n, int blocks)
+{
+  int k = -1, cost = 1 + (blocks <= kMgBandFewBlocks ? kMgBandCostFew : kMgBandCost);
+  for (int i = 0; i < n; ++i)
+    if (windows[i] > 0 && windows[i] - 1 + i < cost) {
+      k = i;
+      cost = windows[i] - 1 + i;
+    }
+  return k;
+}
+
+// ---------------------------------------------------------------------------
 // The workgroups of a CG solve's group, elected on the device (elect_group in
 // kernels.hpp): what a workgroup proposes, and who belongs to the group.  The
 // first proposal holds.

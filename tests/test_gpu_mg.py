@@ -164,3 +164,29 @@ def test_mg_batch_equals_single_solves(gpu, oracle_mod):
     rco, To, qxo, qyo = o.solve()
     assert rco == singles[0][0] and o.info().cg_iters_total == outs[0][3]["cg_iters_total"]
     assert np.array_equal(To, _np(outs[0][0])) and np.array_equal(qxo, _np(outs[0][1]))
+
+
+@pytest.mark.parametrize("nx, ny", [(256, 40), (447, 24), (460, 200), (387, 611), (648, 120),
+                                    (720, 20), (800, 130)])
+def test_mg_first_lds_level(oracle_mod, gpu, nx, ny):
+    """Long rows: the banded form with as many levels in LDS as there may be,
+    with one or two fewer, and the unbanded form, alone and in a batch: the
+    oracle's E, G and iteration count bit for bit."""
+    w = cavity_2d(n=nx, ny=ny, kn=0.05, particles=4 * (nx * ny + 2 * (nx + ny)))
+    Dx, Dy = _diff(w)
+    kw = dict(newton=True, diff_x=Dx, diff_y=Dy, tally_faces=oracle_mod.FACES_OFF,
+              cg_precond=oracle_mod.PRECOND_MG)
+    o = oracle_mod.Oracle(w, **kw)
+    s = gpu.Solver(w, **kw)
+    assert o.step(1) == 0 and s.step(1) == 0
+    _, _, E, G = s.state()
+    assert np.array_equal(o.E(), _np(E)) and np.array_equal(o.G(), _np(G))
+    assert o.info().cg_iters_last == s.stats()["cg_iters_last"]
+    kw.update(max_iters=2, res_tol=1e-30, rng_mode=oracle_mod.CRN)
+    s = gpu.Solver(w, **kw)
+    T = _np(s.solve()[1])
+    b = gpu.BatchSolver([w, w], **kw)
+    outs = b.solve()[1]
+    b.close()
+    for out in outs:
+        assert np.array_equal(T, _np(out[0]))

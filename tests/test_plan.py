@@ -71,6 +71,8 @@ int bands(int stripes, double flights, int T, int rounds)
   return bands_form(stripes != 0, flights, T, rounds) + 10 * bands_timed(stripes != 0, flights, T);
 }
 
+int band_level(const int *windows, int n, int blocks) { return mg_band_level(windows, n, blocks); }
+
 // out: blocks of all bands, rounds, LDS bytes, round 0's units
 void blocks(int nx, int ny, int K, uint32_t N, int null, int faces, int rays, int64_t *out)
 {
@@ -366,3 +368,24 @@ def test_elected_groups_never_keep_each_other_waiting(plan, groups):
             assert ran == [want for _, want in groups]
     if groups == [(200, 200)] * 3:          # (only whole groups: they never run)
         assert not all(_run_groups(plan, groups, 0, 0))
+
+
+# windows of the finest prolongation with 0, 1 and 2 levels fewer in LDS (0: no row
+# fits), tree blocks of the mesh, and the choice that measured fastest or, of two
+# within 5%, either
+@pytest.mark.parametrize("windows, blocks, want", [
+    ((1, 1, 1), 256, 0),      # 256 x 256
+    ((7, 1, 1), 175, 1),      # 447 x 100
+    ((7, 1, 1), 250, 1),      # 400 x 160
+    ((13, 2, 2), 827, 1),     # 460 x 460
+    ((3, 2, 2), 1211, 0),     # 467 x 664: the LDS level is as good as the window
+    ((0, 8, 2), 40, 2),       # the first that fits is not the best
+    ((0, 0, 0), 57, -1),      # 720 x 20: rows too long for two levels more
+    ((0, 0, 4), 124, -1),     # 720 x 44
+    ((0, 4, 4), 360, -1),     # 720 x 128
+    ((0, 6, 3), 648, 2),      # 648 x 256
+    ((0, 4, 3), 63, -1),      # 800 x 20 of a batch
+])
+def test_banded_multigrid_level(plan, windows, blocks, want):
+    w = np.array(windows, dtype=np.int32)
+    assert plan.band_level(w.ctypes.data_as(C.POINTER(C.c_int)), len(w), blocks) == want
