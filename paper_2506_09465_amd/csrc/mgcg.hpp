@@ -1196,7 +1196,7 @@ __global__ __launch_bounds__(kCgThreadsMax) void mgcg_kernel(MGArgs a, int G)
   else mgcg_solve<kSpanDevice>(a, G, rank, lds, red, s_lv);
 }
 
-// the banded form (mgband.hpp), for the meshes whose rows fit its windows;
+// the banded form (mgband.hpp), for the meshes whose rows leave it few windows;
 // workgroups of at most kMgBandThreads threads, whose lanes then have the
 // registers its batched loads take
 constexpr int kMgBandThreads = 512;
